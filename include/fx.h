@@ -163,8 +163,8 @@ int fx_axy_expw(fx_dtype dt, double a, const void* X, const void* Y, const void*
 
 /* *d_out = accu(X % Y) = sum_i X[i]*Y[i], as FP64 (FP dtypes) or, for
  * FX_U32, the full u64 sum stored in d_out's 8 bytes.  Per-thread sums are
- * compensated (Neumaier) in the compute type and combined in FP64 in a fixed
- * order by the last block to finish.  ws: fx_workspace_bytes(FX_R_ACCU). */
+ * kept in FP64 (FP32, BF16 and FP16 storage) or compensated (Neumaier, FP64
+ * storage) and combined in FP64 in a fixed order by the last block to finish.  ws: fx_workspace_bytes(FX_R_ACCU). */
 int fx_accu_xy(fx_dtype dt, const void* X, const void* Y, int64_t n, void* d_out,
                void* ws, size_t ws_bytes, const fx_launch* cfg, void* stream);
 
@@ -403,7 +403,7 @@ int fx_tape_eval_static(const fx_tape* t, fx_dtype dt, const void* const* inputs
  * library's flags and cached per process by its text.  The compiled kernel
  * reads each input once (and writes once, element-wise), like a
  * compile-time expression, without the interpreter's per-instruction cost;
- * its reductions follow the fused ones (compensated per-thread sums, FP64
+ * its reductions follow the fused ones (the same per-thread sums, FP64
  * block and cross-block combine, single-pass finish).  FP32, FP64, BF16 and
  * FP16 storage; the launch configuration is the library default of the kind
  * and storage type. */

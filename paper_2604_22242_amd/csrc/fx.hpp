@@ -5,8 +5,8 @@
 //   dot(A, B)    = sum of A's and B's element-wise products
 //   norm_fro(E)  = square root of the sum of E's squared elements
 //   sum(E, 0|1)  = column sums | row sums
-// Each fuses E into the reduction: one kernel, inputs read once, compensated
-// per-thread sums and an FP64 combine (u64 for u32 expressions).  E may be an
+// Each fuses E into the reduction: one kernel, inputs read once, FP64
+// (for FP64 data compensated) per-thread sums and an FP64 combine (u64 for u32 expressions).  E may be an
 // expression or a dmat view.  The scalar results go to device memory; the
 // workspace is sized by fx_workspace_bytes and zeroed once by the caller.
 // Z = E itself is eval(z, E, cfg, stream).

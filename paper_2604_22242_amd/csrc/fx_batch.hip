@@ -135,8 +135,7 @@ __global__ __launch_bounds__(kMaxBlock) void k_batch(const batch_desc* __restric
     T* z = static_cast<T*>(d.out);
     const int64_t i0 = (int64_t)tl.index * tile_elems;
     const int64_t i1 = min(d.n, i0 + tile_elems);
-    // one compensated chain per thread (the interpreter between two passes
-    // leaves the chain's dependent additions ample time; a chain per vector
+    // one sum per thread (the interpreter between two passes leaves the chain's dependent additions ample time; a chain per vector
     // lane would cost registers, and with them occupancy)
     accum<C> acc;
     for (int64_t e0 = i0; e0 < i1; e0 += pass) {

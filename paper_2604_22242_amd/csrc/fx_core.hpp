@@ -1,5 +1,5 @@
 // Core device/host helpers of the fused-expression library for gfx950:
-// storage/compute type traits, 16-byte vector loads and stores, compensated
+// storage/compute type traits, 16-byte vector loads and stores, exact or compensated
 // per-thread accumulation, wave64 + LDS block reduction, launch
 // configuration and error reporting.
 #pragma once
@@ -96,15 +96,24 @@ __device__ __forceinline__ void store_lanes(T* __restrict__ p, int64_t i, const 
 }
 
 // ---------------------------------------------------------------------------
-// Per-thread accumulation.  Floating point: compensated summation in the
-// compute type with Neumaier's refinement of Kahan's method, one compensated
-// add per element: the running sum s, and c, the sum of the exact rounding
-// errors of the additions into s; the thread's sum is s + c, handed upward in
-// FP64.  Each error is taken with Knuth's branch-free TwoSum (six additions,
-// exact whichever operand is larger), which on gfx950 avoids the compare and
-// selects of the magnitude test, and the hazard waits between them.  The
-// error of the sum is about u |sum| plus a term of order n u^2 times the sum
-// of the magnitudes of the thread's terms, so cancellation costs no accuracy.
+// Per-thread accumulation, one add per element, handed upward in FP64.
+//
+// FP32 compute: a running sum in FP64.  Each term widens exactly, so a thread's
+// sum of n terms is off by at most n 2^-53 times the sum of their magnitudes
+// (an FP32 pair kept with Neumaier's compensation: n 2^-48).  On gfx950
+// v_add_f64 issues at the FP32 rate, so this is two instructions an element (a
+// conversion and an add) against the pair's seven: the matrix workload's column
+// sums took 95 us in BF16 storage and 130 in FP32 with the pair, 84 and 120 so.
+//
+// FP64 compute: compensated summation with Neumaier's refinement of Kahan's
+// method: the running sum s, and c, the sum of the exact rounding errors of
+// the additions into s; the sum is s + c.  Each error is taken with Knuth's
+// branch-free TwoSum (six additions, exact whichever operand is larger), which
+// on gfx950 avoids the compare and selects of the magnitude test, and the
+// hazard waits between them.  The error of the sum is about u |sum| plus a
+// term of order n u^2 times the sum of the magnitudes of the thread's terms,
+// so cancellation costs no accuracy.
+//
 // Integers: plain u64, exact.
 
 __device__ __forceinline__ float absv(float x) { return __builtin_fabsf(x); }
@@ -125,13 +134,18 @@ template <class C> struct accum {
     return __builtin_isfinite(s) ? (double)s + (double)c : (double)s;
   }
 };
+template <> struct accum<float> {
+  double s = 0;
+  __device__ __forceinline__ void add(float t) { s += (double)t; }
+  __device__ __forceinline__ double value() const { return s; }
+};
 template <> struct accum<uint32_t> {
   uint64_t s = 0;
   __device__ __forceinline__ void add(uint64_t t) { s += t; }
   __device__ __forceinline__ uint64_t value() const { return s; }
 };
 
-// A thread's compensated sums, one per vector lane: the elements at lane j
+// A thread's sums, one per vector lane: the elements at lane j
 // of the vectors a thread visits form chain j, added in the order the thread
 // visits its vectors.  Separate chains keep the dependent additions apart so
 // that they overlap (one long chain per thread is latency-bound when few
@@ -240,7 +254,8 @@ inline bool pow2(int v) { return v > 0 && (v & (v - 1)) == 0; }
 
 // The library's default block size and EPT of a result kind (0 element-wise,
 // FX_R_*) for storage elements of `elem` bytes.  They do not depend on the
-// shape (the grid does), so generated kernel source can fix them in its text.
+// shape (the grid does, and small full reductions take a smaller EPT), so
+// generated kernel source can fix them in its text.
 constexpr int default_block(int kind, int elem) {
   return kind == 0 ? 512
        : kind == FX_R_COLSUM ? (elem >= 4 ? 512 : 256)
@@ -248,7 +263,18 @@ constexpr int default_block(int kind, int elem) {
        : elem >= 4 ? 256 : 512;  // full reductions
 }
 constexpr int default_ept(int kind, int elem) {
-  return kind == 0 ? 1 : kind == FX_R_COLSUM ? (elem >= 4 ? 2 : 1) : 2;
+  return kind == 0 ? 1
+       : kind == FX_R_COLSUM ? (elem >= 4 ? 2 : 1)
+       : kind == FX_R_ROWSUM ? 2
+       : elem >= 4 ? 4 : 2;  // full reductions
+}
+
+// Blocks of a generated full reduction for the `split` that resolve() chose
+// from its block and EPT: a tree known only at run time may be bound by its
+// arithmetic, which one block per CU (a wave per SIMD) does not overlap with
+// its loads, so a grid that fills the chip is doubled.
+inline int generated_full_split(int split, int cus, int64_t tiles) {
+  return split < cus ? split : (int)(tiles < 2 * (int64_t)cus ? tiles : 2 * (int64_t)cus);
 }
 
 // Validate the user-facing fields (zeros mean "choose").

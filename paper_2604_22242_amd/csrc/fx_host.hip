@@ -61,11 +61,17 @@ int check_launch(const fx_launch* c) {
 // 8192 x 8192 in FP32, FP64 and BF16; accu at 2^28 in BF16):
 //   element-wise: one tile per block, no grid-stride loop, 512 threads x one
 //     16-byte vector per input (6.6 TB/s FP32 on the C2 expression);
-//   full reductions: two blocks per CU, EPT 2 (each block takes one ticket:
-//     tens of thousands of tickets on one counter serialise); 256 threads
-//     for 4- and 8-byte types, 512 for half types, whose compensated sums
-//     cost twice the arithmetic per byte and need the extra waves to hide
-//     the loads (BF16 accu at 2^28: 0.156 against 0.213 ms);
+//   full reductions: one block per CU (each block takes one ticket: tens of
+//     thousands of tickets on one counter serialise); 256 threads, EPT 4 for
+//     4- and 8-byte types, 512 threads, EPT 2 for half types.  With its loads
+//     that deep in flight one block per CU streams faster than two, whose
+//     waves spread over twice the address range: accu at 2^28 FP32 291-295
+//     against 298 us, 2^27 FP64 293 against 300, 2^28 BF16 153 against 157,
+//     2^22 FP32 10.9 against 12.3.  Below 2^21 elements EPT 2 is faster (more
+//     blocks share the latency: 2^20 FP64 7.8 against 8.7 us), every thread
+//     gets 8 vectors but at least kReduceMinBlocks blocks run (2^20 BF16: 64
+//     blocks 6.4 us, 32 blocks 7.5), and an input of at most 32 KB is one
+//     block, which needs no cross-block finish (2^12 FP32 2.7 against 3.9 us);
 //   column sums: one block per column (512 threads, EPT 2 for 4- and
 //     8-byte types; 256 threads, EPT 1 for half types), a column split into
 //     chunks when there are fewer columns than blocks to fill the chip;
@@ -74,9 +80,10 @@ int check_launch(const fx_launch* c) {
 //     0.130 against 0.146 ms for EPT 4 on the FP32 matrix workload once each
 //     tile's loads are issued together), with enough column chunks for 8
 //     waves per CU.
-static constexpr int kReduceBlocksPerCU = 2;
-static constexpr int kReduceMinBlocks = 32;
-static constexpr int kReduceMinTilesPerBlock = 4;
+static constexpr int kReduceMinBlocks = 64;
+static constexpr int kReduceMinVecs = 8;  // per thread
+static constexpr int64_t kReduceDeepFrom = (int64_t)1 << 21;
+static constexpr int64_t kReduceOneBlockBytes = 32 << 10;
 static constexpr int kColsumBlocksPerCU = 8;
 static constexpr int kRowsumWavesPerCU = 8;
 constexpr int kRowsumMinCols = 32;
@@ -97,19 +104,14 @@ launch resolve(int kind, int elem, int64_t n_rows, int64_t n_cols, const fx_laun
   if (ew || full) {
     L.block = c.block ? c.block : default_block(kind, elem);
     L.ept = c.ept ? c.ept : default_ept(kind, elem);
+    if (full && !c.ept && n < kReduceDeepFrom) L.ept = 2;
     const int64_t tiles = std::max<int64_t>(1, ceil_div(n, (int64_t)L.block * L.ept * vec16));
-    // full reductions: one ticket per block; below 2^24 elements the tickets
-    // of two blocks per CU cost more than the extra bandwidth buys (measured:
-    // 8.0 vs 10.3 us at 2^20), above it two per CU keep HBM busier.  Small
-    // ones also give every block at least four tiles (but keep 32 blocks):
-    // the single-pass finish is a few serial round trips plus one ticket per
-    // block, which the work of a one- or two-tile block does not cover
-    // (2^20 elements: 128 blocks 6.3 us, 256 blocks 7.3 us).
-    const int64_t per_cu = n < ((int64_t)1 << 24) ? 1 : kReduceBlocksPerCU;
-    const int64_t want =
-        ew ? tiles
-           : std::min<int64_t>(std::min<int64_t>(tiles, cus * per_cu),
-                               std::max<int64_t>(kReduceMinBlocks, tiles / kReduceMinTilesPerBlock));
+    int64_t want = tiles;
+    if (full) {
+      const int64_t per_block = (int64_t)L.block * kReduceMinVecs * vec16;
+      want = std::min<int64_t>({tiles, cus, std::max<int64_t>(kReduceMinBlocks, n / per_block)});
+      if (n * elem <= kReduceOneBlockBytes) want = 1;
+    }
     L.split = c.split ? c.split : (int)std::min<int64_t>(want, 1 << 30);
   } else if (kind == FX_R_COLSUM) {
     L.block = c.block ? c.block : default_block(kind, elem);

@@ -60,7 +60,7 @@ struct map_sq {
   __device__ static double finish(double s) { return ::sqrt(s); }
 };
 
-// Add the map M of a thread's EPT x N values of one tile to its compensated
+// Add the map M of a thread's EPT x N values of one tile to its
 // lane sums, one element at a time (lane j's chain takes vector 0's, then
 // vector 1's ... element j).
 template <class M, int N, int EPT, class C>
@@ -264,7 +264,7 @@ __global__ __launch_bounds__(kMaxBlock) void k_colsum_thin(E e, int64_t n_rows, 
 // Row sums.  Thread owns rows [r0, r0+N) (one vector per column, so a wave
 // reads 64 consecutive vectors of a column) and walks the columns
 // [s*cpc, (s+1)*cpc) of its chunk EPT at a time (EPT loads per input in
-// flight), keeping N compensated row sums.  With split > 1 the chunk
+// flight), keeping N row sums.  With split > 1 the chunk
 // partials go to partials[s*n_rows + r]; the block that draws the last
 // ticket of its row block (counters[blockIdx.x]) adds them in chunk order.
 // N > 1 requires N | n_rows and aligned leaves.

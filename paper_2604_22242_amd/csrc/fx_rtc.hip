@@ -8,7 +8,7 @@
 // ahead-of-time template instantiation and the tape interpreter.  The
 // generated kernel does the reads and writes of a compile-time one with no
 // interpreter cost; its skeletons take the same per-thread element
-// assignment, compensated per-thread sums in the compute type, wave64 + LDS
+// assignment, the same per-thread sums, wave64 + LDS
 // block sums in FP64 and single-pass ticket finish as the compile-time
 // skeletons, with the library's default block size and EPT of the kind and
 // storage type written into the text.
@@ -216,16 +216,16 @@ int fx_rtc_create(const fx_node* nodes, int32_t n_nodes, fx_dtype dt, int kind, 
   if (int rc = emit_body(nodes, n_nodes, dt != FX_F64, body, &n_in)) return rc;
   // the library's default block size and EPT of this kind and storage type
   // (they do not depend on the shape; the split does, and is chosen per call)
-  const launch L = resolve(kind == FX_R_NORM ? FX_R_ACCU : kind, ty.elem, 1, 1, nullptr, true);
-  std::string src = kernel_source(body, n_in, ty, kind, L.block, L.ept, n_nodes - 1);
+  const int block = default_block(kind, ty.elem), ept = default_ept(kind, ty.elem);
+  std::string src = kernel_source(body, n_in, ty, kind, block, ept, n_nodes - 1);
   fx_rtc* h = new (std::nothrow) fx_rtc;
   if (!h) return fail(FX_E_ARG, "out of host memory");
   h->dt = dt;
   h->kind = kind;
   h->n_in = n_in;
   h->elem = ty.elem;
-  h->block = L.block;
-  h->ept = L.ept;
+  h->block = block;
+  h->ept = ept;
   h->source = src;
   if (int rc = jit_obtain(src.data(), src.size(), &h->prog, &h->compile_ms)) {
     delete h;
@@ -276,10 +276,12 @@ int fx_rtc_eval(fx_rtc* r, const void* const* inputs, int32_t n_inputs, fx_shape
   if (n == 0 && !full)  // sums over an empty dimension
     return r->dt == FX_F64 ? fill_zero<double>(out, nout, st) : fill_zero<float>(out, nout, st);
   const int rkind = kind == FX_R_NORM ? FX_R_ACCU : kind;
-  const launch L = resolve(rkind, r->elem, rows, cols, nullptr, true);
-  if (L.block != r->block || L.ept != r->ept)
-    return fail(FX_E_CONFIG, "launch configuration differs from the generated kernel's");
   const int N = 16 / r->elem;
+  const fx_launch text{r->block, r->ept, 0, 0};  // what the source fixes
+  launch L = resolve(rkind, r->elem, rows, cols, &text, true);
+  if (full)
+    L.split = generated_full_split(L.split, device_cus(),
+                                   ceil_div(n, (int64_t)r->block * r->ept * N));
   const int vec = kind == 0 || full || rows % N == 0 ? N : 1;
   const ws_layout W = workspace_for(rkind, rows, cols, L, vec);
   if (W.total() > 0 && (!ws || ws_bytes < W.total()))

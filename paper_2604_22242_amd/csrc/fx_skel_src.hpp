@@ -11,7 +11,7 @@
 //   fx_eval<N>(FX_ARGS, raw, r)   the expression on those N elements
 //   fx_at(FX_ARGS, i)             the expression at element i
 // The skeletons are those of the compile-time kernels: EPT vectors per input
-// loaded before any arithmetic, compensated per-thread sums in the compute type,
+// loaded before any arithmetic, per-thread sums in FP64 or compensated,
 // FP64 wave64 + LDS block sums and the single-pass agent-scope ticket finish.
 #pragma once
 
@@ -93,28 +93,37 @@ extern "C" __global__ __launch_bounds__(FX_BLOCK) void fx_rtc_ew(FX_PARAMS, st_t
 }
 )";
 
-// Sums: compensated per-thread sums in the compute type (Neumaier's
-// refinement of Kahan's method: c collects the exact rounding error of every
-// addition into s, taken with Knuth's TwoSum), one compensated add per
-// element, handed upward in FP64; the block sum is a
+// Sums, as in the compile-time skeletons: per-thread sums in FP64 where the
+// compute type is FP32, compensated ones (Neumaier's refinement of Kahan's
+// method: c collects the exact rounding error of every addition into s, taken
+// with Knuth's TwoSum) where it is FP64, one add per element, handed upward in
+// FP64; the block sum is a
 // wave64 butterfly and then the waves' results in order; partials are
 // published with agent-scope stores and the block that draws the last ticket
 // of an agent-scope counter adds them in index order after one acquire, then
 // clears the counter.
 inline constexpr char kSums[] = R"(
-struct fx_acc {
-  ct_t s, c;
-};
-__device__ __forceinline__ void fx_add(fx_acc& a, ct_t t) {
+template <class C> struct fx_acc_of {
+  C s = 0, c = 0;
+  __device__ __forceinline__ void add(C t) {
 #pragma clang fp contract(off)
-  const ct_t u = a.s + t;
-  const ct_t tv = u - a.s, sv = u - tv;  // TwoSum: the exact error of a.s + t
-  a.c += (a.s - sv) + (t - tv);
-  a.s = u;
-}
-__device__ __forceinline__ double fx_value(const fx_acc& a) {
-  return __builtin_isfinite(a.s) ? (double)a.s + (double)a.c : (double)a.s;
-}
+    const C u = s + t;
+    const C tv = u - s, sv = u - tv;  // TwoSum: the exact error of s + t
+    c += (s - sv) + (t - tv);
+    s = u;
+  }
+  __device__ __forceinline__ double value() const {
+    return __builtin_isfinite(s) ? (double)s + (double)c : (double)s;
+  }
+};
+template <> struct fx_acc_of<float> {
+  double s = 0;
+  __device__ __forceinline__ void add(float t) { s += (double)t; }
+  __device__ __forceinline__ double value() const { return s; }
+};
+typedef fx_acc_of<ct_t> fx_acc;
+__device__ __forceinline__ void fx_add(fx_acc& a, ct_t t) { a.add(t); }
+__device__ __forceinline__ double fx_value(const fx_acc& a) { return a.value(); }
 // one chain per vector lane, added in FP64 in lane order
 template <int N> __device__ __forceinline__ double fx_lanes_value(const fx_acc (&a)[N]) {
   double t = fx_value(a[0]);
@@ -161,8 +170,6 @@ extern "C" __global__ __launch_bounds__(FX_BLOCK) void fx_rtc_full(FX_PARAMS, lo
                                                                    unsigned* counter, double* out) {
   __shared__ double lds[FX_BLOCK / 64];
   fx_acc acc[FX_N];
-#pragma unroll
-  for (int j = 0; j < FX_N; ++j) acc[j] = fx_acc{0, 0};
   const long nv = n / FX_N;
   const long tile = (long)FX_BLOCK * FX_EPT;
   for (long t = blockIdx.x; t * tile < nv; t += gridDim.x) {
@@ -231,8 +238,6 @@ __device__ __forceinline__ void fx_colsum(FX_PARAMS, long n_rows, int split, lon
   const long base = col * n_rows + r0;
   const long nv = r1 > r0 ? (r1 - r0) / N : 0;
   fx_acc acc[N];
-#pragma unroll
-  for (int j = 0; j < N; ++j) acc[j] = fx_acc{0, 0};
   const long tile = (long)FX_BLOCK * FX_EPT;
   for (long t0 = 0; t0 < nv; t0 += tile) {
     const long v0 = t0 + threadIdx.x;
@@ -303,8 +308,6 @@ __device__ __forceinline__ void fx_rowsum(FX_PARAMS, long n_rows, long n_cols, i
   const long c0 = (long)s * cpc;
   const long c1 = n_cols < c0 + cpc ? n_cols : c0 + cpc;
   fx_acc acc[N];
-#pragma unroll
-  for (int j = 0; j < N; ++j) acc[j] = fx_acc{0, 0};
   if (active) {
     long c = c0;
     for (; c + FX_EPT <= c1; c += FX_EPT) {

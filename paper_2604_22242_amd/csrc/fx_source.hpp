@@ -237,7 +237,7 @@ template <class E, class T, int KIND> constexpr auto program_text() {
   using S = src<E, 0, 0>;
   using C = typename E::ct;
   static_assert(KIND == 0 || std::is_floating_point_v<C>,
-                "generated reductions are compensated floating-point sums");
+                "generated reductions are floating-point sums");
   constexpr int L = S::leaves, J = S::scalars;
   constexpr int elem = (int)sizeof(T);
   constexpr int rk = KIND == FX_R_NORM ? FX_R_ACCU : KIND;
@@ -311,7 +311,8 @@ int eval_source(const E& e, void* out, void* ws, size_t ws_bytes, hipStream_t st
     hipLaunchKernelGGL((k_fill_zero<O>), dim3(grid), dim3(256), 0, st, static_cast<O*>(out), nout);
     return hip_check(hipGetLastError(), "k_fill_zero launch");
   }
-  const launch L = resolve(rk, elem, rows, cols, nullptr, true);
+  const fx_launch text{default_block(rk, elem), default_ept(rk, elem), 0, 0};  // fixed in the source
+  const launch L = resolve(rk, elem, rows, cols, &text, true);
   constexpr int N = 16 / elem;
   const int vec = KIND == 0 || full || rows % N == 0 ? N : 1;
   const ws_layout W = workspace_for(rk, rows, cols, L, vec);
