@@ -367,8 +367,8 @@ int32_t fx_tape_program(const fx_tape* t, uint16_t* op, uint8_t* slot, uint8_t* 
  * threads, EPT 2 for 4- and 8-byte types from 2^20 elements on);
  * accu / norm 512 threads, EPT 2 (1 for half types), 2 blocks per CU;
  * column sums 256 threads, EPT 2 (1 for half types), one block per column
- * when there are at least as many columns as CUs; row sums 256 threads,
- * EPT 2, one row per thread, 64 column chunks.  The split default applies
+ * when there are at least as many columns as CUs; row sums 512 threads,
+ * EPT 2 (1 for half types).  The split default applies
  * only when all of cfg is 0 (or cfg is NULL); then a model attached with
  * fx_tape_set_model chooses instead.  Tapes are compiled for EPT 1, 2 and 4
  * and for vectors of one element, 8 or 16 bytes: other explicit values give

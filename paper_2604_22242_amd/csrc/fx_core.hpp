@@ -259,13 +259,13 @@ inline bool pow2(int v) { return v > 0 && (v & (v - 1)) == 0; }
 constexpr int default_block(int kind, int elem) {
   return kind == 0 ? 512
        : kind == FX_R_COLSUM ? (elem >= 4 ? 512 : 256)
-       : kind == FX_R_ROWSUM ? (elem >= 4 ? 256 : 64)
+       : kind == FX_R_ROWSUM ? (elem >= 4 ? 256 : 512)
        : elem >= 4 ? 256 : 512;  // full reductions
 }
 constexpr int default_ept(int kind, int elem) {
   return kind == 0 ? 1
        : kind == FX_R_COLSUM ? (elem >= 4 ? 2 : 1)
-       : kind == FX_R_ROWSUM ? 2
+       : kind == FX_R_ROWSUM ? (elem >= 4 ? 2 : 1)
        : elem >= 4 ? 4 : 2;  // full reductions
 }
 

@@ -75,18 +75,21 @@ int check_launch(const fx_launch* c) {
 //   column sums: one block per column (512 threads, EPT 2 for 4- and
 //     8-byte types; 256 threads, EPT 1 for half types), a column split into
 //     chunks when there are fewer columns than blocks to fill the chip;
-//   row sums: each thread owns one row vector and keeps EPT columns in
-//     flight (256 threads for 4- and 8-byte types, 64 for half types; EPT 2:
-//     0.130 against 0.146 ms for EPT 4 on the FP32 matrix workload once each
-//     tile's loads are issued together), with enough column chunks for 8
-//     waves per CU.
+//   row sums: two blocks per CU, 256 threads, EPT 2 for 4- and 8-byte types,
+//     512 threads, EPT 1 for half types (whose arithmetic wants the waves):
+//     matrix workload FP32 118 us against 126 with four blocks per CU, FP64
+//     234 against 252, BF16 97; fewer chunks where a thread would get less
+//     than two columns, and at most 128, since the finish reads them all
+//     (64 x 32768 BF16: 17 us with 128 chunks, 22 with 512).
 static constexpr int kReduceMinBlocks = 64;
 static constexpr int kReduceMinVecs = 8;  // per thread
 static constexpr int64_t kReduceDeepFrom = (int64_t)1 << 21;
 static constexpr int64_t kReduceOneBlockBytes = 32 << 10;
 static constexpr int kColsumBlocksPerCU = 8;
-static constexpr int kRowsumWavesPerCU = 8;
-constexpr int kRowsumMinCols = 32;
+static constexpr int kRowsumBlocksPerCU = 2;
+static constexpr int kRowsumMinCols = 2;
+static constexpr int kRowsumMaxSplit = 128;
+static constexpr int kRowsumChunksHeld = 64;
 
 launch resolve(int kind, int elem, int64_t n_rows, int64_t n_cols, const fx_launch* cfg,
                bool aligned16) {
@@ -128,13 +131,14 @@ launch resolve(int kind, int elem, int64_t n_rows, int64_t n_cols, const fx_laun
   } else {  // FX_R_ROWSUM
     L.block = c.block ? c.block : default_block(kind, elem);
     L.ept = c.ept ? c.ept : default_ept(kind, elem);
-    const int64_t rblocks = std::max<int64_t>(1, ceil_div(n_rows, (int64_t)L.block * vec16));
-    const int64_t target = cus * kRowsumWavesPerCU * 64 / L.block;
-    int64_t s = c.split ? c.split : ceil_div(target, rblocks);
-    // a defaulted split keeps at least kRowsumMinCols columns per chunk: the
-    // finish adds `split` partials per row one after another, so thousands of
-    // one-column chunks (a short, wide matrix) cost more than they spread
-    if (!c.split) s = std::min<int64_t>(s, std::max<int64_t>(1, n_cols / kRowsumMinCols));
+    const int rl = rowsum_lanes(n_rows, vec16);
+    const int64_t tiles = std::max<int64_t>(1, ceil_div(n_rows, (int64_t)rl * vec16));
+    int64_t s = c.split;
+    if (!s) {
+      const int64_t per_thread = (int64_t)(L.block / rl) * kRowsumMinCols;
+      s = std::min<int64_t>({ceil_div(cus * kRowsumBlocksPerCU, tiles), kRowsumMaxSplit,
+                             std::max<int64_t>(1, n_cols / per_thread)});
+    }
     s = std::min<int64_t>(s, std::max<int64_t>(1, n_cols));
     L.split = (int)std::max<int64_t>(1, std::min<int64_t>(s, 65535));
   }
@@ -149,8 +153,11 @@ launch resolve(int kind, int elem, int64_t n_rows, int64_t n_cols, const fx_laun
 // held-out trees these give 1.10x the best against 1.47x for the library
 // defaults.  Element-wise FP32 / FP64 tapes of 2^20 elements or more take
 // two vectors per thread.  Column sums keep the split heuristic when there are fewer
-// columns than CUs (one block per column would leave the chip idle); row
-// sums use one row per thread in 64 column chunks.  The split default
+// columns than CUs (one block per column would leave the chip idle), and row
+// sums keep it always: 512 threads on full vectors are within 2% of the best
+// of 144 configurations on the trees swept since their kernel combines in the
+// block (4096 x 4096 FP32, 30 instructions: 92 us; 256 threads of one row each
+// in 64 chunks, the default until then: 153).  The split default
 // applies only when the whole configuration is left at 0: a caller that
 // sets any field and leaves split at 0 gets the library's split heuristic.
 fx_launch tape_launch(int kind, int elem, int64_t n_rows, int64_t n_cols, const fx_launch* cfg) {
@@ -162,7 +169,7 @@ fx_launch tape_launch(int kind, int elem, int64_t n_rows, int64_t n_cols, const 
   switch (kind) {
     case FX_R_ACCU: case FX_R_NORM: d = fx_launch{512, half ? 1 : 2, 16, 2 * cus}; break;
     case FX_R_COLSUM: d = fx_launch{256, half ? 1 : 2, 16, n_cols >= cus ? 1 : 0}; break;
-    case FX_R_ROWSUM: d = fx_launch{256, 2, elem, 64}; break;
+    case FX_R_ROWSUM: d = fx_launch{512, half ? 1 : 2, 16, 0}; break;
     default:
       // two vectors per thread fill an interpreter pass for 4- and 8-byte
       // types; they pay off once there are enough elements to keep the chip
@@ -195,8 +202,8 @@ ws_layout workspace_for(int kind, int64_t n_rows, int64_t n_cols, const launch& 
     }
   } else if (kind == FX_R_ROWSUM) {
     if (L.split > 1) {
-      // counters for the worst case of one element per vector
-      W.counter_bytes = round256((size_t)ceil_div(n_rows, L.block) * 4);
+      // one counter per row tile: 64 rows or more, or the whole matrix
+      W.counter_bytes = round256((size_t)ceil_div(n_rows, 64) * 4);
       W.partial_bytes = (size_t)n_rows * L.split * 8;
     }
   }
@@ -238,6 +245,13 @@ size_t fx_workspace_bytes(int kind, fx_dtype dt, fx_shape shape, const fx_launch
     const fx_launch t = tape_launch(kind, elem, shape.n_rows, shape.n_cols, cfg);
     launch T = resolve(kind, elem, shape.n_rows, shape.n_cols, &t, true);
     b = std::max(b, workspace_for(kind, shape.n_rows, shape.n_cols, T, 16 / elem).total());
+    // row sums: a workspace sized by the defaults holds kRowsumChunksHeld
+    // column chunks, so that a launch model's or a caller's own split of that
+    // many fits it
+    if (kind == FX_R_ROWSUM && (!cfg || (!cfg->block && !cfg->ept && !cfg->vec_bytes && !cfg->split))) {
+      T.split = (int)std::min<int64_t>(kRowsumChunksHeld, std::max<int64_t>(1, shape.n_cols));
+      b = std::max(b, workspace_for(kind, shape.n_rows, shape.n_cols, T, 16 / elem).total());
+    }
   }
   return b;
 }

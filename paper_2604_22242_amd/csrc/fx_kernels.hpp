@@ -261,60 +261,119 @@ __global__ __launch_bounds__(kMaxBlock) void k_colsum_thin(E e, int64_t n_rows, 
 }
 
 // ============================================================================
-// Row sums.  Thread owns rows [r0, r0+N) (one vector per column, so a wave
-// reads 64 consecutive vectors of a column) and walks the columns
-// [s*cpc, (s+1)*cpc) of its chunk EPT at a time (EPT loads per input in
-// flight), keeping N row sums.  With split > 1 the chunk
-// partials go to partials[s*n_rows + r]; the block that draws the last
-// ticket of its row block (counters[blockIdx.x]) adds them in chunk order.
-// N > 1 requires N | n_rows and aligned leaves.
+// Row sums.  A block owns a tile of rl * N rows (rl lanes hold one column's
+// rows as vectors, so a wave reads 64 / rl columns at a time and the block
+// S = blockDim / rl) and chunk s of the columns: steps s, s + split, ... of
+// S * EPT columns each.  Thread group g takes every S-th column of a step, EPT
+// loads per input in flight.  The S partial sums of a row are added through
+// LDS in group order; with split > 1 the chunk partials go to
+// partials[s*n_rows + r], and the block that draws the last ticket of its row
+// tile (counters[blockIdx.x]) adds them, all its waves reading, in a fixed
+// order.  N > 1 requires N | n_rows and aligned leaves.
+//
+// What bounds it is HBM (BF16: the expression's arithmetic), provided that
+// * the partials are few and the finish short.  With a chunk per wave and no
+//   combine in the block the BF16 matrix workload published 128 partials per
+//   row, which its last blocks added one wave per 512 rows: 210 us;
+// * the blocks sweep memory together.  With a contiguous run of columns per
+//   chunk the chunks' streams lie megabytes apart: FP32 matrix workload 149 us,
+//   with interleaved steps and otherwise alike 126, with two blocks per CU 118
+//   (its column sums, contiguous by nature: 118-120).
+// Now BF16 97, FP32 118, FP64 234 us; with the former kernel 210, 151, 270.
+// Dynamic LDS: blockDim * N values.
+
+// Lanes of a wave that share a column: n_rows in vectors of `vec` elements,
+// fewer (down to 128-byte runs) where that gives the finish more row tiles to
+// work on.
+constexpr int kRowsumMinLanes = 8, kRowsumMinTiles = 16;
+inline int rowsum_lanes(int64_t n_rows, int vec) {
+  int rl = 1;
+  while (rl < 64 && (int64_t)rl * vec < n_rows) rl *= 2;
+  while (rl > kRowsumMinLanes && n_rows < (int64_t)kRowsumMinTiles * rl * vec) rl /= 2;
+  return rl;
+}
+
+// Row idx of the tile: the sum over groups of lds[g * rows + idx], in order.
+template <class D>
+__device__ __forceinline__ D sum_groups(const D* lds, int rows, int idx, int groups) {
+  D t = lds[idx];
+  for (int g = 1; g < groups; ++g) t += lds[g * rows + idx];
+  return t;
+}
 
 template <class E, class O, int N, int EPT>
 __global__ __launch_bounds__(kMaxBlock) void k_rowsum(E e, int64_t n_rows, int64_t n_cols, int split,
-                                                    int64_t cpc,
+                                                    int rl,
                                                     typename wide<typename E::ct>::type* partials,
                                                     unsigned* counters, O* out) {
   using C = typename E::ct;
   using D = typename wide<C>::type;
-  const int s = blockIdx.y;
-  const int64_t r0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * N;
-  const bool active = r0 < n_rows;
-  const int64_t c0 = (int64_t)s * cpc;
-  const int64_t c1 = min(n_cols, c0 + cpc);
+  extern __shared__ __align__(16) unsigned char fx_dyn_lds[];
+  D* lds = reinterpret_cast<D*>(fx_dyn_lds);
+  const int s = blockIdx.y, t = threadIdx.x;
+  const int rows = rl * N, S = blockDim.x / rl;  // rows per tile, columns per step
+  const int lr = t % rl, g = t / rl;
+  const int64_t row0 = (int64_t)blockIdx.x * rows;
+  const int64_t r0 = row0 + lr * N;
   accum<C> acc[N];
-  if (active) {
-    int64_t c = c0;
-    for (; c + EPT <= c1; c += EPT) {
+  if (r0 < n_rows) {
+    int64_t c = (int64_t)s * (EPT * S) + g;
+    for (; c + (EPT - 1) * S < n_cols; c += (int64_t)split * (EPT * S)) {
       lanes<C, N> r[EPT];
-      eval_tile<N, EPT>(e, r0 + c * n_rows, n_rows, r);
+      eval_tile<N, EPT>(e, r0 + c * n_rows, S * n_rows, r);
 #pragma unroll
       for (int j = 0; j < N; ++j)  // row j's EPT columns, in column order
 #pragma unroll
         for (int k = 0; k < EPT; ++k) acc[j].add(r[k].v[j]);
     }
-    for (; c < c1; ++c) {
+    for (; c < n_cols; c += S) {  // (fewer than EPT of them)
       lanes<C, N> r = e.template at_vec<N, kNT>(r0 + c * n_rows);
 #pragma unroll
       for (int j = 0; j < N; ++j) acc[j].add(r.v[j]);
     }
   }
-  if (split == 1) {
-    if (active)
 #pragma unroll
-      for (int j = 0; j < N; ++j) out[r0 + j] = static_cast<O>(acc[j].value());
-    return;
+  for (int j = 0; j < N; ++j) lds[t * N + j] = acc[j].value();  // [group][row]
+  __syncthreads();
+  for (int i = t; i < rows; i += blockDim.x) {
+    if (row0 + i >= n_rows) break;
+    const D v = sum_groups(lds, rows, i, S);
+    if (split == 1) out[row0 + i] = static_cast<O>(v);
+    else publish(partials + (int64_t)s * n_rows + row0 + i, v);
   }
-  if (active)
-#pragma unroll
-    for (int j = 0; j < N; ++j) publish(partials + (int64_t)s * n_rows + r0 + j, acc[j].value());
+  if (split == 1) return;
   if (take_last_ticket(counters + blockIdx.x, split)) {
-    if (active) {
+    // fl lanes side by side over rows; each of the F thread groups adds every
+    // F-th chunk of its rows, then the groups' sums are added in order
+    const int fl = rows < 64 ? rows : 64, F = blockDim.x / fl, f = t / fl;
+    D sum[N];
 #pragma unroll
-      for (int j = 0; j < N; ++j)
-        out[r0 + j] = static_cast<O>(sum_strided<D>(partials + r0 + j, n_rows, split));
+    for (int j = 0; j < N; ++j) sum[j] = 0;
+    constexpr int U = N >= 8 ? 4 : 8;  // chunks in flight per row
+    for (int q = f; q < split; q += U * F) {
+      D v[U][N];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+          const int i = t % fl + fl * j;
+          const bool in = i < rows && row0 + i < n_rows && q + u * F < split;
+          v[u][j] = in ? partials[(int64_t)(q + u * F) * n_rows + row0 + i] : D(0);
+        }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int j = 0; j < N; ++j) sum[j] += v[u][j];
     }
+    // (rows / fl <= N: rl * N rows, at least 64 of them per step unless the
+    // whole tile is smaller)
+#pragma unroll
+    for (int j = 0; j < N; ++j)
+      if (t % fl + fl * j < rows) lds[f * rows + t % fl + fl * j] = sum[j];
     __syncthreads();
-    if (threadIdx.x == 0) reset_counter(counters + blockIdx.x);
+    for (int i = t; i < rows; i += blockDim.x)
+      if (row0 + i < n_rows) out[row0 + i] = static_cast<O>(sum_groups(lds, rows, i, F));
+    if (t == 0) reset_counter(counters + blockIdx.x);
   }
 }
 
@@ -538,13 +597,13 @@ int reduce_dim_direct(int kind, const E& e, O* out, void* ws, size_t ws_bytes,
       });
     });
   }
-  const int64_t cpc = ceil_div(cols, L.split);
-  const int64_t rblocks = ceil_div(rows, (int64_t)L.block * vec);
+  const int rl = rowsum_lanes(rows, vec);
+  const int64_t rblocks = ceil_div(rows, (int64_t)rl * vec);
   return with_vec<T, E>(vec, [&](auto Nc) {
     return with_ept<max_ept<E>::value>(L.ept, [&](auto Ec) {
       constexpr int N = decltype(Nc)::value, EPT = decltype(Ec)::value;
-      hipLaunchKernelGGL((k_rowsum<E, O, N, EPT>), dim3((unsigned)rblocks, L.split), dim3(L.block), 0,
-                         st, e, rows, cols, L.split, cpc, parts, ctr, out);
+      hipLaunchKernelGGL((k_rowsum<E, O, N, EPT>), dim3((unsigned)rblocks, L.split), dim3(L.block),
+                         sizeof(D) * L.block * N, st, e, rows, cols, L.split, rl, parts, ctr, out);
       return hip_check(hipGetLastError(), "k_rowsum launch");
     });
   });

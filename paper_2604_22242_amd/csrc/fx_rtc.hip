@@ -310,9 +310,9 @@ int fx_rtc_eval(fx_rtc* r, const void* const* inputs, int32_t n_inputs, fx_shape
     void* args[] = {&p[0], &p[1], &p[2], &p[3], &rows_l, &split, &rpc, &parts, &ctr, &o};
     return jit_launch(f, cols, split, r->block, args, st);
   }
-  long cpc = (long)ceil_div(cols, split);
-  const int64_t rblocks = ceil_div(rows, (int64_t)r->block * vec);
-  void* args[] = {&p[0], &p[1], &p[2], &p[3], &rows_l, &cols_l, &split, &cpc, &parts, &ctr, &o};
+  int rl = rowsum_lanes(rows, vec);
+  const int64_t rblocks = ceil_div(rows, (int64_t)rl * vec);
+  void* args[] = {&p[0], &p[1], &p[2], &p[3], &rows_l, &cols_l, &split, &rl, &parts, &ctr, &o};
   return jit_launch(f, rblocks, split, r->block, args, st);
 }
 

@@ -293,28 +293,35 @@ extern "C" __global__ __launch_bounds__(FX_BLOCK) void fx_rtc_colsum_s(FX_PARAMS
 }
 )";
 
-// Row sums: a thread owns rows [r0, r0 + N) (one vector per column, so a
-// wave reads consecutive vectors of one column) and walks the columns of its
-// chunk FX_EPT at a time; with split > 1 the chunk partials go to
-// partials[s*n_rows + r] and the last block of a row block adds them in
-// chunk order.  The vector variant needs FX_N | n_rows.
+// Row sums, as the compile-time skeleton: a block owns rl * N rows and every
+// split-th step of S * FX_EPT columns, thread group g (rl threads: one column's
+// rows as vectors) every S-th column of a step; the groups' sums are added
+// through LDS and with split > 1 the last block of a row tile adds the chunk
+// partials.  The vector variant needs FX_N | n_rows.
 inline constexpr char kRowsum[] = R"(
+__device__ __forceinline__ double fx_groups(const double* lds, int rows, int i, int groups) {
+  double t = lds[i];
+  for (int g = 1; g < groups; ++g) t += lds[g * rows + i];
+  return t;
+}
 template <int N>
-__device__ __forceinline__ void fx_rowsum(FX_PARAMS, long n_rows, long n_cols, int split, long cpc,
-                                          double* partials, unsigned* counters, acc_out_t* out) {
-  const int s = blockIdx.y;
-  const long r0 = ((long)blockIdx.x * FX_BLOCK + threadIdx.x) * N;
-  const bool active = r0 < n_rows;
-  const long c0 = (long)s * cpc;
-  const long c1 = n_cols < c0 + cpc ? n_cols : c0 + cpc;
+__device__ __forceinline__ void fx_rowsum(FX_PARAMS, long n_rows, long n_cols, int split, int rl,
+                                          double* partials, unsigned* counters,
+                                          acc_out_t* out) {
+  __shared__ double lds[FX_BLOCK * N];
+  const int s = blockIdx.y, t = threadIdx.x;
+  const int rows = rl * N, S = FX_BLOCK / rl;
+  const int lr = t % rl, g = t / rl;
+  const long row0 = (long)blockIdx.x * rows;
+  const long r0 = row0 + lr * N;
   fx_acc acc[N];
-  if (active) {
-    long c = c0;
-    for (; c + FX_EPT <= c1; c += FX_EPT) {
+  if (r0 < n_rows) {
+    long c = (long)s * (FX_EPT * S) + g;
+    for (; c + (FX_EPT - 1) * S < n_cols; c += (long)split * (FX_EPT * S)) {
       fx_raw<N> raw[FX_EPT];
       ct_t r[FX_EPT][N];
 #pragma unroll
-      for (int k = 0; k < FX_EPT; ++k) fx_load<N>(FX_ARGS, r0 + (c + k) * n_rows, raw[k]);
+      for (int k = 0; k < FX_EPT; ++k) fx_load<N>(FX_ARGS, r0 + (c + k * S) * n_rows, raw[k]);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int k = 0; k < FX_EPT; ++k) fx_eval<N>(FX_ARGS, raw[k], r[k]);
@@ -323,7 +330,7 @@ __device__ __forceinline__ void fx_rowsum(FX_PARAMS, long n_rows, long n_cols, i
 #pragma unroll
         for (int k = 0; k < FX_EPT; ++k) fx_add(acc[j], r[k][j]);
     }
-    for (; c < c1; ++c) {
+    for (; c < n_cols; c += S) {  // (fewer than FX_EPT of them)
       fx_raw<N> raw;
       ct_t r[N];
       fx_load<N>(FX_ARGS, r0 + c * n_rows, raw);
@@ -332,35 +339,53 @@ __device__ __forceinline__ void fx_rowsum(FX_PARAMS, long n_rows, long n_cols, i
       for (int j = 0; j < N; ++j) fx_add(acc[j], r[j]);
     }
   }
-  if (split == 1) {
-    if (active)
 #pragma unroll
-      for (int j = 0; j < N; ++j) out[r0 + j] = (acc_out_t)fx_value(acc[j]);
-    return;
+  for (int j = 0; j < N; ++j) lds[t * N + j] = fx_value(acc[j]);
+  __syncthreads();
+  for (int i = t; i < rows; i += FX_BLOCK) {
+    if (row0 + i >= n_rows) break;
+    const double v = fx_groups(lds, rows, i, S);
+    if (split == 1) out[row0 + i] = (acc_out_t)v;
+    else fx_publish(partials + (long)s * n_rows + row0 + i, v);
   }
-  if (active)
-#pragma unroll
-    for (int j = 0; j < N; ++j) fx_publish(partials + (long)s * n_rows + r0 + j, fx_value(acc[j]));
+  if (split == 1) return;
   if (fx_last_ticket(counters + blockIdx.x, split)) {
-    if (active) {
+    const int fl = rows < 64 ? rows : 64, F = FX_BLOCK / fl, f = t / fl;
+    double sum[N];
 #pragma unroll
-      for (int j = 0; j < N; ++j) {
-        double t = 0;
-        for (int q = 0; q < split; ++q) t += partials[(long)q * n_rows + r0 + j];
-        out[r0 + j] = (acc_out_t)t;
-      }
+    for (int j = 0; j < N; ++j) sum[j] = 0;
+    constexpr int U = N >= 8 ? 4 : 8;
+    for (int q = f; q < split; q += U * F) {
+      double v[U][N];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+          const int i = t % fl + fl * j;
+          const bool in = i < rows && row0 + i < n_rows && q + u * F < split;
+          v[u][j] = in ? partials[(long)(q + u * F) * n_rows + row0 + i] : 0.0;
+        }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int j = 0; j < N; ++j) sum[j] += v[u][j];
     }
+#pragma unroll
+    for (int j = 0; j < N; ++j)
+      if (t % fl + fl * j < rows) lds[f * rows + t % fl + fl * j] = sum[j];
     __syncthreads();
-    if (threadIdx.x == 0) fx_reset(counters + blockIdx.x);
+    for (int i = t; i < rows; i += FX_BLOCK)
+      if (row0 + i < n_rows) out[row0 + i] = (acc_out_t)fx_groups(lds, rows, i, F);
+    if (t == 0) fx_reset(counters + blockIdx.x);
   }
 }
 extern "C" __global__ __launch_bounds__(FX_BLOCK) void fx_rtc_rowsum_v(FX_PARAMS, long n_rows, long n_cols,
-    int split, long cpc, double* partials, unsigned* counters, acc_out_t* out) {
-  fx_rowsum<FX_N>(FX_ARGS, n_rows, n_cols, split, cpc, partials, counters, out);
+    int split, int rl, double* partials, unsigned* counters, acc_out_t* out) {
+  fx_rowsum<FX_N>(FX_ARGS, n_rows, n_cols, split, rl, partials, counters, out);
 }
 extern "C" __global__ __launch_bounds__(FX_BLOCK) void fx_rtc_rowsum_s(FX_PARAMS, long n_rows, long n_cols,
-    int split, long cpc, double* partials, unsigned* counters, acc_out_t* out) {
-  fx_rowsum<1>(FX_ARGS, n_rows, n_cols, split, cpc, partials, counters, out);
+    int split, int rl, double* partials, unsigned* counters, acc_out_t* out) {
+  fx_rowsum<1>(FX_ARGS, n_rows, n_cols, split, rl, partials, counters, out);
 }
 )";
 

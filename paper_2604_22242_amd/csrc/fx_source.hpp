@@ -345,7 +345,7 @@ int eval_source(const E& e, void* out, void* ws, size_t ws_bytes, hipStream_t st
   void* parts = W.total() > 0 ? static_cast<char*>(ws) + W.counter_bytes : nullptr;
   void* ctr = W.total() > 0 ? ws : nullptr;
   int split = std::max(1, L.split);  // thin columns run as one chunk per column
-  long rpc = 0, cpc = 0;
+  long rpc = 0;
   if constexpr (KIND == 0) {
     args.insert(args.end(), {&o, &n_l});
     return jit_launch(fn, L.split, 1, L.block, args.data(), st);
@@ -357,9 +357,9 @@ int eval_source(const E& e, void* out, void* ws, size_t ws_bytes, hipStream_t st
     args.insert(args.end(), {&rows_l, &split, &rpc, &parts, &ctr, &o});
     return jit_launch(fn, cols, split, L.block, args.data(), st);
   } else {
-    cpc = (long)ceil_div(cols, split);
-    args.insert(args.end(), {&rows_l, &cols_l, &split, &cpc, &parts, &ctr, &o});
-    return jit_launch(fn, ceil_div(rows, (int64_t)L.block * vec), split, L.block, args.data(), st);
+    int rl = rowsum_lanes(rows, vec);
+    args.insert(args.end(), {&rows_l, &cols_l, &split, &rl, &parts, &ctr, &o});
+    return jit_launch(fn, ceil_div(rows, (int64_t)rl * vec), split, L.block, args.data(), st);
   }
 }
 

@@ -36,3 +36,36 @@ def test_full_reduction_edges(dtype, edge):
             call()
             torch.cuda.synchronize()
             assert_close(out.cpu().numpy(), v, mu, dtype, "%s %s %d" % (what, edge, rep))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64", "bf16"])
+@pytest.mark.parametrize("shape", [(1, 5000), (5, 4097), (64, 3000), (72, 1000), (200, 333),
+                                   (512, 700), (1000, 129), (4096, 3), (33000, 2)])
+def test_row_sum_tiles(dtype, shape):
+    """Row tiles from one row to the full 64 vectors, remainders of the row
+    tile and of the column step, chunk counts from one to more than there are
+    steps; through the fused, source and tape paths."""
+    torch, fx = need_gpu()
+    rows, cols = shape
+    host, (X, Y, W) = inputs(22, rows * cols, dtype)
+    dc = getattr(fx, CODE[dtype])
+    acc = torch.float64 if dtype == "f64" else torch.float32
+    out = torch.empty(rows, dtype=acc, device="cuda")
+    v, mu = oracle.evaluate(oracle.EXPRS["c2_z"], host, dtype, shape=shape, reduce="rowsum")
+    for cfg in (None, (64, 1, 16, 1), (256, 2, 16, 3), (512, 4, 16, 40), (192, 2, SIZE[dtype], 5)):
+        ws = fx.workspace(fx.R_ROWSUM, dc, shape, cfg)
+        for rep in range(2):
+            out.fill_(float("nan"))
+            fx.fx_c2_rowsum(X, Y, W, out, shape, ws, cfg)
+            torch.cuda.synchronize()
+            assert_close(out.cpu().numpy(), v, mu, dtype, "%s %s %d" % (shape, cfg, rep))
+    nodes = [("leaf", -1, -1, 0, 0), ("leaf", -1, -1, 1, 0), ("mul", 0, 1, -1, 0)]
+    v, mu = oracle.evaluate(oracle.EXPRS["xy"], host, dtype, shape=shape, reduce="rowsum")
+    ws = fx.workspace(fx.R_ROWSUM, dc, shape)
+    rtc, tape = fx.Rtc(nodes, dc, fx.R_ROWSUM), fx.Tape(nodes)
+    for what, call in (("source", lambda: rtc.eval([X, Y], out, shape, ws)),
+                       ("tape", lambda: fx.fx_tape_eval(tape, [X, Y], out, shape, fx.R_ROWSUM, ws))):
+        out.fill_(float("nan"))
+        call()
+        torch.cuda.synchronize()
+        assert_close(out.cpu().numpy(), v, mu, dtype, "%s %s" % (what, shape))
