@@ -31,8 +31,9 @@
  *   - n = 0 (or an empty shape) is a valid no-op; a scalar reduction of
  *     nothing writes 0.
  *   - Pointers need only the alignment of their element type; 16-byte
- *     vector loads are used when every pointer of a call is 16-byte aligned,
- *     element-wise loads otherwise.
+ *     vector loads are used at any of them (gfx950's global memory
+ *     instructions need no more).  Batches alone read element by element
+ *     unless every pointer is 16-byte aligned.
  *   - An element-wise output may be exactly one of the inputs (in place);
  *     partial overlap is not allowed.
  *   - Inputs are read with streaming (nontemporal) loads.  An element-wise

@@ -56,8 +56,16 @@ template <> struct raw<4> { using type = unsigned int; };
 template <> struct raw<8> { using type = unsigned int __attribute__((ext_vector_type(2))); };
 template <> struct raw<16> { using type = unsigned int __attribute__((ext_vector_type(4))); };
 
-// Load N consecutive elements at p + i (p + i aligned to N*sizeof(T)) and
-// widen them to the compute type.  NT selects the nontemporal (streaming)
+// A container loaded or stored at an address aligned only to an element of T.
+// gfx950's global memory instructions take any byte address (the compiler's
+// unaligned-access mode, on for amdhsa), so a 16-byte vector at an odd element
+// is the same one instruction as an aligned one; what it costs is the cache
+// lines that a wave's run straddles, one more per KB.
+template <int B, class T> struct raw_at {
+  typedef typename raw<B>::type type __attribute__((aligned(alignof(T))));
+};
+
+// Load N consecutive elements at p + i and widen them to the compute type.  NT selects the nontemporal (streaming)
 // cache policy.
 // Vectors wider than 16 bytes (a wide leaf inside an expression of a
 // narrower storage type) are read as several 16-byte loads.
@@ -66,13 +74,13 @@ __device__ __forceinline__ lanes<ct_t<T>, N> load_lanes(const T* __restrict__ p,
   constexpr int BYTES = N * (int)sizeof(T);
   constexpr int CHUNK = BYTES > 16 ? 16 : BYTES;
   constexpr int PER = CHUNK / (int)sizeof(T);  // elements per load
-  using R = typename raw<CHUNK>::type;
+  using R = typename raw_at<CHUNK, T>::type;
   T s[N];
 #pragma unroll
   for (int c = 0; c < N / PER; ++c) {
     const R* q = reinterpret_cast<const R*>(p + i + c * PER);
-    R r = NT ? __builtin_nontemporal_load(q) : *q;
-    __builtin_memcpy(s + c * PER, &r, sizeof(R));
+    typename raw<CHUNK>::type r = NT ? __builtin_nontemporal_load(q) : *q;
+    __builtin_memcpy(s + c * PER, &r, CHUNK);
   }
   lanes<ct_t<T>, N> out;
 #pragma unroll
@@ -84,12 +92,13 @@ __device__ __forceinline__ lanes<ct_t<T>, N> load_lanes(const T* __restrict__ p,
 // store them at p + i.
 template <int N, bool NT, class T>
 __device__ __forceinline__ void store_lanes(T* __restrict__ p, int64_t i, const lanes<ct_t<T>, N>& x) {
-  using R = typename raw<N * (int)sizeof(T)>::type;
+  constexpr int BYTES = N * (int)sizeof(T);
+  using R = typename raw_at<BYTES, T>::type;
   T s[N];
 #pragma unroll
   for (int j = 0; j < N; ++j) s[j] = static_cast<T>(x.v[j]);
-  R r;
-  __builtin_memcpy(&r, s, sizeof(R));
+  typename raw<BYTES>::type r;
+  __builtin_memcpy(&r, s, BYTES);
   R* q = reinterpret_cast<R*>(p + i);
   if (NT) __builtin_nontemporal_store(r, q);
   else *q = r;

@@ -32,23 +32,20 @@ namespace fx {
 struct expr_tag {};
 template <class E> constexpr bool is_expr_v = std::is_base_of_v<expr_tag, E>;
 
-// Host-side facts gathered from every leaf: common shape and alignment.
+// Host-side facts gathered from every leaf: the common shape.
 struct leaf_info {
   int64_t n_rows = -1, n_cols = -1;
   bool shape_ok = true;
   bool any_null = false;
-  uintptr_t addr_or = 0;  // OR of all leaf addresses (alignment test)
   void add(const void* p, int64_t r, int64_t c) {
     if (!p && r * c > 0) any_null = true;
     if (n_rows < 0) { n_rows = r; n_cols = c; }
     else if (r != n_rows || c != n_cols) shape_ok = false;
-    addr_or |= reinterpret_cast<uintptr_t>(p);
   }
   void add_shape(int64_t r, int64_t c) {  // an expression without array leaves
     if (n_rows < 0) { n_rows = r; n_cols = c; }
     else if (r != n_rows || c != n_cols) shape_ok = false;
   }
-  bool aligned(int bytes) const { return (addr_or & (uintptr_t)(bytes - 1)) == 0; }
 };
 
 // Identity of a leaf for de-duplication: the same address read as the same

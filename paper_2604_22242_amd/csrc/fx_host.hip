@@ -92,7 +92,7 @@ static constexpr int kRowsumMaxSplit = 128;
 static constexpr int kRowsumChunksHeld = 64;
 
 launch resolve(int kind, int elem, int64_t n_rows, int64_t n_cols, const fx_launch* cfg,
-               bool aligned16) {
+               bool vectors) {
   fx_launch c = cfg ? *cfg : fx_launch{0, 0, 0, 0};
   launch L;
   const bool ew = kind == 0;
@@ -102,7 +102,7 @@ launch resolve(int kind, int elem, int64_t n_rows, int64_t n_cols, const fx_laun
   const int64_t cus = device_cus();
   int vb = c.vec_bytes ? c.vec_bytes : 16;
   if (vb < elem) vb = elem;
-  if (!aligned16) vb = elem;
+  if (!vectors) vb = elem;
   L.vec_bytes = vb;
   if (ew || full) {
     L.block = c.block ? c.block : default_block(kind, elem);
@@ -136,7 +136,7 @@ launch resolve(int kind, int elem, int64_t n_rows, int64_t n_cols, const fx_laun
     int64_t s = c.split;
     if (!s) {
       const int64_t per_thread = (int64_t)(L.block / rl) * kRowsumMinCols;
-      s = std::min<int64_t>({ceil_div(cus * kRowsumBlocksPerCU, tiles), kRowsumMaxSplit,
+      s = std::min<int64_t>({cus * kRowsumBlocksPerCU / tiles, kRowsumMaxSplit,
                              std::max<int64_t>(1, n_cols / per_thread)});
     }
     s = std::min<int64_t>(s, std::max<int64_t>(1, n_cols));

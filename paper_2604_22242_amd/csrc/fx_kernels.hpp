@@ -115,6 +115,21 @@ __device__ __forceinline__ void eval_tile(const Fused<E>& f, int64_t base, int64
   }
 }
 
+// Workgroups are dispatched to the eight XCDs round-robin by block id, and
+// each XCD has its own L2.  Where a leading dimension is not a multiple of
+// the 128-byte line (10000 floats = 40000 B), vertically adjacent tiles
+// share the line their column runs straddle; under the plain order those two
+// tiles run on different XCDs and both fetch it from HBM (12% more reads for
+// submatrices, 25% with transposes).  xcd_order() gives each XCD a
+// contiguous run of tiles instead (a bijection on [0, G)), so the second
+// fetch of a shared line is an L2 hit.
+constexpr uint32_t kXcds = 8;
+__device__ __forceinline__ uint32_t xcd_order(uint32_t b, uint32_t G) {
+  const uint32_t per = G / kXcds, extra = G % kXcds;
+  const uint32_t xcd = b % kXcds, k = b / kXcds;
+  return xcd * per + (xcd < extra ? xcd : extra) + k;
+}
+
 // ============================================================================
 // Element-wise: Z[i] = E(i), i < n.
 
@@ -202,8 +217,13 @@ __global__ __launch_bounds__(kMaxBlock) void k_full(E e, int64_t n, typename wid
 // column c: a contiguous run read blockDim * N elements at a time, EPT loads
 // per input in flight.  With split > 1 the chunk partials go to
 // partials[c*split + s] and the block that draws the last ticket on
-// counters[c] adds them in chunk order.  N > 1 requires N | n_rows and
-// aligned leaves; rpc is a multiple of N.
+// counters[c] adds them in chunk order.  rpc is a multiple of N; the rows of the
+// last chunk that are no whole vector are taken as one that ends with the
+// column and overlaps the one before (n_rows >= N), its first lanes left out.
+//
+// Columns that are no multiple of N rows long start at any element, where
+// loads of single elements, the alternative, are bound by their issue: 6001 x
+// 2999 FP16 80 us, with vectors at any element 28.
 
 template <class E, class O, int N, int EPT>
 __global__ __launch_bounds__(kMaxBlock) void k_colsum(E e, int64_t n_rows, int split, int64_t rpc,
@@ -218,9 +238,11 @@ __global__ __launch_bounds__(kMaxBlock) void k_colsum(E e, int64_t n_rows, int s
   const int64_t r1 = min(n_rows, r0 + rpc);
   const int64_t base = col * n_rows + r0;
   const int64_t nv = r1 > r0 ? (r1 - r0) / N : 0;
+  // vectors with the overlapping one
+  const int64_t nvt = r1 > r0 + nv * N ? nv + 1 : nv;
   lane_accum<C, N> acc;
   const int64_t tile = (int64_t)blockDim.x * EPT;
-  for (int64_t t0 = 0; t0 < nv; t0 += tile) {
+  for (int64_t t0 = 0; t0 < nvt; t0 += tile) {
     const int64_t v0 = t0 + threadIdx.x;
     if (t0 + tile <= nv) {
       lanes<C, N> r[EPT];
@@ -230,7 +252,13 @@ __global__ __launch_bounds__(kMaxBlock) void k_colsum(E e, int64_t n_rows, int s
 #pragma unroll
       for (int k = 0; k < EPT; ++k) {
         const int64_t v = v0 + k * blockDim.x;
-        if (v < nv) add_lanes<map_id>(acc, e.template at_vec<N, kNT>(base + v * N));
+        if (v < nvt) {
+          // lanes from `lo` on are new (0 but for the overlapping vector)
+          const int lo = v < nv ? 0 : (int)((nv + 1) * N - (r1 - r0));
+          const lanes<C, N> r = e.template at_vec<N, kNT>(base + v * N - lo);
+#pragma unroll
+          for (int j = 0; j < N; ++j) acc.a[j].add(j >= lo ? r.v[j] : C(0));
+        }
       }
     }
   }
@@ -269,7 +297,10 @@ __global__ __launch_bounds__(kMaxBlock) void k_colsum_thin(E e, int64_t n_rows, 
 // LDS in group order; with split > 1 the chunk partials go to
 // partials[s*n_rows + r], and the block that draws the last ticket of its row
 // tile (counters[blockIdx.x]) adds them, all its waves reading, in a fixed
-// order.  N > 1 requires N | n_rows and aligned leaves.
+// order.  The last rows of a tile that are no whole vector are taken as one that
+// ends with the matrix's rows and overlaps the one before (n_rows >= N); single
+// elements, the alternative for n_rows no multiple of N, made 133 us of 6001 x
+// 2999 FP16 where this takes 35.
 //
 // What bounds it is HBM (BF16: the expression's arithmetic), provided that
 // * the partials are few and the finish short.  With a chunk per wave and no
@@ -310,13 +341,21 @@ __global__ __launch_bounds__(kMaxBlock) void k_rowsum(E e, int64_t n_rows, int64
   using D = typename wide<C>::type;
   extern __shared__ __align__(16) unsigned char fx_dyn_lds[];
   D* lds = reinterpret_cast<D*>(fx_dyn_lds);
-  const int s = blockIdx.y, t = threadIdx.x;
+  // Where columns are no whole number of cache lines, vertically adjacent row
+  // tiles share lines: the tiles of one chunk then run on one XCD (6001 x 2999
+  // FP32 47 -> 43 us, FP64 88 -> 81; with aligned columns the plain order is
+  // the faster, 8192 x 8192 FP64 234 against 251)
+  uint32_t b = blockIdx.y * gridDim.x + blockIdx.x;
+  if (n_rows * (int64_t)sizeof(typename E::storage) % 128) b = xcd_order(b, gridDim.x * gridDim.y);
+  const int s = b / gridDim.x, tile = b % gridDim.x, t = threadIdx.x;
   const int rows = rl * N, S = blockDim.x / rl;  // rows per tile, columns per step
   const int lr = t % rl, g = t / rl;
-  const int64_t row0 = (int64_t)blockIdx.x * rows;
-  const int64_t r0 = row0 + lr * N;
+  const int64_t row0 = (int64_t)tile * rows;
+  const int64_t first = row0 + lr * N;
+  const int sh = first + N > n_rows && first < n_rows ? (int)(first + N - n_rows) : 0;
+  const int64_t r0 = first - sh;  // lanes below sh repeat rows of the vector before
   accum<C> acc[N];
-  if (r0 < n_rows) {
+  if (first < n_rows) {
     int64_t c = (int64_t)s * (EPT * S) + g;
     for (; c + (EPT - 1) * S < n_cols; c += (int64_t)split * (EPT * S)) {
       lanes<C, N> r[EPT];
@@ -333,7 +372,8 @@ __global__ __launch_bounds__(kMaxBlock) void k_rowsum(E e, int64_t n_rows, int64
     }
   }
 #pragma unroll
-  for (int j = 0; j < N; ++j) lds[t * N + j] = acc[j].value();  // [group][row]
+  for (int j = 0; j < N; ++j)  // [group][row]
+    if (j >= sh) lds[t * N + j - sh] = acc[j].value();
   __syncthreads();
   for (int i = t; i < rows; i += blockDim.x) {
     if (row0 + i >= n_rows) break;
@@ -342,7 +382,7 @@ __global__ __launch_bounds__(kMaxBlock) void k_rowsum(E e, int64_t n_rows, int64
     else publish(partials + (int64_t)s * n_rows + row0 + i, v);
   }
   if (split == 1) return;
-  if (take_last_ticket(counters + blockIdx.x, split)) {
+  if (take_last_ticket(counters + tile, split)) {
     // fl lanes side by side over rows; each of the F thread groups adds every
     // F-th chunk of its rows, then the groups' sums are added in order
     const int fl = rows < 64 ? rows : 64, F = blockDim.x / fl, f = t / fl;
@@ -373,7 +413,7 @@ __global__ __launch_bounds__(kMaxBlock) void k_rowsum(E e, int64_t n_rows, int64
     __syncthreads();
     for (int i = t; i < rows; i += blockDim.x)
       if (row0 + i < n_rows) out[row0 + i] = static_cast<O>(sum_groups(lds, rows, i, F));
-    if (t == 0) reset_counter(counters + blockIdx.x);
+    if (t == 0) reset_counter(counters + tile);
   }
 }
 
@@ -427,9 +467,10 @@ template <class T, class E = void, class F> inline int with_vec(int vec_elems, F
 }
 
 // Resolve a configuration for `n_elems` elements of storage size `elem` with
-// `n_leaves` distinct inputs.  kind: 0 element-wise, FX_R_* reductions.
+// `n_leaves` distinct inputs.  kind: 0 element-wise, FX_R_* reductions;
+// vectors: false where a column is shorter than a vector (one element then).
 launch resolve(int kind, int elem, int64_t n_rows, int64_t n_cols, const fx_launch* cfg,
-               bool aligned16);
+               bool vectors);
 
 // Workspace layout: [counters, 256-byte aligned][FP64/u64 partials].
 struct ws_layout {
@@ -474,9 +515,7 @@ int eval_direct(T* z, const E& e, const fx_launch* cfg, hipStream_t st) {
   if (n == 0) return FX_OK;
   if (!z) return fail(FX_E_ARG, "NULL output pointer");
   if (int rc = check_launch(cfg)) return rc;
-  leaf_info li = info_of(e);
-  li.addr_or |= reinterpret_cast<uintptr_t>(z);
-  launch L = resolve(0, sizeof(T), rows, cols, cfg, li.aligned(16));
+  launch L = resolve(0, sizeof(T), rows, cols, cfg, true);
   clamp_ept<E>(L, cfg);
   const int vec = L.vec_bytes / (int)sizeof(T);
   return with_vec<T, E>(vec, [&](auto Nc) {
@@ -524,8 +563,7 @@ int reduce_full_direct(const E& e, void* out, void* ws, size_t ws_bytes, const f
   if (!out) return fail(FX_E_ARG, "NULL output pointer");
   if (int rc = check_launch(cfg)) return rc;
   const int64_t n = rows * cols;
-  leaf_info li = info_of(e);
-  launch L = resolve(FX_R_ACCU, sizeof(T), rows, cols, cfg, li.aligned(16));
+  launch L = resolve(FX_R_ACCU, sizeof(T), rows, cols, cfg, true);
   clamp_ept<E>(L, cfg);
   const int vec = L.vec_bytes / (int)sizeof(T);
   ws_layout W = workspace_for(FX_R_ACCU, rows, cols, L, vec);
@@ -571,9 +609,8 @@ int reduce_dim_direct(int kind, const E& e, O* out, void* ws, size_t ws_bytes,
     hipLaunchKernelGGL((k_fill_zero<O>), dim3(grid), dim3(256), 0, st, out, nout);
     return hip_check(hipGetLastError(), "k_fill_zero launch");
   }
-  leaf_info li = info_of(e);
   const int W16 = 16 / (int)sizeof(T);
-  launch L = resolve(kind, sizeof(T), rows, cols, cfg, li.aligned(16) && rows % W16 == 0);
+  launch L = resolve(kind, sizeof(T), rows, cols, cfg, rows >= W16);
   clamp_ept<E>(L, cfg);
   const int vec = L.vec_bytes / (int)sizeof(T);
   ws_layout W = workspace_for(kind, rows, cols, L, vec);

@@ -30,12 +30,14 @@ inline int skeleton_kernels(int kind, const char** names) {
 }
 
 
-// Loads: N consecutive elements at p, one 16-byte streaming load (N = FX_N)
-// or one element (N = 1).
+// Loads: N consecutive elements at p, one 16-byte streaming load (N = FX_N;
+// any element may start it: columns need not be whole vectors) or one element
+// (N = 1).
 inline constexpr char kLoads[] = R"(typedef unsigned int fx_u32x4 __attribute__((ext_vector_type(4)));
+typedef fx_u32x4 fx_u32x4_at __attribute__((aligned(alignof(st_t))));
 template <int N> struct fx_ld {
   __device__ static __forceinline__ void run(const st_t* p, st_t* o) {
-    const fx_u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const fx_u32x4*>(p));
+    const fx_u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const fx_u32x4_at*>(p));
     __builtin_memcpy(o, &v, 16);
   }
 };
@@ -224,8 +226,8 @@ extern "C" __global__ __launch_bounds__(FX_BLOCK) void fx_rtc_full(FX_PARAMS, lo
 // Column sums: block (column c, chunk s) sums rows [s*rpc, (s+1)*rpc) of
 // column c, a contiguous run; with split > 1 the chunk partials go to
 // partials[c*split + s] and the last block of column c adds them in chunk
-// order.  The vector variant needs FX_N | n_rows (rpc is then a multiple of
-// FX_N).
+// order.  rpc is a multiple of N; the last rows that are no whole vector are
+// taken as one that overlaps the one before (n_rows >= N).
 inline constexpr char kColsum[] = R"(
 template <int N>
 __device__ __forceinline__ void fx_colsum(FX_PARAMS, long n_rows, int split, long rpc, double* partials,
@@ -237,9 +239,10 @@ __device__ __forceinline__ void fx_colsum(FX_PARAMS, long n_rows, int split, lon
   const long r1 = n_rows < r0 + rpc ? n_rows : r0 + rpc;
   const long base = col * n_rows + r0;
   const long nv = r1 > r0 ? (r1 - r0) / N : 0;
+  const long nvt = r1 > r0 + nv * N ? nv + 1 : nv;  // with the overlapping vector
   fx_acc acc[N];
   const long tile = (long)FX_BLOCK * FX_EPT;
-  for (long t0 = 0; t0 < nv; t0 += tile) {
+  for (long t0 = 0; t0 < nvt; t0 += tile) {
     const long v0 = t0 + threadIdx.x;
     if (t0 + tile <= nv) {
       fx_raw<N> raw[FX_EPT];
@@ -257,13 +260,14 @@ __device__ __forceinline__ void fx_colsum(FX_PARAMS, long n_rows, int split, lon
 #pragma unroll
       for (int k = 0; k < FX_EPT; ++k) {
         const long v = v0 + (long)k * FX_BLOCK;
-        if (v < nv) {
+        if (v < nvt) {
+          const int lo = v < nv ? 0 : (int)((nv + 1) * N - (r1 - r0));
           fx_raw<N> raw;
           ct_t r[N];
-          fx_load<N>(FX_ARGS, base + v * N, raw);
+          fx_load<N>(FX_ARGS, base + v * N - lo, raw);
           fx_eval<N>(FX_ARGS, raw, r);
 #pragma unroll
-          for (int j = 0; j < N; ++j) fx_add(acc[j], r[j]);
+          for (int j = 0; j < N; ++j) fx_add(acc[j], j >= lo ? r[j] : (ct_t)0);
         }
       }
     }
@@ -297,7 +301,8 @@ extern "C" __global__ __launch_bounds__(FX_BLOCK) void fx_rtc_colsum_s(FX_PARAMS
 // split-th step of S * FX_EPT columns, thread group g (rl threads: one column's
 // rows as vectors) every S-th column of a step; the groups' sums are added
 // through LDS and with split > 1 the last block of a row tile adds the chunk
-// partials.  The vector variant needs FX_N | n_rows.
+// partials.  The matrix's last rows that are no whole vector are taken as one
+// that overlaps the one before (n_rows >= N).
 inline constexpr char kRowsum[] = R"(
 __device__ __forceinline__ double fx_groups(const double* lds, int rows, int i, int groups) {
   double t = lds[i];
@@ -309,13 +314,22 @@ __device__ __forceinline__ void fx_rowsum(FX_PARAMS, long n_rows, long n_cols, i
                                           double* partials, unsigned* counters,
                                           acc_out_t* out) {
   __shared__ double lds[FX_BLOCK * N];
-  const int s = blockIdx.y, t = threadIdx.x;
+  // where columns are no whole number of cache lines, the row tiles of one
+  // chunk (which share lines) run on one of the eight XCDs
+  unsigned b = blockIdx.y * gridDim.x + blockIdx.x;
+  if (n_rows * (long)sizeof(st_t) % 128) {
+    const unsigned G = gridDim.x * gridDim.y, xcd = b % 8;
+    b = xcd * (G / 8) + (xcd < G % 8 ? xcd : G % 8) + b / 8;
+  }
+  const int s = b / gridDim.x, tile = b % gridDim.x, t = threadIdx.x;
   const int rows = rl * N, S = FX_BLOCK / rl;
   const int lr = t % rl, g = t / rl;
-  const long row0 = (long)blockIdx.x * rows;
-  const long r0 = row0 + lr * N;
+  const long row0 = (long)tile * rows;
+  const long first = row0 + lr * N;
+  const int sh = first + N > n_rows && first < n_rows ? (int)(first + N - n_rows) : 0;
+  const long r0 = first - sh;  // lanes below sh repeat rows of the vector before
   fx_acc acc[N];
-  if (r0 < n_rows) {
+  if (first < n_rows) {
     long c = (long)s * (FX_EPT * S) + g;
     for (; c + (FX_EPT - 1) * S < n_cols; c += (long)split * (FX_EPT * S)) {
       fx_raw<N> raw[FX_EPT];
@@ -340,7 +354,8 @@ __device__ __forceinline__ void fx_rowsum(FX_PARAMS, long n_rows, long n_cols, i
     }
   }
 #pragma unroll
-  for (int j = 0; j < N; ++j) lds[t * N + j] = fx_value(acc[j]);
+  for (int j = 0; j < N; ++j)
+    if (j >= sh) lds[t * N + j - sh] = fx_value(acc[j]);
   __syncthreads();
   for (int i = t; i < rows; i += FX_BLOCK) {
     if (row0 + i >= n_rows) break;
@@ -349,7 +364,7 @@ __device__ __forceinline__ void fx_rowsum(FX_PARAMS, long n_rows, long n_cols, i
     else fx_publish(partials + (long)s * n_rows + row0 + i, v);
   }
   if (split == 1) return;
-  if (fx_last_ticket(counters + blockIdx.x, split)) {
+  if (fx_last_ticket(counters + tile, split)) {
     const int fl = rows < 64 ? rows : 64, F = FX_BLOCK / fl, f = t / fl;
     double sum[N];
 #pragma unroll
@@ -376,7 +391,7 @@ __device__ __forceinline__ void fx_rowsum(FX_PARAMS, long n_rows, long n_cols, i
     __syncthreads();
     for (int i = t; i < rows; i += FX_BLOCK)
       if (row0 + i < n_rows) out[row0 + i] = (acc_out_t)fx_groups(lds, rows, i, F);
-    if (t == 0) fx_reset(counters + blockIdx.x);
+    if (t == 0) fx_reset(counters + tile);
   }
 }
 extern "C" __global__ __launch_bounds__(FX_BLOCK) void fx_rtc_rowsum_v(FX_PARAMS, long n_rows, long n_cols,

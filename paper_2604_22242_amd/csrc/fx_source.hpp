@@ -314,7 +314,7 @@ int eval_source(const E& e, void* out, void* ws, size_t ws_bytes, hipStream_t st
   const fx_launch text{default_block(rk, elem), default_ept(rk, elem), 0, 0};  // fixed in the source
   const launch L = resolve(rk, elem, rows, cols, &text, true);
   constexpr int N = 16 / elem;
-  const int vec = KIND == 0 || full || rows % N == 0 ? N : 1;
+  const int vec = KIND == 0 || full || rows >= N ? N : 1;
   const ws_layout W = workspace_for(rk, rows, cols, L, vec);
   if (W.total() > 0 && (!ws || ws_bytes < W.total()))
     return fail(FX_E_WORKSPACE, "workspace of %zu bytes needed, %zu given", W.total(), ws_bytes);

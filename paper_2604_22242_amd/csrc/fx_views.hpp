@@ -350,21 +350,6 @@ __device__ __forceinline__ void stage(const Binary<Op, A, B>& e, const tile_ctx<
   stage<TOFF + trans_count<A>::value, N>(e.b, x, rows, cols);
 }
 
-// Workgroups are dispatched to the eight XCDs round-robin by block id, and
-// each XCD has its own L2.  Where a leading dimension is not a multiple of
-// the 128-byte line (10000 floats = 40000 B), vertically adjacent tiles
-// share the line their column runs straddle; under the plain order those two
-// tiles run on different XCDs and both fetch it from HBM (12% more reads for
-// submatrices, 25% with transposes).  xcd_order() gives each XCD a
-// contiguous run of tiles instead (a bijection on [0, G)), so the second
-// fetch of a shared line is an L2 hit.
-constexpr uint32_t kXcds = 8;
-__device__ __forceinline__ uint32_t xcd_order(uint32_t b, uint32_t G) {
-  const uint32_t per = G / kXcds, extra = G % kXcds;
-  const uint32_t xcd = b % kXcds, k = b / kXcds;
-  return xcd * per + (xcd < extra ? xcd : extra) + k;
-}
-
 // Z (dense rows x cols) = E over a grid of tiles, numbered down the tile
 // columns (tile t: tile row t % tile_rows, tile column t / tile_rows) and
 // taken in xcd_order.  (Launching the partner tiles (I, J) and (J, I) side
