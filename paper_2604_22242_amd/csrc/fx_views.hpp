@@ -12,14 +12,15 @@
 //
 // Evaluation.  A diagonal is a vector, so expressions over diagonals run
 // through the linear skeletons.  Expressions with Sub or Trans leaves run
-// through k_ew2d: one block per output tile ((16 * N) x 64 with transposed
-// leaves, (64 * N) x 16 without), each thread a vector of N consecutive rows
-// in four columns.  Dense and submatrix leaves
-// are read straight from HBM (16-byte vectors when every view is aligned);
-// a transposed leaf's source tile is first staged in LDS by the whole block
-// with coalesced reads along the source's columns (column pitch 16 * N + 1
-// elements, so the strided LDS writes do not conflict), and the threads
-// then read their transposed vectors from LDS.
+// through k_ew2d: one block per output tile (128 x 64, 64 x 64 for 8-byte
+// types, with transposed leaves; (64 * N) x 16 without), each thread a vector
+// of N consecutive rows in several columns.  Dense and submatrix leaves are
+// read straight from HBM, 16-byte vectors at any element; a part of the
+// expression all of whose leaves are transposed, such as t(B + C), is first
+// evaluated over its source tile and staged in LDS by the whole block, read
+// along the source's columns and written at an odd column pitch (so the
+// strided LDS writes do not conflict); the threads then read their transposed
+// vectors from LDS.
 #pragma once
 
 #include "fx_kernels.hpp"
@@ -200,14 +201,24 @@ template <class T> inline auto t(const dmat<T>& m) { return t(m.expr()); }
 
 // ---- traits -------------------------------------------------------------------
 
-// Number of transposed leaves (each gets an LDS tile), and whether the
+// Is every leaf transposed (and there is one)?  Such a part of the expression
+// is staged as one LDS tile.
+template <class E> struct all_trans { static constexpr bool value = false; };
+template <class T> struct all_trans<Trans<T>> { static constexpr bool value = true; };
+template <class Op, class A> struct all_trans<Unary<Op, A>> : all_trans<A> {};
+template <class Op, class A, bool L> struct all_trans<Scalar<Op, A, L>> : all_trans<A> {};
+template <class Op, class A, class B> struct all_trans<Binary<Op, A, B>> {
+  static constexpr bool value = all_trans<A>::value && all_trans<B>::value;
+};
+
+// Number of LDS tiles (the largest all-transposed parts), and whether the
 // expression needs the 2-D skeleton.
-template <class E> struct trans_count { static constexpr int value = 0; };
-template <class T> struct trans_count<Trans<T>> { static constexpr int value = 1; };
-template <class Op, class A> struct trans_count<Unary<Op, A>> : trans_count<A> {};
-template <class Op, class A, bool L> struct trans_count<Scalar<Op, A, L>> : trans_count<A> {};
-template <class To, class A> struct trans_count<Convert<To, A>> : trans_count<A> {};
-template <class Op, class A, class B> struct trans_count<Binary<Op, A, B>> {
+template <class E, bool WHOLE = all_trans<E>::value> struct trans_count { static constexpr int value = 0; };
+template <class E> struct trans_count<E, true> { static constexpr int value = 1; };
+template <class Op, class A> struct trans_count<Unary<Op, A>, false> : trans_count<A> {};
+template <class Op, class A, bool L> struct trans_count<Scalar<Op, A, L>, false> : trans_count<A> {};
+template <class To, class A> struct trans_count<Convert<To, A>, false> : trans_count<A> {};
+template <class Op, class A, class B> struct trans_count<Binary<Op, A, B>, false> {
   static constexpr int value = trans_count<A>::value + trans_count<B>::value;
 };
 
@@ -223,169 +234,276 @@ template <class Op, class A, class B> struct needs_2d<Binary<Op, A, B>> {
 
 // ---- 2-D evaluation -------------------------------------------------------------
 
-constexpr int kTileCols = 64;
 constexpr int kTileThreads = 256;
-template <int N> constexpr int kTileRows = 16 * N;
-template <int N> constexpr int kTilePitch = 16 * N + 1;
-template <int N> constexpr int kTileBuf = kTileCols * kTilePitch<N>;
 
-// The tile being computed; NL is the vector width the LDS tiles were laid
-// out for (a scalar read inside a vector tile keeps that layout).
-template <class C, int NL> struct tile_ctx {
+// Tile geometry.  With transposed parts (KT > 0) the tile is 128 rows (64 of
+// 8-byte types), so that a column of a direct leaf is read in 512-byte runs
+// (256 of 2-byte types), by 32 columns (Q = 1; 17 KB of LDS per staged part) or
+// 64 (Q = 4 and 2-byte types; 33 KB).  The wider tile is the faster one where
+// columns are whole cache lines and its blocks are many (4096 x 4096 FP64 128
+// us against 143); with few blocks they fill the chip unevenly (3001 x 3001
+// FP32 44 against 30), elsewhere the two are even.  The one-element variant,
+// for views narrower than a vector, keeps 16 x 64.  Without transposed parts
+// the tile is (64 N) x (4 Q): 1 KB runs (square tiles, 256-byte runs: measured
+// slower), Q columns per thread.
+template <int KT, int N, int Q, class T> struct tile_geo {
+  static constexpr int TR = KT == 0 ? 64 * N : N == 1 ? 16 : sizeof(T) == 8 ? 64 : 128;
+  static constexpr int TC = KT == 0 ? 4 * Q : N == 1 || Q == 4 || sizeof(T) == 2 ? 64 : 32;
+  static constexpr int RV = TR / N;              // threads down a column
+  static constexpr int CG = kTileThreads / RV;   // columns at a time
+  static constexpr int P = TR + 1;               // LDS column pitch
+};
+
+// The tile being computed (G: its geometry; NTL: streaming loads of the direct
+// leaves).
+template <class C, class G, bool NTL> struct tile_ctx {
+  static constexpr bool nt = NTL;
   C* lds;
   int64_t r0, c0;
 };
 
-// at2<TOFF, N>(e, r, c, x): rows r..r+N-1 of column c.  TOFF numbers the
-// transposed leaves depth-first (their LDS tiles).
-template <int TOFF, int N, class T, int NL>
-__device__ __forceinline__ lanes<ct_t<T>, N> at2(const Leaf<T>& e, int64_t r, int64_t c,
-                                                 const tile_ctx<ct_t<T>, NL>&) {
-  if constexpr (N > 1) return load_lanes<N, kNT>(e.p, r + c * e.n_rows);
-  lanes<ct_t<T>, N> v;
-  v.v[0] = static_cast<ct_t<T>>(e.p[r + c * e.n_rows]);
-  return v;
+// Streaming loads of the direct leaves pay where every column is a whole number
+// of cache lines and the data exceed what the last-level cache keeps for the
+// next call (8192 x 8192 FP32 a*A + t(B + C) + log(D^2): 222 us against 234).
+// Otherwise ordinary ones do: the lines that runs straddle are read again by
+// the tile beside (10000 x 10000 FP32: 378 against 410), and small data are found in
+// that cache (4096 x 4096 FP64 sum of two submatrices, 101 MB: 15 us against
+// 18).  Without transposed parts the runs are long and only size counts.
+constexpr uint64_t kCachedBelow = uint64_t(176) << 20;
+template <class T> inline bool whole_lines(const Leaf<T>& e) { return e.n_rows * sizeof(T) % 128 == 0; }
+template <class T> inline bool whole_lines(const Sub<T>& e) { return e.ld * sizeof(T) % 128 == 0; }
+template <class T> inline bool whole_lines(const Trans<T>& e) { return e.ld * sizeof(T) % 128 == 0; }
+template <class T> inline bool whole_lines(const Diag<T>&) { return true; }
+template <class Op, class A> inline bool whole_lines(const Unary<Op, A>& e) { return whole_lines(e.a); }
+template <class Op, class A, bool L> inline bool whole_lines(const Scalar<Op, A, L>& e) {
+  return whole_lines(e.a);
 }
-template <int TOFF, int N, class T, int NL>
-__device__ __forceinline__ lanes<ct_t<T>, N> at2(const Sub<T>& e, int64_t r, int64_t c,
-                                                 const tile_ctx<ct_t<T>, NL>&) {
-  if constexpr (N > 1) return load_lanes<N, kNT>(e.p, e.off + r + c * e.ld);
-  lanes<ct_t<T>, N> v;
-  v.v[0] = static_cast<ct_t<T>>(e.p[e.off + r + c * e.ld]);
-  return v;
+template <class To, class A> inline bool whole_lines(const Convert<To, A>& e) { return whole_lines(e.a); }
+template <class Op, class A, class B> inline bool whole_lines(const Binary<Op, A, B>& e) {
+  return whole_lines(e.a) && whole_lines(e.b);
 }
-template <int TOFF, int N, class T, int NL>
-__device__ __forceinline__ lanes<ct_t<T>, N> at2(const Trans<T>&, int64_t r, int64_t c,
-                                                 const tile_ctx<ct_t<T>, NL>& x) {
-  const ct_t<T>* buf = x.lds + TOFF * kTileBuf<NL> + (c - x.c0) * kTilePitch<NL> + (r - x.r0);
-  lanes<ct_t<T>, N> v;
-#pragma unroll
-  for (int j = 0; j < N; ++j) v.v[j] = buf[j];
-  return v;
+template <class E> struct leaf_count { static constexpr int value = 1; };
+template <class Op, class A> struct leaf_count<Unary<Op, A>> : leaf_count<A> {};
+template <class Op, class A, bool L> struct leaf_count<Scalar<Op, A, L>> : leaf_count<A> {};
+template <class To, class A> struct leaf_count<Convert<To, A>> : leaf_count<A> {};
+template <class Op, class A, class B> struct leaf_count<Binary<Op, A, B>> {
+  static constexpr int value = leaf_count<A>::value + leaf_count<B>::value;
+};
+
+// src2<N>(e, r, c): an all-transposed expression at row r, columns c .. c+N-1
+// of the view: N consecutive rows of every source.  Ordinary (not streaming)
+// loads: where the leading dimension is no whole number of cache lines, the
+// lines a run straddles are read again by the tile beside it, long after, and
+// must stay in the last-level cache until then (10000 x 10000 FP32 a*A +
+// t(B + C) + log(D^2): 419 us with streaming loads and 64 x 64 tiles staged
+// leaf by leaf, 378 now).
+template <int N, class T>
+__device__ __forceinline__ lanes<ct_t<T>, N> src2(const Trans<T>& e, int64_t r, int64_t c) {
+  return load_lanes<N, false>(e.p, e.off + c + r * e.ld);
 }
-template <int TOFF, int N, class T, int NL>
-__device__ __forceinline__ lanes<ct_t<T>, N> at2(const Diag<T>& e, int64_t r, int64_t,
-                                                 const tile_ctx<ct_t<T>, NL>&) {
-  return e.template at_vec<N, kNT>(r);
-}
-template <int TOFF, int N, class Op, class A, int NL>
-__device__ __forceinline__ lanes<typename A::ct, N> at2(const Unary<Op, A>& e, int64_t r, int64_t c,
-                                                        const tile_ctx<typename A::ct, NL>& x) {
-  lanes<typename A::ct, N> v = at2<TOFF, N>(e.a, r, c, x);
+template <int N, class Op, class A>
+__device__ __forceinline__ lanes<typename A::ct, N> src2(const Unary<Op, A>& e, int64_t r, int64_t c) {
+  lanes<typename A::ct, N> v = src2<N>(e.a, r, c);
 #pragma unroll
   for (int j = 0; j < N; ++j) v.v[j] = Op::apply(v.v[j]);
   return v;
 }
-template <int TOFF, int N, class Op, class A, bool L, int NL>
-__device__ __forceinline__ lanes<typename A::ct, N> at2(const Scalar<Op, A, L>& e, int64_t r,
-                                                        int64_t c,
-                                                        const tile_ctx<typename A::ct, NL>& x) {
-  lanes<typename A::ct, N> v = at2<TOFF, N>(e.a, r, c, x);
+template <int N, class Op, class A, bool L>
+__device__ __forceinline__ lanes<typename A::ct, N> src2(const Scalar<Op, A, L>& e, int64_t r, int64_t c) {
+  lanes<typename A::ct, N> v = src2<N>(e.a, r, c);
 #pragma unroll
   for (int j = 0; j < N; ++j) v.v[j] = e.apply1(v.v[j]);
   return v;
 }
-template <int TOFF, int N, class Op, class A, class B, int NL>
-__device__ __forceinline__ lanes<typename A::ct, N> at2(const Binary<Op, A, B>& e, int64_t r,
-                                                        int64_t c,
-                                                        const tile_ctx<typename A::ct, NL>& x) {
-  lanes<typename A::ct, N> u = at2<TOFF, N>(e.a, r, c, x);
-  lanes<typename A::ct, N> w = at2<TOFF + trans_count<A>::value, N>(e.b, r, c, x);
+template <int N, class Op, class A, class B>
+__device__ __forceinline__ lanes<typename A::ct, N> src2(const Binary<Op, A, B>& e, int64_t r, int64_t c) {
+  lanes<typename A::ct, N> u = src2<N>(e.a, r, c);
+  lanes<typename A::ct, N> w = src2<N>(e.b, r, c);
 #pragma unroll
   for (int j = 0; j < N; ++j) u.v[j] = Op::apply(u.v[j], w.v[j]);
   return u;
 }
-template <int TOFF, int N, class To, class A, int NL>
-__device__ __forceinline__ lanes<To, N> at2(const Convert<To, A>& e, int64_t r, int64_t c,
-                                            const tile_ctx<To, NL>& x) {
+
+// at2<TOFF, N>(e, r, c, x): rows r..r+N-1 of column c.  TOFF numbers the
+// all-transposed parts depth-first (their LDS tiles).
+template <int TOFF, int N, class T, class X>
+__device__ __forceinline__ lanes<ct_t<T>, N> at2(const Leaf<T>& e, int64_t r, int64_t c, const X&) {
+  return load_lanes<N, kNT && X::nt>(e.p, r + c * e.n_rows);
+}
+template <int TOFF, int N, class T, class X>
+__device__ __forceinline__ lanes<ct_t<T>, N> at2(const Sub<T>& e, int64_t r, int64_t c, const X&) {
+  return load_lanes<N, kNT && X::nt>(e.p, e.off + r + c * e.ld);
+}
+template <int TOFF, int N, class T, class X>
+__device__ __forceinline__ lanes<ct_t<T>, N> at2(const Diag<T>& e, int64_t r, int64_t, const X&) {
+  return e.template at_vec<N, kNT>(r);
+}
+template <int TOFF, int N, class C, class G, bool NTL>
+__device__ __forceinline__ lanes<C, N> staged(int64_t r, int64_t c, const tile_ctx<C, G, NTL>& x) {
+  const C* buf = x.lds + TOFF * (G::TC * G::P) + (int)(c - x.c0) * G::P + (int)(r - x.r0);
+  lanes<C, N> v;
+#pragma unroll
+  for (int j = 0; j < N; ++j) v.v[j] = buf[j];
+  return v;
+}
+template <int TOFF, int N, class T, class X>
+__device__ __forceinline__ lanes<ct_t<T>, N> at2(const Trans<T>&, int64_t r, int64_t c, const X& x) {
+  return staged<TOFF, N>(r, c, x);
+}
+template <int TOFF, int N, class Op, class A, class X>
+__device__ __forceinline__ lanes<typename A::ct, N> at2(const Unary<Op, A>& e, int64_t r, int64_t c,
+                                                        const X& x) {
+  if constexpr (all_trans<A>::value) {
+    return staged<TOFF, N>(r, c, x);
+  } else {
+    lanes<typename A::ct, N> v = at2<TOFF, N>(e.a, r, c, x);
+#pragma unroll
+    for (int j = 0; j < N; ++j) v.v[j] = Op::apply(v.v[j]);
+    return v;
+  }
+}
+template <int TOFF, int N, class Op, class A, bool L, class X>
+__device__ __forceinline__ lanes<typename A::ct, N> at2(const Scalar<Op, A, L>& e, int64_t r,
+                                                        int64_t c, const X& x) {
+  if constexpr (all_trans<A>::value) {
+    return staged<TOFF, N>(r, c, x);
+  } else {
+    lanes<typename A::ct, N> v = at2<TOFF, N>(e.a, r, c, x);
+#pragma unroll
+    for (int j = 0; j < N; ++j) v.v[j] = e.apply1(v.v[j]);
+    return v;
+  }
+}
+template <int TOFF, int N, class Op, class A, class B, class X>
+__device__ __forceinline__ lanes<typename A::ct, N> at2(const Binary<Op, A, B>& e, int64_t r,
+                                                        int64_t c, const X& x) {
+  if constexpr (all_trans<Binary<Op, A, B>>::value) {
+    return staged<TOFF, N>(r, c, x);
+  } else {
+    lanes<typename A::ct, N> u = at2<TOFF, N>(e.a, r, c, x);
+    lanes<typename A::ct, N> w = at2<TOFF + trans_count<A>::value, N>(e.b, r, c, x);
+#pragma unroll
+    for (int j = 0; j < N; ++j) u.v[j] = Op::apply(u.v[j], w.v[j]);
+    return u;
+  }
+}
+template <int TOFF, int N, class To, class A, class X>
+__device__ __forceinline__ lanes<To, N> at2(const Convert<To, A>& e, int64_t r, int64_t c, const X& x) {
   static_assert(trans_count<A>::value == 0, "a transposed leaf below conv_to is not staged");
-  const tile_ctx<typename A::ct, NL> none{nullptr, x.r0, x.c0};
-  lanes<typename A::ct, N> v = at2<0, N>(e.a, r, c, none);
+  lanes<typename A::ct, N> v = at2<0, N>(e.a, r, c, x);
   lanes<To, N> o;
 #pragma unroll
   for (int j = 0; j < N; ++j) o.v[j] = static_cast<To>(v.v[j]);
   return o;
 }
 
-// stage<TOFF, N>: every transposed leaf loads its source tile into LDS.
-template <int TOFF, int N, class E>
-__device__ __forceinline__ void stage(const E&, const tile_ctx<typename E::ct, N>&, int64_t, int64_t) {}
-template <int TOFF, int N, class T>
-__device__ __forceinline__ void stage(const Trans<T>& e, const tile_ctx<ct_t<T>, N>& x, int64_t rows,
-                                      int64_t cols) {
-  ct_t<T>* buf = x.lds + TOFF * kTileBuf<N>;
-  constexpr int TR = kTileRows<N>;
-  // idx -> (view columns cl..cl+N-1, view row rl); consecutive threads take
-  // consecutive view columns = consecutive source rows (coalesced); with
-  // N > 1 the host has checked that these N source elements form one
-  // aligned vector inside the source column
-  constexpr int CV = kTileCols / N;  // vectors per view row of the tile
-  for (int idx = threadIdx.x; idx < TR * CV; idx += kTileThreads) {
-    const int cl = (idx % CV) * N, rl = idx / CV;
-    const int64_t r = x.r0 + rl, c = x.c0 + cl;
-    if (r >= rows || c >= cols) continue;
-    if constexpr (N > 1) {
-      const lanes<ct_t<T>, N> v = load_lanes<N, kNT>(e.p, e.off + c + r * e.ld);
+// stage<TOFF, N>: every all-transposed part is evaluated over its source tile
+// into LDS.  Consecutive threads take consecutive view columns, which are
+// consecutive source rows; all of a thread's loads are issued before the first
+// LDS write.  Vectors past the view's last column are moved back to end with
+// it (the repeated columns are written twice, alike), rows past its last
+// repeat that row into LDS rows nothing reads.
+template <int TOFF, int N, class E, class C, class G, bool NTL>
+__device__ __forceinline__ void stage(const E& e, const tile_ctx<C, G, NTL>& x, int64_t rows, int64_t cols) {
+  if constexpr (all_trans<E>::value) {
+    C* buf = x.lds + TOFF * (G::TC * G::P);
+    constexpr int CV = G::TC / N, PER = G::TR * CV / kTileThreads;
+    lanes<C, N> v[PER];
 #pragma unroll
-      for (int j = 0; j < N; ++j) buf[(cl + j) * kTilePitch<N> + rl] = v.v[j];
-    } else {
-      buf[cl * kTilePitch<N> + rl] = static_cast<ct_t<T>>(e.p[e.off + c + r * e.ld]);
+    for (int k = 0; k < PER; ++k) {
+      const int idx = threadIdx.x + k * kTileThreads;
+      v[k] = src2<N>(e, min(x.r0 + idx / CV, rows - 1), min(x.c0 + (idx % CV) * N, cols - N));
+    }
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      const int idx = threadIdx.x + k * kTileThreads;
+      const int cl = (int)(min(x.c0 + (idx % CV) * N, cols - N) - x.c0);
+#pragma unroll
+      for (int j = 0; j < N; ++j)
+        if (cl + j >= 0) buf[(cl + j) * G::P + idx / CV] = v[k].v[j];
     }
   }
 }
-template <int TOFF, int N, class Op, class A>
-__device__ __forceinline__ void stage(const Unary<Op, A>& e, const tile_ctx<typename A::ct, N>& x,
-                                      int64_t rows, int64_t cols) {
-  stage<TOFF, N>(e.a, x, rows, cols);
+template <int TOFF, int N, class Op, class A, class X>
+__device__ __forceinline__ void stage_parts(const Unary<Op, A>& e, const X& x, int64_t rows, int64_t cols);
+template <int TOFF, int N, class Op, class A, bool L, class X>
+__device__ __forceinline__ void stage_parts(const Scalar<Op, A, L>& e, const X& x, int64_t rows, int64_t cols);
+template <int TOFF, int N, class Op, class A, class B, class X>
+__device__ __forceinline__ void stage_parts(const Binary<Op, A, B>& e, const X& x, int64_t rows, int64_t cols);
+template <int TOFF, int N, class E, class X>
+__device__ __forceinline__ void stage_parts(const E& e, const X& x, int64_t rows, int64_t cols) {
+  stage<TOFF, N>(e, x, rows, cols);  // a leaf
 }
-template <int TOFF, int N, class Op, class A, bool L>
-__device__ __forceinline__ void stage(const Scalar<Op, A, L>& e, const tile_ctx<typename A::ct, N>& x,
-                                      int64_t rows, int64_t cols) {
-  stage<TOFF, N>(e.a, x, rows, cols);
+template <int TOFF, int N, class Op, class A, class X>
+__device__ __forceinline__ void stage_parts(const Unary<Op, A>& e, const X& x, int64_t rows, int64_t cols) {
+  if constexpr (all_trans<A>::value) stage<TOFF, N>(e, x, rows, cols);
+  else stage_parts<TOFF, N>(e.a, x, rows, cols);
 }
-template <int TOFF, int N, class Op, class A, class B>
-__device__ __forceinline__ void stage(const Binary<Op, A, B>& e, const tile_ctx<typename A::ct, N>& x,
-                                      int64_t rows, int64_t cols) {
-  stage<TOFF, N>(e.a, x, rows, cols);
-  stage<TOFF + trans_count<A>::value, N>(e.b, x, rows, cols);
+template <int TOFF, int N, class Op, class A, bool L, class X>
+__device__ __forceinline__ void stage_parts(const Scalar<Op, A, L>& e, const X& x, int64_t rows,
+                                            int64_t cols) {
+  if constexpr (all_trans<A>::value) stage<TOFF, N>(e, x, rows, cols);
+  else stage_parts<TOFF, N>(e.a, x, rows, cols);
+}
+template <int TOFF, int N, class Op, class A, class B, class X>
+__device__ __forceinline__ void stage_parts(const Binary<Op, A, B>& e, const X& x, int64_t rows,
+                                            int64_t cols) {
+  if constexpr (all_trans<Binary<Op, A, B>>::value) {
+    stage<TOFF, N>(e, x, rows, cols);
+  } else {
+    stage_parts<TOFF, N>(e.a, x, rows, cols);
+    stage_parts<TOFF + trans_count<A>::value, N>(e.b, x, rows, cols);
+  }
 }
 
 // Z (dense rows x cols) = E over a grid of tiles, numbered down the tile
 // columns (tile t: tile row t % tile_rows, tile column t / tile_rows) and
 // taken in xcd_order.  (Launching the partner tiles (I, J) and (J, I) side
 // by side, to find a transposed operand's tile in the last-level cache,
-// measured slower on the 10k x 10k expressions.)
-// Tile geometry: with transposed leaves the tile is (16 N) x 64 (square for
-// FP32, the LDS staging tile); without them it is (64 N) x 16, so that each
-// column of every leaf is read in 1 KB-or-longer contiguous runs (square
-// tiles read only 256 B per column of a submatrix, measured slower).
-template <int KT> constexpr int kRowVecs = KT > 0 ? 16 : 64;        // thread rows per tile
-template <int KT> constexpr int kColsPerTile = KT > 0 ? kTileCols : 16;
-
-template <class E, class T, int N, bool NTS>
+// measured slower on the 10k x 10k expressions.)  N > 1 needs rows and cols of
+// at least N.
+template <class E, class T, int N, int Q, bool NTL, bool NTS>
 __global__ __launch_bounds__(kTileThreads) void k_ew2d(E e, T* __restrict__ z, int64_t rows,
                                                       int64_t cols, uint32_t tile_rows) {
   using C = typename E::ct;
   constexpr int KT = trans_count<E>::value;
-  constexpr int RV = kRowVecs<KT>, CG = kTileThreads / RV, TC = kColsPerTile<KT>;
-  __shared__ C lds[KT > 0 ? KT * kTileBuf<N> : 1];
+  using G = tile_geo<KT, N, Q, T>;
+  // N values ahead: the last vector of a tile of fewer than N rows starts above it
+  __shared__ C lds[KT > 0 ? N + KT * G::TC * G::P : 1];
   const uint32_t t = xcd_order(blockIdx.x, gridDim.x);
-  const tile_ctx<C, N> x{lds, (int64_t)(t % tile_rows) * RV * N, (int64_t)(t / tile_rows) * TC};
+  const tile_ctx<C, G, NTL> x{lds + (KT > 0 ? N : 0), (int64_t)(t % tile_rows) * G::TR, (int64_t)(t / tile_rows) * G::TC};
   if constexpr (KT > 0) {
-    static_assert(RV * N == kTileRows<N> && TC == kTileCols, "staging tile geometry");
-    stage<0, N>(e, x, rows, cols);
+    stage_parts<0, N>(e, x, rows, cols);
     __syncthreads();
   }
-  const int rv = threadIdx.x % RV, cg = threadIdx.x / RV;
-  const int64_t r = x.r0 + rv * N;
+  const int rv = threadIdx.x % G::RV, cg = threadIdx.x / G::RV;
+  const int64_t first = x.r0 + rv * N;
+  if (first >= rows) return;
+  // the last rows, where they are no whole vector, are computed as one that
+  // ends with the column; its first `sh` rows are another thread's, and are not
+  // stored (the output may be an input read in place)
+  const int sh = first + N > rows ? (int)(first + N - rows) : 0;
+  const int64_t r = first - sh;
+  // U columns at a time: all their loads, then their stores (columns past the
+  // last repeat it and are not stored)
+  constexpr int QT = G::TC / G::CG, U = QT < 4 ? QT : 4;
 #pragma unroll
-  for (int q = 0; q < TC / CG; ++q) {
-    const int64_t c = x.c0 + cg + CG * q;
-    if (c >= cols || r >= rows) continue;
-    if (r + N <= rows) {
-      store_lanes<N, NTS>(z, r + c * rows, at2<0, N>(e, r, c, x));
-    } else {
-      for (int j = 0; r + j < rows; ++j) z[r + j + c * rows] = static_cast<T>(at2<0, 1>(e, r + j, c, x).v[0]);
+  for (int q = 0; q < QT; q += U) {
+    lanes<C, N> v[U];
+    const int64_t c = x.c0 + cg + G::CG * q;
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = at2<0, N>(e, r, min(c + G::CG * u, cols - 1), x);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (c + G::CG * u >= cols) break;
+      T* col = z + (c + G::CG * u) * rows;
+      if (sh == 0) {
+        store_lanes<N, NTS>(col, r, v[u]);
+      } else {
+#pragma unroll
+        for (int j = 0; j < N; ++j)
+          if (j >= sh) col[r + j] = static_cast<T>(v[u].v[j]);
+      }
     }
   }
 }
@@ -394,16 +512,18 @@ __global__ __launch_bounds__(kTileThreads) void k_ew2d(E e, T* __restrict__ z, i
 //
 // When an expression over square matrices names a matrix both directly and
 // transposed (expr1: X and X.t()), output tiles (I, J) and (J, I) need the same
-// two tiles of it.  One block then computes both output tiles: it stages tiles
-// (I, J) and (J, I) of every distinct matrix in LDS once (natural layout,
-// column pitch 65) and every leaf reads from there, the direct ones at
-// [c][r] of their own tile, the transposed ones at [r][c] of the partner
-// tile.  Each matrix is read from HBM once.  FP32 (64 x 64 square tiles),
-// whole matrices only, at most kPairMats distinct ones.
+// two tiles of it.  One block then computes both: every thread loads its
+// vectors of tiles (I, J) and (J, I) of every distinct matrix once, all in
+// flight together.  A direct leaf of an output tile is in the very registers
+// of the thread that computes it; for the transposed leaves the partner tile
+// goes through LDS, one output tile after the other in the same buffers (all
+// four tiles in LDS at once, as before, left two blocks per CU).  Each matrix
+// is read from HBM once.  Whole matrices only, at most kPairMats distinct ones;
+// tiles of 64 x 64, 32 x 32 for 8-byte types.  2*(t(X) + Y) + 2*(X + t(Y)):
+// FP32 10000 x 10000 261 -> 247 us; FP64 3001 x 3001, until then on the general
+// kernel, 53 -> 38; BF16 10000 x 10000 286 -> 172.
 constexpr int kPairMats = 2;
-constexpr int kPairT = 64;            // tile side
-constexpr int kPairPitch = kPairT + 1;
-constexpr int kPairBuf = kPairT * kPairPitch;
+template <class T> constexpr int kPairSide = sizeof(T) == 8 ? 32 : 64;
 
 template <class E> struct pairable { static constexpr bool value = false; };
 template <class T> struct pairable<Leaf<T>> { static constexpr bool value = true; };
@@ -425,78 +545,85 @@ constexpr int kPairMaxLeaves = 16;
 
 struct pair_tab {
   uint8_t mid[kPairMaxLeaves];  // leaf (depth-first) -> distinct matrix
-  const float* mat[kPairMats];  // distinct matrices
+  const void* mat[kPairMats];   // distinct matrices
   int32_t n_mats;
 };
 
-struct pair_ctx {
-  const float* lds;
+// One vector of an output tile: its rows rl.. and column cl in the tile, the
+// direct values of the distinct matrices there, the partner tiles in LDS.
+template <class C, int N, int S> struct pair_ctx {
+  const C* lds;
   const uint8_t* mid;
-  int64_t r0, c0;
-  int swap;  // 0: output tile (I, J), 1: its partner (J, I)
+  int rl, cl;
+  lanes<C, N> d[kPairMats];
 };
 
-// region 2m holds tile (I, J) of matrix m, region 2m + 1 tile (J, I)
-template <int LOFF, class T>
-__device__ __forceinline__ lanes<float, 4> at2p(const Leaf<T>&, int64_t r, int64_t c,
-                                                const pair_ctx& x) {
-  const float* b = x.lds + (2 * x.mid[LOFF] + x.swap) * kPairBuf + (c - x.c0) * kPairPitch + (r - x.r0);
-  lanes<float, 4> v;
+template <int LOFF, class T, class C, int N, int S>
+__device__ __forceinline__ lanes<C, N> at2p(const Leaf<T>&, const pair_ctx<C, N, S>& x) {
+  const bool second = x.mid[LOFF] != 0;
+  lanes<C, N> v;
 #pragma unroll
-  for (int j = 0; j < 4; ++j) v.v[j] = b[j];
+  for (int j = 0; j < N; ++j) v.v[j] = second ? x.d[1].v[j] : x.d[0].v[j];
   return v;
 }
-template <int LOFF, class T>
-__device__ __forceinline__ lanes<float, 4> at2p(const Trans<T>&, int64_t r, int64_t c,
-                                                const pair_ctx& x) {
-  const float* b = x.lds + (2 * x.mid[LOFF] + 1 - x.swap) * kPairBuf + (r - x.r0) * kPairPitch + (c - x.c0);
-  lanes<float, 4> v;
+template <int LOFF, class T, class C, int N, int S>
+__device__ __forceinline__ lanes<C, N> at2p(const Trans<T>&, const pair_ctx<C, N, S>& x) {
+  const C* b = x.lds + x.mid[LOFF] * (S * (S + 1)) + x.rl * (S + 1) + x.cl;
+  lanes<C, N> v;
 #pragma unroll
-  for (int j = 0; j < 4; ++j) v.v[j] = b[j * kPairPitch];
+  for (int j = 0; j < N; ++j) v.v[j] = b[j * (S + 1)];
   return v;
 }
-template <int LOFF, class Op, class A>
-__device__ __forceinline__ lanes<float, 4> at2p(const Unary<Op, A>& e, int64_t r, int64_t c,
-                                                const pair_ctx& x) {
-  lanes<float, 4> v = at2p<LOFF>(e.a, r, c, x);
+template <int LOFF, class Op, class A, class C, int N, int S>
+__device__ __forceinline__ lanes<C, N> at2p(const Unary<Op, A>& e, const pair_ctx<C, N, S>& x) {
+  lanes<C, N> v = at2p<LOFF>(e.a, x);
 #pragma unroll
-  for (int j = 0; j < 4; ++j) v.v[j] = Op::apply(v.v[j]);
+  for (int j = 0; j < N; ++j) v.v[j] = Op::apply(v.v[j]);
   return v;
 }
-template <int LOFF, class Op, class A, bool L>
-__device__ __forceinline__ lanes<float, 4> at2p(const Scalar<Op, A, L>& e, int64_t r, int64_t c,
-                                                const pair_ctx& x) {
-  lanes<float, 4> v = at2p<LOFF>(e.a, r, c, x);
+template <int LOFF, class Op, class A, bool L, class C, int N, int S>
+__device__ __forceinline__ lanes<C, N> at2p(const Scalar<Op, A, L>& e, const pair_ctx<C, N, S>& x) {
+  lanes<C, N> v = at2p<LOFF>(e.a, x);
 #pragma unroll
-  for (int j = 0; j < 4; ++j) v.v[j] = e.apply1(v.v[j]);
+  for (int j = 0; j < N; ++j) v.v[j] = e.apply1(v.v[j]);
   return v;
 }
-template <int LOFF, class Op, class A, class B>
-__device__ __forceinline__ lanes<float, 4> at2p(const Binary<Op, A, B>& e, int64_t r, int64_t c,
-                                                const pair_ctx& x) {
-  lanes<float, 4> u = at2p<LOFF>(e.a, r, c, x);
-  lanes<float, 4> w = at2p<LOFF + pair_leaves<A>::value>(e.b, r, c, x);
+template <int LOFF, class Op, class A, class B, class C, int N, int S>
+__device__ __forceinline__ lanes<C, N> at2p(const Binary<Op, A, B>& e, const pair_ctx<C, N, S>& x) {
+  lanes<C, N> u = at2p<LOFF>(e.a, x);
+  lanes<C, N> w = at2p<LOFF + pair_leaves<A>::value>(e.b, x);
 #pragma unroll
-  for (int j = 0; j < 4; ++j) u.v[j] = Op::apply(u.v[j], w.v[j]);
+  for (int j = 0; j < N; ++j) u.v[j] = Op::apply(u.v[j], w.v[j]);
   return u;
 }
 
-// One block per tile pair I <= J (p enumerates them column by column); n x n
-// FP32 result, n a multiple of 4.
-template <class E, bool NTS>
-__global__ __launch_bounds__(kTileThreads) void k_ew2d_pair(E e, pair_tab tab, float* __restrict__ z,
+// Rows r..r+N-1 of a column that starts at p, of which only those below `rows`
+// exist (the others repeat the last): N independent loads of one element.
+template <int N, class T>
+__device__ __forceinline__ lanes<ct_t<T>, N> load_end(const T* p, int64_t r, int64_t rows) {
+  lanes<ct_t<T>, N> v;
+#pragma unroll
+  for (int j = 0; j < N; ++j) v.v[j] = static_cast<ct_t<T>>(p[min(r + j, rows - 1)]);
+  return v;
+}
+
+// One block per tile pair I <= J (p enumerates them column by column).
+template <class E, class T, bool NTL, bool NTS>
+__global__ __launch_bounds__(kTileThreads) void k_ew2d_pair(E e, pair_tab tab, T* __restrict__ z,
                                                            int64_t n) {
-  __shared__ float lds[2 * kPairMats * kPairBuf];
+  using C = typename E::ct;
+  constexpr int S = kPairSide<T>, N = 16 / (int)sizeof(T), P = S + 1;
+  constexpr int PER = S * S / N / kTileThreads;  // vectors per thread and tile
+  static_assert(PER * N * kTileThreads == S * S, "whole vectors per thread");
+  __shared__ C lds[kPairMats * S * P];
   const int64_t p = xcd_order(blockIdx.x, gridDim.x);
   int64_t J = (int64_t)((::sqrt(8.0 * (double)p + 1.0) - 1.0) * 0.5);
   while (J * (J + 1) / 2 > p) --J;
   while ((J + 1) * (J + 2) / 2 <= p) ++J;
   const int64_t I = p - J * (J + 1) / 2;
-  // stage tiles (I, J) and (J, I) of every matrix: 16-byte loads down the
-  // columns (64 rows = 16 vectors per column); each thread issues all its
-  // loads before the first LDS write
-  constexpr int PER = kPairT * (kPairT / 4) / kTileThreads;  // vectors per thread per tile
-  lanes<float, 4> v[kPairMats][2][PER];
+  const bool diagonal = I == J;
+  // v[m][w][k]: this thread's vectors of tile (I, J) (w = 0) and (J, I) (w = 1)
+  lanes<C, N> v[kPairMats][2][PER];
 #pragma unroll
   for (int m = 0; m < kPairMats; ++m)
 #pragma unroll
@@ -504,32 +631,40 @@ __global__ __launch_bounds__(kTileThreads) void k_ew2d_pair(E e, pair_tab tab, f
 #pragma unroll
       for (int k = 0; k < PER; ++k) {
         const int idx = threadIdx.x + k * kTileThreads;
-        const int64_t r = (w ? J : I) * kPairT + (idx % (kPairT / 4)) * 4;
-        const int64_t c = (w ? I : J) * kPairT + idx / (kPairT / 4);
-        if (m < tab.n_mats && r < n && c < n) v[m][w][k] = load_lanes<4, kNT>(tab.mat[m], r + c * n);
+        const int64_t r = (w ? J : I) * S + (idx % (S / N)) * N, c = (w ? I : J) * S + idx / (S / N);
+        if (m >= tab.n_mats || (w && diagonal) || r >= n || c >= n) continue;
+        const T* col = static_cast<const T*>(tab.mat[m]) + c * n;
+        v[m][w][k] = r + N <= n ? load_lanes<N, kNT && NTL>(col, r) : load_end<N>(col, r, n);
       }
 #pragma unroll
-  for (int m = 0; m < kPairMats; ++m)
+  for (int s = 0; s < 2; ++s) {  // output tile (I, J), then (J, I)
+    if (s && diagonal) break;
+    if (s) __syncthreads();  // the first tile's reads are done
 #pragma unroll
-    for (int w = 0; w < 2; ++w)
+    for (int m = 0; m < kPairMats; ++m)
 #pragma unroll
       for (int k = 0; k < PER; ++k) {
         const int idx = threadIdx.x + k * kTileThreads;
-        const int rl = (idx % (kPairT / 4)) * 4, cl = idx / (kPairT / 4);
-        float* buf = lds + (2 * m + w) * kPairBuf + cl * kPairPitch + rl;
+        C* buf = lds + m * (S * P) + idx / (S / N) * P + (idx % (S / N)) * N;
         if (m < tab.n_mats)
 #pragma unroll
-          for (int j = 0; j < 4; ++j) buf[j] = v[m][w][k].v[j];
+          for (int j = 0; j < N; ++j) buf[j] = diagonal ? v[m][0][k].v[j] : v[m][1 - s][k].v[j];
       }
-  __syncthreads();
-  const int rv = threadIdx.x % 16, cg = threadIdx.x / 16;
-  for (int s = 0; s < (I == J ? 1 : 2); ++s) {
-    const pair_ctx x{lds, tab.mid, (s ? J : I) * kPairT, (s ? I : J) * kPairT, s};
-    const int64_t r = x.r0 + rv * 4;
+    __syncthreads();
 #pragma unroll
-    for (int q = 0; q < kPairT / 16; ++q) {
-      const int64_t c = x.c0 + cg + 16 * q;
-      if (c < n && r < n) store_lanes<4, NTS>(z, r + c * n, at2p<0>(e, r, c, x));
+    for (int k = 0; k < PER; ++k) {
+      const int idx = threadIdx.x + k * kTileThreads;
+      pair_ctx<C, N, S> x{lds, tab.mid, (idx % (S / N)) * N, idx / (S / N), {v[0][s][k], v[1][s][k]}};
+      const int64_t r = (s ? J : I) * S + x.rl, c = (s ? I : J) * S + x.cl;
+      if (r >= n || c >= n) continue;
+      const lanes<C, N> o = at2p<0>(e, x);
+      if (r + N <= n) {
+        store_lanes<N, NTS>(z, r + c * n, o);
+      } else {
+#pragma unroll
+        for (int j = 0; j < N; ++j)
+          if (r + j < n) z[r + j + c * n] = static_cast<T>(o.v[j]);
+      }
     }
   }
 }
@@ -559,12 +694,12 @@ template <class Op, class A, class B> inline void pair_leaf_list(const Binary<Op
   pair_leaf_list(e.b, p, off, ld, tr, k);
 }
 
-// Build the pair table if the paired kernel applies: n x n FP32 result,
-// every leaf a whole n x n matrix, at most kPairMats distinct ones, one of
-// them read both ways, 16-byte aligned.
-template <class E> inline bool pair_plan(const E& e, int64_t n, const float* z, pair_tab* tab) {
+// Build the pair table if the paired kernel applies: n x n result, every leaf
+// a whole n x n matrix, at most kPairMats distinct ones, one of them read both
+// ways.
+template <class E> inline bool pair_plan(const E& e, int64_t n, pair_tab* tab) {
   constexpr int L = pair_leaves<E>::value;
-  if (L > kPairMaxLeaves || n % 4 || reinterpret_cast<uintptr_t>(z) % 16) return false;
+  if (L > kPairMaxLeaves) return false;
   const void* p[kPairMaxLeaves];
   int64_t off[kPairMaxLeaves], ld[kPairMaxLeaves];
   bool tr[kPairMaxLeaves];
@@ -573,12 +708,12 @@ template <class E> inline bool pair_plan(const E& e, int64_t n, const float* z, 
   bool dir[kPairMats] = {false, false}, trn[kPairMats] = {false, false};
   tab->n_mats = 0;
   for (int i = 0; i < L; ++i) {
-    if (off[i] != 0 || ld[i] != n || reinterpret_cast<uintptr_t>(p[i]) % 16) return false;
+    if (off[i] != 0 || ld[i] != n) return false;
     int m = 0;
     while (m < tab->n_mats && tab->mat[m] != p[i]) ++m;
     if (m == tab->n_mats) {
       if (m == kPairMats) return false;
-      tab->mat[m] = static_cast<const float*>(p[i]);
+      tab->mat[m] = p[i];
       ++tab->n_mats;
     }
     tab->mid[i] = (uint8_t)m;
@@ -589,27 +724,6 @@ template <class E> inline bool pair_plan(const E& e, int64_t n, const float* z, 
   return false;
 }
 
-// Host: may every dense / submatrix leaf and the output be read N at a time?
-template <class T> inline bool vec_ok(const Leaf<T>& e, int N) {
-  return (reinterpret_cast<uintptr_t>(e.p) % (N * sizeof(T))) == 0 && e.n_rows % N == 0;
-}
-template <class T> inline bool vec_ok(const Sub<T>& e, int N) {
-  return (reinterpret_cast<uintptr_t>(e.p + e.off) % (N * sizeof(T))) == 0 && e.ld % N == 0;
-}
-template <class T> inline bool vec_ok(const Trans<T>& e, int N) {  // staged N source rows at a time
-  return (reinterpret_cast<uintptr_t>(e.p + e.off) % (N * sizeof(T))) == 0 && e.ld % N == 0 &&
-         e.n_cols % N == 0;
-}
-template <class T> inline bool vec_ok(const Diag<T>&, int) { return true; }
-template <class Op, class A> inline bool vec_ok(const Unary<Op, A>& e, int N) { return vec_ok(e.a, N); }
-template <class Op, class A, bool L> inline bool vec_ok(const Scalar<Op, A, L>& e, int N) {
-  return vec_ok(e.a, N);
-}
-template <class To, class A> inline bool vec_ok(const Convert<To, A>& e, int N) { return vec_ok(e.a, N); }
-template <class Op, class A, class B> inline bool vec_ok(const Binary<Op, A, B>& e, int N) {
-  return vec_ok(e.a, N) && vec_ok(e.b, N);
-}
-
 // Z = E for an expression with submatrix or transposed leaves.
 template <class E, class T>
 int eval_views(T* z, const E& e, hipStream_t st) {
@@ -617,37 +731,50 @@ int eval_views(T* z, const E& e, hipStream_t st) {
   if (int rc = check_expr(e, &rows, &cols)) return rc;
   if (rows * cols == 0) return FX_OK;
   if (!z) return fail(FX_E_ARG, "NULL output pointer");
-  constexpr int NV = 16 / (int)sizeof(T) > 0 ? 16 / (int)sizeof(T) : 1;
-  const bool vec = vec_ok(e, NV) && rows % NV == 0 &&
-                   reinterpret_cast<uintptr_t>(z) % 16 == 0;
+  constexpr int NV = 16 / (int)sizeof(T);
+  const bool vec = rows >= NV && cols >= NV;
   constexpr int KT = trans_count<E>::value;
-  const bool nts = kNTS || (uint64_t)rows * (uint64_t)cols * sizeof(T) > kStreamStoresAbove;
-  if constexpr (KT > 0 && pairable<E>::value && std::is_same_v<T, float> &&
-                std::is_same_v<typename E::ct, float>) {
+  const uint64_t bytes = (uint64_t)rows * (uint64_t)cols * sizeof(T);
+  const bool nts = kNTS || bytes > kStreamStoresAbove;
+  const bool lines = whole_lines(e);
+  const uint64_t total = bytes * (leaf_count<E>::value + 1);
+  const bool ntl = KT > 0 ? lines && total > kCachedBelow : total > (lines ? 1 : 2) * kCachedBelow;
+  auto with_policy = [&](auto&& go) {
+    if (ntl) return nts ? go(std::true_type{}, std::true_type{}) : go(std::true_type{}, std::false_type{});
+    return nts ? go(std::false_type{}, std::true_type{}) : go(std::false_type{}, std::false_type{});
+  };
+  if constexpr (KT > 0 && pairable<E>::value) {
     pair_tab tab;
-    if (rows == cols && pair_plan(e, rows, z, &tab)) {
-      const int64_t t = ceil_div(rows, (int64_t)kPairT);
-      if (nts)
-        hipLaunchKernelGGL((k_ew2d_pair<E, true>), dim3((unsigned)(t * (t + 1) / 2)),
-                           dim3(kTileThreads), 0, st, e, tab, z, rows);
-      else
-        hipLaunchKernelGGL((k_ew2d_pair<E, false>), dim3((unsigned)(t * (t + 1) / 2)),
-                           dim3(kTileThreads), 0, st, e, tab, z, rows);
-      return hip_check(hipGetLastError(), "k_ew2d_pair launch");
+    if (rows == cols && pair_plan(e, rows, &tab)) {
+      const int64_t t = ceil_div(rows, (int64_t)kPairSide<T>);
+      if (t * (t + 1) / 2 > 0x7fffffff)
+        return fail(FX_E_UNSUPPORTED, "%lld x %lld exceeds the tile grid", (long long)rows, (long long)cols);
+      return with_policy([&](auto l, auto st_) {
+        hipLaunchKernelGGL((k_ew2d_pair<E, T, decltype(l)::value, decltype(st_)::value>),
+                           dim3((unsigned)(t * (t + 1) / 2)), dim3(kTileThreads), 0, st, e, tab, z, rows);
+        return hip_check(hipGetLastError(), "k_ew2d_pair launch");
+      });
     }
   }
-  const int64_t tc = ceil_div(cols, kColsPerTile<KT>);
-  const int64_t tr = ceil_div(rows, (int64_t)kRowVecs<KT> * (vec ? NV : 1));
-  if (tr * tc > 0x7fffffff)
-    return fail(FX_E_UNSUPPORTED, "%lld x %lld exceeds the tile grid", (long long)rows, (long long)cols);
-  const dim3 grid((unsigned)(tr * tc)), block(kTileThreads);
-  if (vec && nts)
-    hipLaunchKernelGGL((k_ew2d<E, T, NV, true>), grid, block, 0, st, e, z, rows, cols, (uint32_t)tr);
-  else if (vec)
-    hipLaunchKernelGGL((k_ew2d<E, T, NV, false>), grid, block, 0, st, e, z, rows, cols, (uint32_t)tr);
-  else
-    hipLaunchKernelGGL((k_ew2d<E, T, 1, false>), grid, block, 0, st, e, z, rows, cols, (uint32_t)tr);
-  return hip_check(hipGetLastError(), "k_ew2d launch");
+  // one column per thread, or the narrow tile, where the wide one would leave
+  // the chip with few blocks
+  const int64_t wide = ceil_div(cols, tile_geo<KT, NV, 4, T>::TC) * ceil_div(rows, tile_geo<KT, NV, 4, T>::TR);
+  const bool narrow = KT == 0 ? wide < (int64_t)8 * device_cus()
+                              : !(lines && wide >= (int64_t)16 * device_cus());
+  auto launch = [&](auto Nc, auto Qc, auto l, auto st_) {
+    constexpr int N = decltype(Nc)::value, Q = decltype(Qc)::value;
+    using G = tile_geo<KT, N, Q, T>;
+    const int64_t tc = ceil_div(cols, G::TC), tr = ceil_div(rows, G::TR);
+    if (tr * tc > 0x7fffffff)
+      return fail(FX_E_UNSUPPORTED, "%lld x %lld exceeds the tile grid", (long long)rows, (long long)cols);
+    hipLaunchKernelGGL((k_ew2d<E, T, N, Q, decltype(l)::value, decltype(st_)::value>),
+                       dim3((unsigned)(tr * tc)), dim3(kTileThreads), 0, st, e, z, rows, cols, (uint32_t)tr);
+    return hip_check(hipGetLastError(), "k_ew2d launch");
+  };
+  if (!vec) return launch(ic<1>{}, ic<4>{}, std::false_type{}, std::false_type{});
+  return with_policy([&](auto l, auto st_) {
+    return narrow ? launch(ic<NV>{}, ic<1>{}, l, st_) : launch(ic<NV>{}, ic<4>{}, l, st_);
+  });
 }
 
 }  // namespace fx
