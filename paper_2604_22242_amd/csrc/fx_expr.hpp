@@ -105,6 +105,137 @@ template <class T> inline Leaf<T> as_expr(const dmat<T>& m) { return m.expr(); }
 
 // ---- operators ---------------------------------------------------------------
 
+// Several lanes of a unary operator at once.  MOD is an exact change of sign
+// (negation, absolute value, both) made first; it costs nothing, as a source
+// modifier of the instructions that use the operand.
+struct mod_none { template <class C> __device__ static C f(C x) { return x; } };
+struct mod_neg { template <class C> __device__ static C f(C x) { return -x; } };
+struct mod_abs {
+  __device__ static float f(float x) { return __builtin_fabsf(x); }
+  __device__ static double f(double x) { return __builtin_fabs(x); }
+};
+struct mod_nabs { template <class C> __device__ static C f(C x) { return -mod_abs::f(x); } };
+
+// The same value as x, but not one that the compiler can relate to it: keeps a
+// modifier used on both sides of a branch from being computed ahead of it.
+__device__ __forceinline__ float fresh(float x) {
+  asm("" : "+v"(x));
+  return x;
+}
+// Does the condition hold in any active lane of the wave?
+__device__ __forceinline__ bool any_lane(bool c) { return __builtin_amdgcn_ballot_w64(c) != 0; }
+
+// FP32 exp and sqrt.  Both library functions spend a third to a half of their
+// instructions on arguments that hardly ever come (overflow and underflow, a
+// result below the normal range, scaling of tiny arguments).  Here the common
+// range is computed straight, one check covers all N lanes of a thread, and
+// where any lane of the wave falls outside, that lane takes the library
+// function: each element's value depends on it alone.  In issue slots per lane
+// (a transcendental takes four): exp 16 -> 12.5, sqrt 19 -> 10.
+//
+// exp, |x| <= 87: x log2(e) = n + f with n the nearest integer; log2(e) in two
+// parts, the product's rounding error recovered by an FMA, so that f is rounded
+// once; 2^f in hardware; 2^n added to the exponent field (the result and 2^f
+// are normal there).  n is the low end of t, whose ulp is 1.
+__device__ __forceinline__ float exp_common(float x) {
+#pragma clang fp contract(off)
+  const float hi = 0x1.715476p+0f, lo = 0x1.4ae0cp-26f;  // log2(e)
+  const float t = __builtin_fmaf(x, hi, 0x1.8p+23f);
+  const float n = t - 0x1.8p+23f;
+  const float p = x * hi;
+  const float c = __builtin_fmaf(x, lo, __builtin_fmaf(x, hi, -p));
+  const float e = __builtin_amdgcn_exp2f((p - n) + c);
+  return __uint_as_float(__float_as_uint(e) + (__float_as_uint(t) << 23));
+}
+constexpr float kExpCommon = 87.f;
+// r where x lies in the common range, the library's value where not.
+template <class MOD> __device__ __forceinline__ float exp_rare(float x, float r) {
+  const float v = MOD::f(fresh(x));
+  const bool out = !(__builtin_fabsf(v) <= kExpCommon);
+  return any_lane(out) && out ? ::expf(v) : r;
+}
+// IN_PLACE: the check first, for callers short of registers (the tapes, where
+// results held beside the arguments until a later check cost a wave per SIMD);
+// else the arithmetic does not wait for the check (BF16 matrix workload 296 us
+// against 300).
+template <class MOD, bool IN_PLACE, int N> __device__ __forceinline__ void exp_lanes(float (&x)[N]) {
+  float m = __builtin_fabsf(x[0]);
+#pragma unroll
+  for (int j = 1; j < N; ++j) m = __builtin_elementwise_maximum(m, __builtin_fabsf(x[j]));  // NaN propagates
+  if constexpr (IN_PLACE) {
+    if (__builtin_expect(!any_lane(!(m <= kExpCommon)), 1)) {
+#pragma unroll
+      for (int j = 0; j < N; ++j) x[j] = exp_common(MOD::f(fresh(x[j])));
+    } else {
+#pragma unroll
+      for (int j = 0; j < N; ++j) x[j] = exp_rare<MOD>(x[j], exp_common(MOD::f(x[j])));
+    }
+  } else {
+    float r[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) r[j] = exp_common(MOD::f(x[j]));
+    if (__builtin_expect(any_lane(!(m <= kExpCommon)), 0)) {
+#pragma unroll
+      for (int j = 0; j < N; ++j) r[j] = exp_rare<MOD>(x[j], r[j]);
+    }
+#pragma unroll
+    for (int j = 0; j < N; ++j) x[j] = r[j];
+  }
+}
+
+// sqrt, 2^-96 <= x finite, and 0: s = x y from the hardware's y ~ 1 / sqrt(x),
+// then one Newton step on the exact residual x - s s.  Correctly rounded, as
+// the library's: compared for every FP32 in that range.  (The addend, nothing to
+// x from 2^-96 on, keeps y finite at 0.)
+__device__ __forceinline__ float sqrt_common(float x) {
+#pragma clang fp contract(off)
+  const float y = __builtin_amdgcn_rsqf(x + 0x1p-125f);
+  const float s = x * y;
+  return __builtin_fmaf(__builtin_fmaf(-s, s, x), 0.5f * y, s);
+}
+constexpr float kSqrtFrom = 0x1p-96f, kSqrtTo = 0x1.fffffep+127f;
+template <class MOD> __device__ __forceinline__ float sqrt_rare(float x, float r) {
+  const float v = MOD::f(fresh(x));
+  const bool out = !(v >= kSqrtFrom && v <= kSqrtTo) && v != 0.f;
+  return any_lane(out) && out ? ::sqrtf(v) : r;
+}
+template <class MOD, bool IN_PLACE, int N> __device__ __forceinline__ void sqrt_lanes(float (&x)[N]) {
+  float low = MOD::f(x[0]), high = low;
+#pragma unroll
+  for (int j = 1; j < N; ++j) {
+    low = __builtin_fminf(low, MOD::f(x[j]));
+    high = __builtin_elementwise_maximum(high, MOD::f(x[j]));  // NaN propagates
+  }
+  const bool rare = any_lane(!(low >= kSqrtFrom) || !(high <= kSqrtTo));
+  if constexpr (IN_PLACE) {
+    if (__builtin_expect(!rare, 1)) {
+#pragma unroll
+      for (int j = 0; j < N; ++j) x[j] = sqrt_common(MOD::f(fresh(x[j])));
+    } else {
+#pragma unroll
+      for (int j = 0; j < N; ++j) x[j] = sqrt_rare<MOD>(x[j], sqrt_common(MOD::f(x[j])));
+    }
+  } else {
+    float r[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) r[j] = sqrt_common(MOD::f(x[j]));
+    if (__builtin_expect(rare, 0)) {
+#pragma unroll
+      for (int j = 0; j < N; ++j) r[j] = sqrt_rare<MOD>(x[j], r[j]);
+    }
+#pragma unroll
+    for (int j = 0; j < N; ++j) x[j] = r[j];
+  }
+}
+template <class MOD, bool, int N> __device__ __forceinline__ void exp_lanes(double (&x)[N]) {
+#pragma unroll
+  for (int j = 0; j < N; ++j) x[j] = ::exp(MOD::f(x[j]));
+}
+template <class MOD, bool, int N> __device__ __forceinline__ void sqrt_lanes(double (&x)[N]) {
+#pragma unroll
+  for (int j = 0; j < N; ++j) x[j] = ::sqrt(MOD::f(x[j]));
+}
+
 struct op_add { template <class C> __device__ static C apply(C a, C b) { return a + b; } };
 struct op_sub { template <class C> __device__ static C apply(C a, C b) { return a - b; } };
 struct op_schur { template <class C> __device__ static C apply(C a, C b) { return a * b; } };
@@ -118,12 +249,10 @@ struct op_abs {
   __device__ static double apply(double a) { return ::fabs(a); }
 };
 struct op_exp {
-  __device__ static float apply(float a) { return ::expf(a); }
-  __device__ static double apply(double a) { return ::exp(a); }
+  template <class MOD, class C, int N> __device__ static void lanes(C (&x)[N]) { exp_lanes<MOD, false>(x); }
 };
 struct op_sqrt {
-  __device__ static float apply(float a) { return ::sqrtf(a); }
-  __device__ static double apply(double a) { return ::sqrt(a); }
+  template <class MOD, class C, int N> __device__ static void lanes(C (&x)[N]) { sqrt_lanes<MOD, false>(x); }
 };
 struct op_log {
   __device__ static float apply(float a) { return ::logf(a); }
@@ -146,16 +275,50 @@ struct op_gt {
 
 // ---- inner nodes ---------------------------------------------------------------
 
+// N lanes of a unary operator: in one go (Op::lanes) or one by one.
+template <class Op, class MOD, class C, int N> __device__ __forceinline__ void apply_lanes(C (&x)[N]) {
+  if constexpr (std::is_same_v<Op, op_exp> || std::is_same_v<Op, op_sqrt>) {
+    Op::template lanes<MOD>(x);
+  } else {
+#pragma unroll
+    for (int j = 0; j < N; ++j) x[j] = Op::apply(MOD::f(x[j]));
+  }
+}
+
+template <class Op, class A> struct Unary;
+// The operand of a unary operator, the negations and absolute values directly
+// on it (outermost last) split off as its MOD.
+template <class A> struct modded {
+  using mod = mod_none;
+  __host__ __device__ static const A& of(const A& a) { return a; }
+};
+template <class A> struct modded<Unary<op_neg, A>> {
+  using mod = mod_neg;
+  __host__ __device__ static const A& of(const Unary<op_neg, A>& u) { return u.a; }
+};
+template <class A> struct modded<Unary<op_abs, A>> {
+  using mod = mod_abs;
+  __host__ __device__ static const A& of(const Unary<op_abs, A>& u) { return u.a; }
+};
+template <class A> struct modded<Unary<op_neg, Unary<op_abs, A>>> {
+  using mod = mod_nabs;
+  __host__ __device__ static const A& of(const Unary<op_neg, Unary<op_abs, A>>& u) { return u.a.a; }
+};
+
 template <class Op, class A> struct Unary : expr_tag {
   using ct = typename A::ct;
   using storage = typename A::storage;
+  using arg = modded<A>;
   A a;
-  __device__ __forceinline__ ct at(int64_t i) const { return Op::apply(a.at(i)); }
+  __device__ __forceinline__ ct at(int64_t i) const {
+    ct x[1] = {arg::of(a).at(i)};
+    apply_lanes<Op, typename arg::mod>(x);
+    return x[0];
+  }
   template <int N, bool NT>
   __device__ __forceinline__ lanes<ct, N> at_vec(int64_t i) const {
-    lanes<ct, N> x = a.template at_vec<N, NT>(i);
-#pragma unroll
-    for (int j = 0; j < N; ++j) x.v[j] = Op::apply(x.v[j]);
+    lanes<ct, N> x = arg::of(a).template at_vec<N, NT>(i);
+    apply_lanes<Op, typename arg::mod>(x.v);
     return x;
   }
   void collect(leaf_info& li) const { a.collect(li); }
@@ -166,9 +329,8 @@ template <class Op, class A> struct Unary : expr_tag {
   }
   template <int OFF, int N, bool NT, class R>
   __device__ __forceinline__ lanes<ct, N> at_regs(const R* regs, int64_t i) const {
-    lanes<ct, N> x = a.template at_regs<OFF, N, NT>(regs, i);
-#pragma unroll
-    for (int j = 0; j < N; ++j) x.v[j] = Op::apply(x.v[j]);
+    lanes<ct, N> x = arg::of(a).template at_regs<OFF, N, NT>(regs, i);
+    apply_lanes<Op, typename arg::mod>(x.v);
     return x;
   }
   void leaf_ids(leaf_id* out, int& k) const { a.leaf_ids(out, k); }

@@ -172,10 +172,10 @@ template <class C, int S> constexpr int kPassLanes = (64 * 4) / (S * (int)sizeof
     case U_RDIVI: FX_LANES(acc[j] = k / acc[j]) break;                                \
     case U_NEG: FX_LANES(acc[j] = -acc[j]) break;                                     \
     case U_ABS: FX_LANES(acc[j] = op_abs::apply(acc[j])) break;                       \
-    case U_EXP: FX_LANES(acc[j] = op_exp::apply(acc[j])) break;                       \
-    case U_SQRT: FX_LANES(acc[j] = op_sqrt::apply(acc[j])) break;                     \
-    case U_EXP_NABS: FX_LANES(acc[j] = op_exp::apply(-op_abs::apply(acc[j]))) break;  \
-    case U_SQRT_ABS: FX_LANES(acc[j] = op_sqrt::apply(op_abs::apply(acc[j]))) break;  \
+    case U_EXP: exp_lanes<mod_none, true>(acc); break;                                      \
+    case U_SQRT: sqrt_lanes<mod_none, true>(acc); break;                                    \
+    case U_EXP_NABS: exp_lanes<mod_nabs, true>(acc); break;                                 \
+    case U_SQRT_ABS: sqrt_lanes<mod_abs, true>(acc); break;                                 \
     default: break;                                                                   \
   }
 

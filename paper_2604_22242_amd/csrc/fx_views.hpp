@@ -304,8 +304,7 @@ __device__ __forceinline__ lanes<ct_t<T>, N> src2(const Trans<T>& e, int64_t r, 
 template <int N, class Op, class A>
 __device__ __forceinline__ lanes<typename A::ct, N> src2(const Unary<Op, A>& e, int64_t r, int64_t c) {
   lanes<typename A::ct, N> v = src2<N>(e.a, r, c);
-#pragma unroll
-  for (int j = 0; j < N; ++j) v.v[j] = Op::apply(v.v[j]);
+  apply_lanes<Op, mod_none>(v.v);
   return v;
 }
 template <int N, class Op, class A, bool L>
@@ -357,8 +356,7 @@ __device__ __forceinline__ lanes<typename A::ct, N> at2(const Unary<Op, A>& e, i
     return staged<TOFF, N>(r, c, x);
   } else {
     lanes<typename A::ct, N> v = at2<TOFF, N>(e.a, r, c, x);
-#pragma unroll
-    for (int j = 0; j < N; ++j) v.v[j] = Op::apply(v.v[j]);
+    apply_lanes<Op, mod_none>(v.v);
     return v;
   }
 }
@@ -577,8 +575,7 @@ __device__ __forceinline__ lanes<C, N> at2p(const Trans<T>&, const pair_ctx<C, N
 template <int LOFF, class Op, class A, class C, int N, int S>
 __device__ __forceinline__ lanes<C, N> at2p(const Unary<Op, A>& e, const pair_ctx<C, N, S>& x) {
   lanes<C, N> v = at2p<LOFF>(e.a, x);
-#pragma unroll
-  for (int j = 0; j < N; ++j) v.v[j] = Op::apply(v.v[j]);
+  apply_lanes<Op, mod_none>(v.v);
   return v;
 }
 template <int LOFF, class Op, class A, bool L, class C, int N, int S>
