@@ -37,7 +37,9 @@ struct leaf_info {
   int64_t n_rows = -1, n_cols = -1;
   bool shape_ok = true;
   bool any_null = false;
+  int arrays = 0;  // leaves that read one, repeats included
   void add(const void* p, int64_t r, int64_t c) {
+    ++arrays;
     if (!p && r * c > 0) any_null = true;
     if (n_rows < 0) { n_rows = r; n_cols = c; }
     else if (r != n_rows || c != n_cols) shape_ok = false;

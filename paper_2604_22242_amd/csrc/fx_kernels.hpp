@@ -27,7 +27,8 @@
 // Cache policy of streamed loads and stores (measured on MI355X: streaming
 // loads raise the read ceiling from 6.4 to 7.1 TB/s).  FX_NT_STORES forces
 // streaming stores everywhere; by default the element-wise kernel chooses
-// per launch from the size of its output (kStreamStoresAbove).
+// per launch: stores from the size of its output (kStreamStoresAbove), loads
+// from all it touches (kCachedLoadsUpTo).
 #ifndef FX_NT_LOADS
 #define FX_NT_LOADS 1
 #endif
@@ -48,6 +49,18 @@ constexpr bool kNTS = FX_NT_STORES != 0;  // streaming policy for stores
 // that cache) against 6.1-6.2 streaming; from 320 MiB on, ordinary stores
 // fall to 6.0-6.1 TB/s and streaming stores keep 6.2-6.3.
 constexpr uint64_t kStreamStoresAbove = uint64_t(256) << 20;
+// Inputs and output that fit that cache together are read with ordinary loads,
+// which leave the inputs there for the next call on them.  The matrix workload's
+// Z, three inputs and an output, streaming against ordinary loads, us repeated
+// (after the caches were flushed):
+//   of 8 MiB each    FP32  5.2 (10.0)    4.5 (10.6)    BF16  8.1 (10.6)   6.0 (11.4)
+//   of 32 MiB        FP32 23.7 (26.3)   20.0 (25.6)    BF16 25.3 (27.5)  21.3 (26.7)
+//   of 64 MiB        FP32 42.8 (45.5)   37.3 (45.7)    BF16 44.9 (47.0)  38.8 (46.7)
+//   of 96 MiB        FP32 62.1 (64.2)   71.2 (68.0)    BF16 65.1 (67.2)  68.8 (67.3)
+// Reductions keep streaming loads at every size: FP32 column sums of 32 MiB
+// inputs 17.5 (20.4) against 17.9 (21.9), of 64 MiB 31.0 (33.6), 30.2 (36.9).
+// Tapes keep them too: they are bound by their interpreter.
+constexpr uint64_t kCachedLoadsUpTo = uint64_t(256) << 20;
 
 // Maps applied to each element before summation.
 struct map_id {
@@ -83,7 +96,7 @@ __device__ __forceinline__ void add_lanes(lane_accum<C, N>& acc, const lanes<C, 
 // until the previous one has arrived when little arithmetic follows).
 // Expression types with their own evaluation strategy (the run-time tape)
 // overload this.
-template <int N, int EPT, class E>
+template <int N, int EPT, bool NTL = kNT, class E>
 __device__ __forceinline__ void eval_tile(const E& e, int64_t base, int64_t stride,
                                           lanes<typename E::ct, N> (&r)[EPT]) {
   constexpr int L = leaves_of<E>::value;
@@ -91,27 +104,27 @@ __device__ __forceinline__ void eval_tile(const E& e, int64_t base, int64_t stri
     lanes<typename E::ct, N> regs[EPT][L];
     const uint8_t* no_alias = nullptr;
 #pragma unroll
-    for (int k = 0; k < EPT; ++k) e.template gather<0, N, kNT>(regs[k], no_alias, base + k * stride);
+    for (int k = 0; k < EPT; ++k) e.template gather<0, N, NTL>(regs[k], no_alias, base + k * stride);
     __builtin_amdgcn_sched_barrier(0);  // keep every load ahead of the arithmetic
 #pragma unroll
-    for (int k = 0; k < EPT; ++k) r[k] = e.template at_regs<0, N, kNT>(regs[k], base + k * stride);
+    for (int k = 0; k < EPT; ++k) r[k] = e.template at_regs<0, N, NTL>(regs[k], base + k * stride);
   } else {
 #pragma unroll
-    for (int k = 0; k < EPT; ++k) r[k] = e.template at_vec<N, kNT>(base + k * stride);
+    for (int k = 0; k < EPT; ++k) r[k] = e.template at_vec<N, NTL>(base + k * stride);
   }
 }
 
 // Fused<E>: the loads of all EPT vectors first, then the arithmetic.
-template <int N, int EPT, class E>
+template <int N, int EPT, bool NTL = kNT, class E>
 __device__ __forceinline__ void eval_tile(const Fused<E>& f, int64_t base, int64_t stride,
                                           lanes<typename E::ct, N> (&r)[EPT]) {
   lanes<typename E::ct, N> regs[EPT][Fused<E>::L];
 #pragma unroll
-  for (int k = 0; k < EPT; ++k) f.e.template gather<0, N, kNT>(regs[k], f.alias, base + k * stride);
+  for (int k = 0; k < EPT; ++k) f.e.template gather<0, N, NTL>(regs[k], f.alias, base + k * stride);
 #pragma unroll
   for (int k = 0; k < EPT; ++k) {
     f.template resolve<N>(regs[k]);
-    r[k] = f.e.template at_regs<0, N, kNT>(regs[k], base + k * stride);
+    r[k] = f.e.template at_regs<0, N, NTL>(regs[k], base + k * stride);
   }
 }
 
@@ -133,10 +146,10 @@ __device__ __forceinline__ uint32_t xcd_order(uint32_t b, uint32_t G) {
 // ============================================================================
 // Element-wise: Z[i] = E(i), i < n.
 
-// NTS: streaming stores.  The policy is a template parameter: a run-time
-// choice between two otherwise identical stores is merged by the compiler
-// into one store, which drops the streaming hint.
-template <class E, class T, int N, int EPT, bool NTS>
+// NTS: streaming stores, NTL: streaming loads.  The policies are template
+// parameters: a run-time choice between two otherwise identical stores is merged
+// by the compiler into one store, which drops the streaming hint.
+template <class E, class T, int N, int EPT, bool NTS, bool NTL = kNT>
 __global__ __launch_bounds__(kMaxBlock) void k_ew(E e, T* __restrict__ z, int64_t n) {
   using C = typename E::ct;
   const int64_t nv = n / N;  // whole vectors
@@ -147,14 +160,14 @@ __global__ __launch_bounds__(kMaxBlock) void k_ew(E e, T* __restrict__ z, int64_
     const int64_t v0 = t * tile + threadIdx.x;
     if ((t + 1) * tile <= nv) {
       lanes<C, N> r[EPT];
-      eval_tile<N, EPT>(e, v0 * N, (int64_t)blockDim.x * N, r);
+      eval_tile<N, EPT, NTL>(e, v0 * N, (int64_t)blockDim.x * N, r);
 #pragma unroll
       for (int k = 0; k < EPT; ++k) store_lanes<N, NTS>(z, (v0 + k * blockDim.x) * N, r[k]);
     } else {
 #pragma unroll
       for (int k = 0; k < EPT; ++k) {
         const int64_t v = v0 + k * blockDim.x;
-        if (v < nv) store_lanes<N, NTS>(z, v * N, e.template at_vec<N, kNT>(v * N));
+        if (v < nv) store_lanes<N, NTS>(z, v * N, e.template at_vec<N, NTL>(v * N));
       }
     }
   }
@@ -453,6 +466,11 @@ template <class E> struct vec8_compiled { static constexpr bool value = false; }
 template <class E> struct vec8_compiled<Fused<E>> { static constexpr bool value = vec8_compiled<E>::value; };
 template <class E> constexpr bool vec8_compiled_v = vec8_compiled<E>::value;
 
+// Expression types whose element-wise kernel is compiled with ordinary loads as
+// well (kCachedLoadsUpTo).
+template <class E> struct cached_loads { static constexpr bool value = true; };
+template <class E> constexpr bool cached_loads_v = cached_loads<E>::value;
+
 // Vector width in elements: one element, 8 bytes (where compiled) or 16 bytes.
 template <class T, class E = void, class F> inline int with_vec(int vec_elems, F&& f) {
   constexpr int W = 16 / (int)sizeof(T);
@@ -491,6 +509,14 @@ template <class E> int check_expr(const E& e, int64_t* n_rows, int64_t* n_cols) 
   return FX_OK;
 }
 
+// Arrays that e reads.
+template <class E> int arrays_of(const E& e) { return info_of(e).arrays; }
+template <class E> int arrays_of(const Fused<E>& f) {
+  int repeats = 0;
+  for (int k = 0; k < Fused<E>::L; ++k) repeats += f.alias[k] != k;
+  return info_of(f).arrays - repeats;
+}
+
 // A defaulted EPT never exceeds what is compiled for the expression type.
 template <class E> inline void clamp_ept(launch& L, const fx_launch* cfg) {
   if (!(cfg && cfg->ept)) L.ept = std::min(L.ept, max_ept<E>::value);
@@ -521,9 +547,15 @@ int eval_direct(T* z, const E& e, const fx_launch* cfg, hipStream_t st) {
   return with_vec<T, E>(vec, [&](auto Nc) {
     return with_ept<max_ept<E>::value>(L.ept, [&](auto Ec) {
       constexpr int N = decltype(Nc)::value, EPT = decltype(Ec)::value;
-      // (streaming stores are compiled for 16-byte vectors, the default for
-      // outputs of that size)
+      // (the policies are compiled for 16-byte vectors, the default where
+      // they matter)
       if constexpr (N * sizeof(T) == 16) {
+        if constexpr (kNT && cached_loads_v<E>) {
+          if ((uint64_t)n * sizeof(T) * (arrays_of(e) + 1) <= kCachedLoadsUpTo) {
+            hipLaunchKernelGGL((k_ew<E, T, N, EPT, kNTS, false>), dim3(L.split), dim3(L.block), 0, st, e, z, n);
+            return hip_check(hipGetLastError(), "k_ew launch");
+          }
+        }
         if (kNTS || (uint64_t)n * sizeof(T) > kStreamStoresAbove) {
           hipLaunchKernelGGL((k_ew<E, T, N, EPT, true>), dim3(L.split), dim3(L.block), 0, st, e, z, n);
           return hip_check(hipGetLastError(), "k_ew launch");

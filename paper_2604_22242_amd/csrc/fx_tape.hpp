@@ -292,7 +292,7 @@ template <class T, bool BYREF = false, int SLOTS = kTapeSmallSlots> struct TapeE
   }
 };
 
-template <int N, int EPT, class T, bool BYREF, int SLOTS>
+template <int N, int EPT, bool NTL = kNT, class T, bool BYREF, int SLOTS>
 __device__ __forceinline__ void eval_tile(const TapeExpr<T, BYREF, SLOTS>& e, int64_t base, int64_t stride,
                                           lanes<ct_t<T>, N> (&r)[EPT]) {
   using C = ct_t<T>;
@@ -302,7 +302,7 @@ __device__ __forceinline__ void eval_tile(const TapeExpr<T, BYREF, SLOTS>& e, in
   for (int q = 0; q < kTapeMaxIn; ++q)
 #pragma unroll
     for (int k = 0; k < EPT; ++k)
-      in[k][q] = q < n_in ? load_lanes<N, kNT>(e.p[q], base + k * stride) : unset_lanes<C, N>();
+      in[k][q] = q < n_in ? load_lanes<N, NTL>(e.p[q], base + k * stride) : unset_lanes<C, N>();
   // the EPT vectors are interpreted together, in passes of kPassLanes lanes
   lanes<C, N * EPT> flat[kTapeMaxIn];
 #pragma unroll
@@ -319,6 +319,7 @@ __device__ __forceinline__ void eval_tile(const TapeExpr<T, BYREF, SLOTS>& e, in
 }
 
 template <class T, bool B, int S> struct max_ept<TapeExpr<T, B, S>> { static constexpr int value = 4; };
+template <class T, bool B, int S> struct cached_loads<TapeExpr<T, B, S>> { static constexpr bool value = false; };
 template <class T, bool B, int S> struct vec8_compiled<TapeExpr<T, B, S>> {
   static constexpr bool value = true;
 };
