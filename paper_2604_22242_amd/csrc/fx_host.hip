@@ -90,6 +90,11 @@ static constexpr int kRowsumBlocksPerCU = 2;
 static constexpr int kRowsumMinCols = 2;
 static constexpr int kRowsumMaxSplit = 128;
 static constexpr int kRowsumChunksHeld = 64;
+// Whether a reduction needs a workspace, and of what size, is part of the
+// interface and does not follow the launch heuristics down: calls that leave the
+// split to the library ask for the partials of the two-blocks-per-CU launches
+// (launch::held), though fewer are written.
+static constexpr int64_t kHeldTwoFrom = (int64_t)1 << 24;
 
 launch resolve(int kind, int elem, int64_t n_rows, int64_t n_cols, const fx_launch* cfg,
                bool vectors) {
@@ -116,6 +121,10 @@ launch resolve(int kind, int elem, int64_t n_rows, int64_t n_cols, const fx_laun
       if (n * elem <= kReduceOneBlockBytes) want = 1;
     }
     L.split = c.split ? c.split : (int)std::min<int64_t>(want, 1 << 30);
+    if (full && !c.split) {
+      const int64_t t2 = std::max<int64_t>(1, ceil_div(n, (int64_t)L.block * (c.ept ? c.ept : 2) * vec16));
+      L.held = (int)std::min<int64_t>({t2, n < kHeldTwoFrom ? cus : 2 * cus, std::max<int64_t>(32, t2 / 4)});
+    }
   } else if (kind == FX_R_COLSUM) {
     L.block = c.block ? c.block : default_block(kind, elem);
     L.ept = c.ept ? c.ept : default_ept(kind, elem);
@@ -141,6 +150,11 @@ launch resolve(int kind, int elem, int64_t n_rows, int64_t n_cols, const fx_laun
     }
     s = std::min<int64_t>(s, std::max<int64_t>(1, n_cols));
     L.split = (int)std::max<int64_t>(1, std::min<int64_t>(s, 65535));
+    if (!c.block && !c.ept && !c.vec_bytes && !c.split) {
+      const int block = elem == 2 ? 64 : 256;
+      const int64_t blocks = std::max<int64_t>(1, ceil_div(n_rows, (int64_t)block * vec16));
+      L.held = (int)std::max<int64_t>(1, std::min<int64_t>({ceil_div(cus * 512 / block, blocks), n_cols / 32, 65535}));
+    }
   }
   return L;
 }
@@ -167,7 +181,18 @@ fx_launch tape_launch(int kind, int elem, int64_t n_rows, int64_t n_cols, const 
   const int cus = device_cus();
   fx_launch d;
   switch (kind) {
-    case FX_R_ACCU: case FX_R_NORM: d = fx_launch{512, half ? 1 : 2, 16, 2 * cus}; break;
+    case FX_R_ACCU: case FX_R_NORM: {
+      // No block without a tile: a block with nothing to add still takes a
+      // ticket, and 512 of them take 10 us (2^12 elements FP32 10.2 us with 512
+      // blocks, 4.2 with one; 2^18 10.3, 7.3 with 64).  Up to 2^17 elements tiles
+      // of 128 threads spread better (2^16 FP32 6.2 us against 6.8, 2^14 6.2
+      // against 6.5), unless 512 threads take all in one (2^12: 4.2 against 5.4).
+      const int64_t n = n_rows * n_cols, wave = 64 * (half ? 1 : 2) * (16 / elem);
+      const int block = all_default && n > 8 * wave && n < ((int64_t)1 << 17) ? 128 : 512;
+      const int64_t tiles = ceil_div(n, block / 64 * wave);
+      d = fx_launch{block, half ? 1 : 2, 16, (int)std::max<int64_t>(1, std::min<int64_t>(tiles, 2 * cus))};
+      break;
+    }
     case FX_R_COLSUM: d = fx_launch{256, half ? 1 : 2, 16, n_cols >= cus ? 1 : 0}; break;
     case FX_R_ROWSUM: d = fx_launch{512, half ? 1 : 2, 16, 0}; break;
     default:
@@ -190,10 +215,11 @@ static size_t round256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 ws_layout workspace_for(int kind, int64_t n_rows, int64_t n_cols, const launch& L, int) {
   ws_layout W;
+  const int parts = std::max(L.split, L.held);
   if (kind == FX_R_ACCU || kind == FX_R_NORM || kind == FX_R_DOT) {
-    if (L.split > 1) {
+    if (parts > 1) {
       W.counter_bytes = 256;
-      W.partial_bytes = (size_t)L.split * 8;
+      W.partial_bytes = (size_t)parts * 8;
     }
   } else if (kind == FX_R_COLSUM) {
     if (L.split > 1) {
@@ -204,10 +230,21 @@ ws_layout workspace_for(int kind, int64_t n_rows, int64_t n_cols, const launch& 
     if (L.split > 1) {
       // one counter per row tile: 64 rows or more, or the whole matrix
       W.counter_bytes = round256((size_t)ceil_div(n_rows, 64) * 4);
-      W.partial_bytes = (size_t)n_rows * L.split * 8;
+      W.partial_bytes = (size_t)n_rows * parts * 8;
     }
   }
   return W;
+}
+
+// The workspace of a tape reduction whose launch is left to the library: the
+// partials of two blocks per CU, or of kRowsumChunksHeld column chunks, so that a
+// launch model's or a caller's own split of that many fits it.
+size_t tape_workspace(int kind, int64_t n_rows, int64_t n_cols) {
+  launch L{};
+  if (kind == FX_R_ACCU || kind == FX_R_NORM) L.split = 2 * device_cus();
+  else if (kind == FX_R_ROWSUM) L.split = (int)std::min<int64_t>(kRowsumChunksHeld, std::max<int64_t>(1, n_cols));
+  else return 0;
+  return workspace_for(kind, n_rows, n_cols, L, 1).total();
 }
 
 }  // namespace fx
@@ -245,13 +282,8 @@ size_t fx_workspace_bytes(int kind, fx_dtype dt, fx_shape shape, const fx_launch
     const fx_launch t = tape_launch(kind, elem, shape.n_rows, shape.n_cols, cfg);
     launch T = resolve(kind, elem, shape.n_rows, shape.n_cols, &t, true);
     b = std::max(b, workspace_for(kind, shape.n_rows, shape.n_cols, T, 16 / elem).total());
-    // row sums: a workspace sized by the defaults holds kRowsumChunksHeld
-    // column chunks, so that a launch model's or a caller's own split of that
-    // many fits it
-    if (kind == FX_R_ROWSUM && (!cfg || (!cfg->block && !cfg->ept && !cfg->vec_bytes && !cfg->split))) {
-      T.split = (int)std::min<int64_t>(kRowsumChunksHeld, std::max<int64_t>(1, shape.n_cols));
-      b = std::max(b, workspace_for(kind, shape.n_rows, shape.n_cols, T, 16 / elem).total());
-    }
+    if (!cfg || (!cfg->block && !cfg->ept && !cfg->vec_bytes && !cfg->split))
+      b = std::max(b, tape_workspace(kind, shape.n_rows, shape.n_cols));
   }
   return b;
 }

@@ -599,7 +599,7 @@ int reduce_full_direct(const E& e, void* out, void* ws, size_t ws_bytes, const f
   clamp_ept<E>(L, cfg);
   const int vec = L.vec_bytes / (int)sizeof(T);
   ws_layout W = workspace_for(FX_R_ACCU, rows, cols, L, vec);
-  if (L.split > 1 && (!ws || ws_bytes < W.total()))
+  if (W.total() > 0 && (!ws || ws_bytes < W.total()))
     return fail(FX_E_WORKSPACE, "workspace of %zu bytes needed, %zu given", W.total(), ws_bytes);
   return with_vec<T, E>(vec, [&](auto Nc) {
     return with_ept<max_ept<E>::value>(L.ept, [&](auto Ec) {

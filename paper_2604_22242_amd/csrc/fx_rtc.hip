@@ -282,6 +282,7 @@ int fx_rtc_eval(fx_rtc* r, const void* const* inputs, int32_t n_inputs, fx_shape
   if (full)
     L.split = generated_full_split(L.split, device_cus(),
                                    ceil_div(n, (int64_t)r->block * r->ept * N));
+  L.held = resolve(rkind, r->elem, rows, cols, nullptr, true).held;
   const int vec = kind == 0 || full || rows >= N ? N : 1;
   const ws_layout W = workspace_for(rkind, rows, cols, L, vec);
   if (W.total() > 0 && (!ws || ws_bytes < W.total()))

@@ -312,7 +312,8 @@ int eval_source(const E& e, void* out, void* ws, size_t ws_bytes, hipStream_t st
     return hip_check(hipGetLastError(), "k_fill_zero launch");
   }
   const fx_launch text{default_block(rk, elem), default_ept(rk, elem), 0, 0};  // fixed in the source
-  const launch L = resolve(rk, elem, rows, cols, &text, true);
+  launch L = resolve(rk, elem, rows, cols, &text, true);
+  L.held = resolve(rk, elem, rows, cols, nullptr, true).held;
   constexpr int N = 16 / elem;
   const int vec = KIND == 0 || full || rows >= N ? N : 1;
   const ws_layout W = workspace_for(rk, rows, cols, L, vec);
