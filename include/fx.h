@@ -371,7 +371,8 @@ int32_t fx_tape_program(const fx_tape* t, uint16_t* op, uint8_t* slot, uint8_t* 
  * threads, EPT 2 for 4- and 8-byte types from 2^20 elements on);
  * accu / norm 512 threads (128 between one tile of those and 2^17 elements),
  * EPT 2 (1 for half types), a block per tile up to 2 per CU;
- * column sums 256 threads, EPT 2 (1 for half types), one block per column
+ * column sums up to 256 threads (512 with at most two columns per CU; no more
+ * than the column has work for), EPT 2 (1 for half types), one block per column
  * when there are at least as many columns as CUs; row sums 512 threads,
  * EPT 2 (1 for half types).  The split default applies
  * only when all of cfg is 0 (or cfg is NULL); then a model attached with

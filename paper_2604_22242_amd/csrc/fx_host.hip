@@ -72,9 +72,10 @@ int check_launch(const fx_launch* c) {
 //     gets 8 vectors but at least kReduceMinBlocks blocks run (2^20 BF16: 64
 //     blocks 6.4 us, 32 blocks 7.5), and an input of at most 32 KB is one
 //     block, which needs no cross-block finish (2^12 FP32 2.7 against 3.9 us);
-//   column sums: one block per column (512 threads, EPT 2 for 4- and
-//     8-byte types; 256 threads, EPT 1 for half types), a column split into
-//     chunks when there are fewer columns than blocks to fill the chip;
+//   column sums: one block per column, 512 threads, EPT 2 for 4- and 8-byte
+//     types, 256, EPT 1 for half types, fewer where the column has no work for
+//     them (colsum_launch), a column split into chunks only where there are
+//     fewer columns than CUs;
 //   row sums: two blocks per CU, 256 threads, EPT 2 for 4- and 8-byte types,
 //     512 threads, EPT 1 for half types (whose arithmetic wants the waves):
 //     matrix workload FP32 118 us against 126 with four blocks per CU, FP64
@@ -85,7 +86,6 @@ static constexpr int kReduceMinBlocks = 64;
 static constexpr int kReduceMinVecs = 8;  // per thread
 static constexpr int64_t kReduceDeepFrom = (int64_t)1 << 21;
 static constexpr int64_t kReduceOneBlockBytes = 32 << 10;
-static constexpr int kColsumBlocksPerCU = 8;
 static constexpr int kRowsumBlocksPerCU = 2;
 static constexpr int kRowsumMinCols = 2;
 static constexpr int kRowsumMaxSplit = 128;
@@ -95,6 +95,27 @@ static constexpr int kRowsumChunksHeld = 64;
 // split to the library ask for the partials of the two-blocks-per-CU launches
 // (launch::held), though fewer are written.
 static constexpr int64_t kHeldTwoFrom = (int64_t)1 << 24;
+
+// Column sums: threads for a column of n_rows, at most `block` of them with `ept`
+// vectors each.  A thread without a vector costs its share of the block's start and
+// end (128 x 32768 FP32 102 us with 512 threads, 15.5 with 64; 1024 x 4096 17 and 10),
+// so no more threads than take ept vectors each; with few columns, whose blocks
+// do not fill the chip, than take one.  A column of half storage takes twice its 256
+// threads where there are one or two whole columns per CU (8192 x 512 BF16 11.4,
+// 8.8; chunked columns run as fast with 256: 65536 x 64 13.6 and 13.9).
+static fx_launch colsum_launch(int elem, int64_t n_rows, int64_t n_cols, int block, int ept) {
+  const int vec = 16 / elem;
+  const int64_t cus = device_cus();
+  if (elem == 2 && n_cols >= cus && n_cols <= 2 * cus) block = 512;
+  const int64_t each = (int64_t)vec * (n_cols < 4 * cus ? 1 : ept);
+  int b = 64;
+  while (b < block && b * each < n_rows) b *= 2;
+  return fx_launch{b, (int64_t)b * vec >= n_rows ? 1 : ept, 16, 0};
+}
+// One thread per column up to 64 bytes of it (C2 column sums, thin against one
+// wave per column: FP32 16 rows 84 and 95 us, 24 rows 97 and 65; FP64 8 rows 48 and
+// 270, 16 rows 151 and 138; BF16 32 rows 38 and 76, 40 rows the wave's 65).
+static constexpr int64_t kThinColumnBytes = 64;
 
 launch resolve(int kind, int elem, int64_t n_rows, int64_t n_cols, const fx_launch* cfg,
                bool vectors) {
@@ -126,16 +147,31 @@ launch resolve(int kind, int elem, int64_t n_rows, int64_t n_cols, const fx_laun
       L.held = (int)std::min<int64_t>({t2, n < kHeldTwoFrom ? cus : 2 * cus, std::max<int64_t>(32, t2 / 4)});
     }
   } else if (kind == FX_R_COLSUM) {
-    L.block = c.block ? c.block : default_block(kind, elem);
-    L.ept = c.ept ? c.ept : default_ept(kind, elem);
-    if (!c.split && n_rows <= 32) {
+    const fx_launch d = colsum_launch(elem, n_rows, n_cols, default_block(kind, elem), default_ept(kind, elem));
+    L.block = c.block ? c.block : c.ept ? default_block(kind, elem) : d.block;
+    L.ept = c.ept ? c.ept : c.block ? default_ept(kind, elem) : d.ept;
+    if (!c.split && n_rows * elem <= kThinColumnBytes) {
       L.split = 0;  // thin columns: one thread per column
     } else {
-      const int64_t target = cus * kColsumBlocksPerCU;
-      int64_t s = c.split ? c.split : ceil_div(target, std::max<int64_t>(1, n_cols));
-      // every chunk holds at least one full pass of the block
-      s = std::min<int64_t>(s, std::max<int64_t>(1, ceil_div(n_rows, (int64_t)L.block * vec16)));
+      const int64_t ncol = std::max<int64_t>(1, n_cols);
+      int64_t s = c.split;
+      if (s) {
+        s = std::min<int64_t>(s, std::max<int64_t>(1, ceil_div(n_rows, (int64_t)L.block * vec16)));
+      } else {
+        // Chunks only where there are fewer columns than CUs (each column
+        // combined across blocks costs its last block some microseconds: 4096 x
+        // 1024 FP32 11 us whole, 16 in two chunks), each at least a pass of the
+        // block; about a block per CU, two from 64 columns on (32768 x 128 FP32
+        // 13.3 us with 8 chunks, 18.1 with 16; 2^22 x 1 21 us with 256, 71 with
+        // 2048).
+        const int64_t target = ncol * 4 >= cus ? 2 * cus : cus;
+        s = ncol >= cus ? 1 : ceil_div(target, ncol);
+        s = std::min<int64_t>(s, n_rows / ((int64_t)L.block * vec16 * L.ept));
+      }
       L.split = (int)std::max<int64_t>(1, std::min<int64_t>(s, 65535));
+      if (!c.split && n_rows > 32)
+        L.held = (int)std::min<int64_t>({ceil_div(8 * cus, ncol), 65535, std::max<int64_t>(1, ceil_div(
+            n_rows, (int64_t)(c.block ? c.block : default_block(kind, elem)) * vec16))});
     }
   } else {  // FX_R_ROWSUM
     L.block = c.block ? c.block : default_block(kind, elem);
@@ -193,7 +229,13 @@ fx_launch tape_launch(int kind, int elem, int64_t n_rows, int64_t n_cols, const 
       d = fx_launch{block, half ? 1 : 2, 16, (int)std::max<int64_t>(1, std::min<int64_t>(tiles, 2 * cus))};
       break;
     }
-    case FX_R_COLSUM: d = fx_launch{256, half ? 1 : 2, 16, n_cols >= cus ? 1 : 0}; break;
+    case FX_R_COLSUM:
+      // 512 threads with at most two columns per CU, as above 256 (8192 x 512 FP32
+      // 15.8 us with 256, 12.3); fewer for short columns (128 x 32768 FP32 109 us, 24)
+      d = fx_launch{256, half ? 1 : 2, 16, 0};
+      if (all_default) d = colsum_launch(elem, n_rows, n_cols, n_cols <= 2 * cus ? 512 : 256, half ? 1 : 2);
+      d.split = n_cols >= cus ? 1 : 0;
+      break;
     case FX_R_ROWSUM: d = fx_launch{512, half ? 1 : 2, 16, 0}; break;
     default:
       // two vectors per thread fill an interpreter pass for 4- and 8-byte
@@ -222,12 +264,12 @@ ws_layout workspace_for(int kind, int64_t n_rows, int64_t n_cols, const launch& 
       W.partial_bytes = (size_t)parts * 8;
     }
   } else if (kind == FX_R_COLSUM) {
-    if (L.split > 1) {
+    if (parts > 1) {
       W.counter_bytes = round256((size_t)n_cols * 4);
-      W.partial_bytes = (size_t)n_cols * L.split * 8;
+      W.partial_bytes = (size_t)n_cols * parts * 8;
     }
   } else if (kind == FX_R_ROWSUM) {
-    if (L.split > 1) {
+    if (parts > 1) {
       // one counter per row tile: 64 rows or more, or the whole matrix
       W.counter_bytes = round256((size_t)ceil_div(n_rows, 64) * 4);
       W.partial_bytes = (size_t)n_rows * parts * 8;
