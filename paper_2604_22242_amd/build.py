@@ -82,6 +82,19 @@ def build(jobs: int | None = None, extra: list[str] | None = None, verbose: bool
     return out
 
 
+def build_user(src: str, out: str) -> str:
+    """Compile a user's program (one source on top of the front end's headers)
+    into the shared library `out`, linked against libfx.so."""
+    tmp = out + ".tmp%d" % os.getpid()
+    rel = os.path.relpath(HERE, os.path.dirname(out))
+    cmd = [HIPCC] + CFLAGS + ["-shared", src, "-L" + HERE, "-l:" + os.path.basename(LIB), "-Wl,-rpath,$ORIGIN/" + rel, "-o", tmp]
+    p = subprocess.run(cmd, capture_output=True, text=True)
+    if p.returncode != 0:
+        raise RuntimeError("hipcc failed on %s:\n%s" % (src, p.stderr))
+    os.replace(tmp, out)
+    return out
+
+
 if __name__ == "__main__":
     ap = argparse.ArgumentParser()
     ap.add_argument("--jobs", type=int, default=None)

@@ -516,20 +516,23 @@ __global__ __launch_bounds__(kTileThreads) void k_ew2d(E e, T* __restrict__ z, i
 // of the thread that computes it; for the transposed leaves the partner tile
 // goes through LDS, one output tile after the other in the same buffers (all
 // four tiles in LDS at once, as before, left two blocks per CU).  Each matrix
-// is read from HBM once.  Whole matrices only, at most kPairMats distinct ones;
+// is read from HBM once.  Whole matrices of the output's type only, at most
+// kPairMats distinct ones;
 // tiles of 64 x 64, 32 x 32 for 8-byte types.  2*(t(X) + Y) + 2*(X + t(Y)):
 // FP32 10000 x 10000 261 -> 247 us; FP64 3001 x 3001, until then on the general
 // kernel, 53 -> 38; BF16 10000 x 10000 286 -> 172.
 constexpr int kPairMats = 2;
 template <class T> constexpr int kPairSide = sizeof(T) == 8 ? 32 : 64;
 
-template <class E> struct pairable { static constexpr bool value = false; };
-template <class T> struct pairable<Leaf<T>> { static constexpr bool value = true; };
-template <class T> struct pairable<Trans<T>> { static constexpr bool value = true; };
-template <class Op, class A> struct pairable<Unary<Op, A>> : pairable<A> {};
-template <class Op, class A, bool L> struct pairable<Scalar<Op, A, L>> : pairable<A> {};
-template <class Op, class A, class B> struct pairable<Binary<Op, A, B>> {
-  static constexpr bool value = pairable<A>::value && pairable<B>::value;
+// Every leaf a whole matrix, direct or transposed, of the output's storage type T
+// (the kernel reads its matrices as that).
+template <class E, class T> struct pairable { static constexpr bool value = false; };
+template <class T> struct pairable<Leaf<T>, T> { static constexpr bool value = true; };
+template <class T> struct pairable<Trans<T>, T> { static constexpr bool value = true; };
+template <class Op, class A, class T> struct pairable<Unary<Op, A>, T> : pairable<A, T> {};
+template <class Op, class A, bool L, class T> struct pairable<Scalar<Op, A, L>, T> : pairable<A, T> {};
+template <class Op, class A, class B, class T> struct pairable<Binary<Op, A, B>, T> {
+  static constexpr bool value = pairable<A, T>::value && pairable<B, T>::value;
 };
 template <class E> struct pair_leaves { static constexpr int value = 0; };
 template <class T> struct pair_leaves<Leaf<T>> { static constexpr int value = 1; };
@@ -740,7 +743,7 @@ int eval_views(T* z, const E& e, hipStream_t st) {
     if (ntl) return nts ? go(std::true_type{}, std::true_type{}) : go(std::true_type{}, std::false_type{});
     return nts ? go(std::false_type{}, std::true_type{}) : go(std::false_type{}, std::false_type{});
   };
-  if constexpr (KT > 0 && pairable<E>::value) {
+  if constexpr (KT > 0 && pairable<E, T>::value) {
     pair_tab tab;
     if (rows == cols && pair_plan(e, rows, &tab)) {
       const int64_t t = ceil_div(rows, (int64_t)kPairSide<T>);
