@@ -253,6 +253,13 @@ template <int KT, int N, int Q, class T> struct tile_geo {
   static constexpr int CG = kTileThreads / RV;   // columns at a time
   static constexpr int P = TR + 1;               // LDS column pitch
 };
+// The wide tile (Q = 4) is compiled where two of its blocks, at least, share a
+// CU's 160 KB of LDS: for at most two staged parts of 4- or 8-byte types.  More
+// parts take the narrow one, whose LDS is half (five parts 83 KB, nine 149).
+template <int KT, int N, class T> constexpr bool wide_tile() {
+  using G = tile_geo<KT, N, 4, T>;
+  return KT == 0 || 2 * (N + KT * G::TC * G::P) * sizeof(ct_t<T>) <= 160 * 1024;
+}
 
 // The tile being computed (G: its geometry; NTL: streaming loads of the direct
 // leaves).
@@ -773,7 +780,10 @@ int eval_views(T* z, const E& e, hipStream_t st) {
   };
   if (!vec) return launch(ic<1>{}, ic<4>{}, std::false_type{}, std::false_type{});
   return with_policy([&](auto l, auto st_) {
-    return narrow ? launch(ic<NV>{}, ic<1>{}, l, st_) : launch(ic<NV>{}, ic<4>{}, l, st_);
+    if constexpr (wide_tile<KT, NV, T>()) {
+      if (!narrow) return launch(ic<NV>{}, ic<4>{}, l, st_);
+    }
+    return launch(ic<NV>{}, ic<1>{}, l, st_);
   });
 }
 

@@ -12,7 +12,18 @@ static int pair(void* z, const void* x, const void* y, int64_t n, void* st) {
   return eval_views(static_cast<TZ*>(z), 2 * (t(X) + Y) + (X + t(Y)), S(st));
 }
 
+// 2*X + A^T%X + B^T%X + C^T%X + D^T%X + E^T%X (m: X, A, B, C, D, E): five transposed parts.
+template <class T> static int five(void* z, const void* const* m, int64_t n, void* st) {
+  auto M = [&](int q) { return leaf<T>(m[q], n, n); };
+  const auto X = M(0);
+  return eval_views(static_cast<T*>(z), 2 * X + t(M(1)) % X + t(M(2)) % X + t(M(3)) % X + t(M(4)) % X +
+                                            t(M(5)) % X, S(st));
+}
+
 extern "C" {
+
+int user_five_f32(void* z, const void* const* m, int64_t n, void* st) { return five<float>(z, m, n, st); }
+int user_five_f64(void* z, const void* const* m, int64_t n, void* st) { return five<double>(z, m, n, st); }
 
 int user_pair_bf16_of_f32(void* z, const void* x, const void* y, int64_t n, void* st) {
   return pair<bf16_t, float>(z, x, y, n, st);

@@ -1,6 +1,6 @@
 """View expressions of a user's own program (tests/native/user_views.hip), which
 no entry point instantiates: matrices read both directly and transposed whose
-storage is not the output's, against numpy in FP64."""
+storage is not the output's, and five transposed parts, against numpy in FP64."""
 import ctypes
 import os
 
@@ -39,7 +39,7 @@ def _matrix(torch, seed, n, dt):
 def test_program_builds():
     L = _lib()
     assert all(hasattr(L, f) for f in ("user_pair_bf16_of_f32", "user_pair_f32_of_bf16",
-                                       "user_pair_f16_of_bf16"))
+                                       "user_pair_f16_of_bf16", "user_five_f32", "user_five_f64"))
 
 
 def test_pairs_only_of_the_outputs_storage(tmp_path):
@@ -77,3 +77,24 @@ def test_mixed_storage_pairs(out, store):
         u, step = torch.finfo(dt[out]).eps / 2, 2.0 ** -25 if out == "f16" else 0.0
         bound = 3.01 * 2.0 ** -24 * mag + 1.01 * u * abs(want) + step
         assert (abs(got - want) <= bound).all(), (n, abs(got - want).max())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("n", [3, 33, 130, 2048])
+def test_five_transposed_parts(dtype, n):
+    torch, _ = need_gpu()
+    dt = {"f32": torch.float32, "f64": torch.float64}[dtype]
+    dev, host = zip(*(_matrix(torch, 100 * n + q, n, dt) for q in range(6)))
+    z = torch.full((n * n,), float("nan"), dtype=dt, device="cuda")
+    ptrs = (ctypes.c_void_p * 6)(*[t.data_ptr() for t in dev])
+    st = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    assert getattr(_lib(), "user_five_" + dtype)(ctypes.c_void_p(z.data_ptr()), ptrs, ctypes.c_int64(n), st) == 0
+    torch.cuda.synchronize()
+    got = z.to(torch.float64).cpu().numpy().reshape(n, n).T
+    X = host[0]
+    want = 2 * X + sum(M.T * X for M in host[1:])
+    mag = 2 * abs(X) + sum(abs(M.T * X) for M in host[1:])
+    # five products and five additions, the reference's own in FP64
+    u = torch.finfo(dt).eps / 2 + (2.0 ** -53 if dtype == "f64" else 0)
+    assert (abs(got - want) <= 10.01 * u * mag).all(), (n, abs(got - want).max())
