@@ -12,9 +12,8 @@
 //
 // Evaluation.  A diagonal is a vector, so expressions over diagonals run
 // through the linear skeletons.  Expressions with Sub or Trans leaves run
-// through k_ew2d: one block per output tile (128 x 64, 64 x 64 for 8-byte
-// types, with transposed leaves; (64 * N) x 16 without), each thread a vector
-// of N consecutive rows in several columns.  Dense and submatrix leaves are
+// through k_ew2d: one block per output tile, each thread a vector of N
+// consecutive rows in several columns.  Dense and submatrix leaves are
 // read straight from HBM, 16-byte vectors at any element; a part of the
 // expression all of whose leaves are transposed, such as t(B + C), is first
 // evaluated over its source tile and staged in LDS by the whole block, read
@@ -242,10 +241,21 @@ constexpr int kTileThreads = 256;
 // 64 (Q = 4 and 2-byte types; 33 KB).  The wider tile is the faster one where
 // columns are whole cache lines and its blocks are many (4096 x 4096 FP64 128
 // us against 143); with few blocks they fill the chip unevenly (3001 x 3001
-// FP32 44 against 30), elsewhere the two are even.  The one-element variant,
-// for views narrower than a vector, keeps 16 x 64.  Without transposed parts
+// FP32 44 against 30), elsewhere the two are even.  Without transposed parts
 // the tile is (64 N) x (4 Q): 1 KB runs (square tiles, 256-byte runs: measured
 // slower), Q columns per thread.
+//
+// One element per thread row (N = 1; tiles of 16 x 64, 64 x 16 without
+// transposed parts) is for small results and for short columns.  Up to 4 MB of
+// a result with transposed parts the tiles of vectors are too few to cover their
+// own latency (FP32 512 x 512: 2*(t(X) + Y) + 2*(X + t(Y)) 3.1 us against 5.4 in
+// paired tiles, 1024 x 1024 4.3 and 5.8, 1500 x 1500 9.4 and 7.6; BF16 expr2 1001
+// x 1001 4.6 and 8.1, 2000 x 2000 11.4 and 10.7).  Without them, columns of up
+// to 32 rows leave most of a 64 N row tile idle (sum of two submatrices of 4 x
+// 131072 FP32: 7.9 us against 12.6, 16 x 32768: 3.7 and 4.8, 64 x 8192: 2.8 and
+// 2.9).
+constexpr uint64_t kElementBelow = uint64_t(4) << 20;
+constexpr int kElementRows = 32;
 template <int KT, int N, int Q, class T> struct tile_geo {
   static constexpr int TR = KT == 0 ? 64 * N : N == 1 ? 16 : sizeof(T) == 8 ? 64 : 128;
   static constexpr int TC = KT == 0 ? 4 * Q : N == 1 || Q == 4 || sizeof(T) == 2 ? 64 : 32;
@@ -739,9 +749,9 @@ int eval_views(T* z, const E& e, hipStream_t st) {
   if (rows * cols == 0) return FX_OK;
   if (!z) return fail(FX_E_ARG, "NULL output pointer");
   constexpr int NV = 16 / (int)sizeof(T);
-  const bool vec = rows >= NV && cols >= NV;
   constexpr int KT = trans_count<E>::value;
   const uint64_t bytes = (uint64_t)rows * (uint64_t)cols * sizeof(T);
+  const bool vec = KT > 0 ? rows >= NV && cols >= NV && bytes > kElementBelow : rows > kElementRows;
   const bool nts = kNTS || bytes > kStreamStoresAbove;
   const bool lines = whole_lines(e);
   const uint64_t total = bytes * (leaf_count<E>::value + 1);
@@ -752,7 +762,7 @@ int eval_views(T* z, const E& e, hipStream_t st) {
   };
   if constexpr (KT > 0 && pairable<E, T>::value) {
     pair_tab tab;
-    if (rows == cols && pair_plan(e, rows, &tab)) {
+    if (vec && rows == cols && pair_plan(e, rows, &tab)) {
       const int64_t t = ceil_div(rows, (int64_t)kPairSide<T>);
       if (t * (t + 1) / 2 > 0x7fffffff)
         return fail(FX_E_UNSUPPORTED, "%lld x %lld exceeds the tile grid", (long long)rows, (long long)cols);
@@ -763,11 +773,12 @@ int eval_views(T* z, const E& e, hipStream_t st) {
       });
     }
   }
-  // one column per thread, or the narrow tile, where the wide one would leave
-  // the chip with few blocks
+  // one column per thread where four would leave the chip with few blocks or
+  // threads without a column; the narrow tile of transposed parts as above
   const int64_t wide = ceil_div(cols, tile_geo<KT, NV, 4, T>::TC) * ceil_div(rows, tile_geo<KT, NV, 4, T>::TR);
-  const bool narrow = KT == 0 ? wide < (int64_t)8 * device_cus()
-                              : !(lines && wide >= (int64_t)16 * device_cus());
+  const bool narrow = KT > 0 ? !(lines && wide >= (int64_t)16 * device_cus())
+                             : cols < tile_geo<KT, NV, 4, T>::TC ||
+                                   wide < (int64_t)8 * device_cus();
   auto launch = [&](auto Nc, auto Qc, auto l, auto st_) {
     constexpr int N = decltype(Nc)::value, Q = decltype(Qc)::value;
     using G = tile_geo<KT, N, Q, T>;

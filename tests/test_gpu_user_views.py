@@ -63,7 +63,7 @@ def test_pairs_only_of_the_outputs_storage(tmp_path):
 def test_mixed_storage_pairs(out, store):
     torch, _ = need_gpu()
     dt = {"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}
-    for n in (7, 64, 131, 514):
+    for n in (7, 64, 131, 514, 1601):
         x, X = _matrix(torch, n, n, dt[store])
         y, Y = _matrix(torch, n + 1, n, dt[store])
         z = torch.full((n * n,), float("nan"), dtype=dt[out], device="cuda")
