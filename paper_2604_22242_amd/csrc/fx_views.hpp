@@ -239,11 +239,13 @@ constexpr int kTileThreads = 256;
 // 8-byte types), so that a column of a direct leaf is read in 512-byte runs
 // (256 of 2-byte types), by 32 columns (Q = 1; 17 KB of LDS per staged part) or
 // 64 (Q = 4 and 2-byte types; 33 KB).  The wider tile is the faster one where
-// columns are whole cache lines and its blocks are many (4096 x 4096 FP64 128
-// us against 143); with few blocks they fill the chip unevenly (3001 x 3001
-// FP32 44 against 30), elsewhere the two are even.  Without transposed parts
-// the tile is (64 N) x (4 Q): 1 KB runs (square tiles, 256-byte runs: measured
-// slower), Q columns per thread.
+// columns start at multiples of 16 KB and its blocks are many (4096 x 4096
+// FP64 a*A + t(B + C) + log(D^2): 126 us against 142; 8192 x 8192 FP32 245
+// and 247), the narrow one elsewhere (5856 x 5856 FP64 248 against 254, 10000 x
+// 10000 FP64 716 and 730; with few blocks the wide ones fill the chip unevenly,
+// 3001 x 3001 FP32 30 and 44).  Without transposed parts the tile is (64 N) x
+// (4 Q): 1 KB runs (square tiles, 256-byte runs: measured slower), Q columns per
+// thread.
 //
 // One element per thread row (N = 1; tiles of 16 x 64, 64 x 16 without
 // transposed parts) is for small results and for short columns.  Up to 4 MB of
@@ -279,33 +281,68 @@ template <class C, class G, bool NTL> struct tile_ctx {
   int64_t r0, c0;
 };
 
-// Streaming loads of the direct leaves pay where every column is a whole number
-// of cache lines and the data exceed what the last-level cache keeps for the
-// next call (8192 x 8192 FP32 a*A + t(B + C) + log(D^2): 222 us against 234).
-// Otherwise ordinary ones do: the lines that runs straddle are read again by
-// the tile beside (10000 x 10000 FP32: 378 against 410), and small data are found in
-// that cache (4096 x 4096 FP64 sum of two submatrices, 101 MB: 15 us against
-// 18).  Without transposed parts the runs are long and only size counts.
-constexpr uint64_t kCachedBelow = uint64_t(176) << 20;
-template <class T> inline bool whole_lines(const Leaf<T>& e) { return e.n_rows * sizeof(T) % 128 == 0; }
-template <class T> inline bool whole_lines(const Sub<T>& e) { return e.ld * sizeof(T) % 128 == 0; }
-template <class T> inline bool whole_lines(const Trans<T>& e) { return e.ld * sizeof(T) % 128 == 0; }
-template <class T> inline bool whole_lines(const Diag<T>&) { return true; }
-template <class Op, class A> inline bool whole_lines(const Unary<Op, A>& e) { return whole_lines(e.a); }
-template <class Op, class A, bool L> inline bool whole_lines(const Scalar<Op, A, L>& e) {
-  return whole_lines(e.a);
+// Cache policy of the direct leaves, by the bytes of all arrays and by where the
+// columns start (sums of two and four submatrices, "2" and "4"; the 10000 x
+// 10000 expressions expr1 and expr2; us with streaming against ordinary loads).
+//  * All that fits the 256 MiB last-level cache takes ordinary loads, which leave
+//    it there for the next call: FP32 4900 x 4900 "4" 23.9 against 18.5, 3000 x
+//    3000 expr1 26 and 21; FP64 6000 x 6000 "2" (216 MB) 36.6 and 31.4.
+//  * More takes streaming loads: FP32 10000 x 10000 "4" 92 and 100, 4096 x 4096
+//    expr2 (335 MB) 52 and 67.
+//  * With transposed parts and columns that are no whole number of cache lines,
+//    the lines that the runs straddle are read again by the tile beside; far
+//    beyond the cache those reads decide, and ordinary loads are the better ones
+//    again: FP32 10000 x 10000 expr1 267 and 250, FP64 5999 x 5999 expr2 300 and
+//    293 (864 MB), but FP64 5000 x 5000 expr1 (600 MB) 111 and 130.
+//  * Columns of submatrices that start at multiples of 16 KB share a few sets of
+//    the caches, and hold less in them: streaming from 176 MiB on (FP32 8192 x
+//    8192 "2", 201 MB: 33 and 37), and between the 32 MB of the eight L2 caches
+//    and 64 MiB (FP32 4096 x 4096 "2": 9.4 and 10.7, 16384 x 1000 8.0 and 8.6).
+constexpr uint64_t kMiB = uint64_t(1) << 20;
+constexpr uint64_t kStraddledBelow = 640 * kMiB, kSetsBelow = 176 * kMiB, kSetsFrom = 32 * kMiB,
+                   kSetsTo = 64 * kMiB;
+constexpr int kSetsPitch = 16384;
+
+// Is every column pitch of e a multiple of `bytes`?
+template <class T> inline bool pitch_of(const Leaf<T>& e, int bytes) { return e.n_rows * sizeof(T) % bytes == 0; }
+template <class T> inline bool pitch_of(const Sub<T>& e, int bytes) { return e.ld * sizeof(T) % bytes == 0; }
+template <class T> inline bool pitch_of(const Trans<T>& e, int bytes) { return e.ld * sizeof(T) % bytes == 0; }
+template <class T> inline bool pitch_of(const Diag<T>&, int) { return true; }
+template <class Op, class A> inline bool pitch_of(const Unary<Op, A>& e, int bytes) { return pitch_of(e.a, bytes); }
+template <class Op, class A, bool L> inline bool pitch_of(const Scalar<Op, A, L>& e, int bytes) {
+  return pitch_of(e.a, bytes);
 }
-template <class To, class A> inline bool whole_lines(const Convert<To, A>& e) { return whole_lines(e.a); }
-template <class Op, class A, class B> inline bool whole_lines(const Binary<Op, A, B>& e) {
-  return whole_lines(e.a) && whole_lines(e.b);
+template <class To, class A> inline bool pitch_of(const Convert<To, A>& e, int bytes) {
+  return pitch_of(e.a, bytes);
 }
-template <class E> struct leaf_count { static constexpr int value = 1; };
-template <class Op, class A> struct leaf_count<Unary<Op, A>> : leaf_count<A> {};
-template <class Op, class A, bool L> struct leaf_count<Scalar<Op, A, L>> : leaf_count<A> {};
-template <class To, class A> struct leaf_count<Convert<To, A>> : leaf_count<A> {};
-template <class Op, class A, class B> struct leaf_count<Binary<Op, A, B>> {
-  static constexpr int value = leaf_count<A>::value + leaf_count<B>::value;
+template <class Op, class A, class B> inline bool pitch_of(const Binary<Op, A, B>& e, int bytes) {
+  return pitch_of(e.a, bytes) && pitch_of(e.b, bytes);
+}
+
+// Storage bytes per element of the result that e reads, each array once.
+struct view_arrays {
+  const void* p[16];
+  int n = 0, bytes = 0;
+  void add(const void* q, int elem) {
+    for (int i = 0; i < n; ++i)
+      if (p[i] == q) return;
+    if (n < 16) p[n++] = q;
+    bytes += elem;
+  }
 };
+template <class T> inline void arrays_in(const Leaf<T>& e, view_arrays& v) { v.add(e.p, sizeof(T)); }
+template <class T> inline void arrays_in(const Sub<T>& e, view_arrays& v) { v.add(e.p, sizeof(T)); }
+template <class T> inline void arrays_in(const Trans<T>& e, view_arrays& v) { v.add(e.p, sizeof(T)); }
+template <class T> inline void arrays_in(const Diag<T>&, view_arrays&) {}
+template <class Op, class A> inline void arrays_in(const Unary<Op, A>& e, view_arrays& v) { arrays_in(e.a, v); }
+template <class Op, class A, bool L> inline void arrays_in(const Scalar<Op, A, L>& e, view_arrays& v) {
+  arrays_in(e.a, v);
+}
+template <class To, class A> inline void arrays_in(const Convert<To, A>& e, view_arrays& v) { arrays_in(e.a, v); }
+template <class Op, class A, class B> inline void arrays_in(const Binary<Op, A, B>& e, view_arrays& v) {
+  arrays_in(e.a, v);
+  arrays_in(e.b, v);
+}
 
 // src2<N>(e, r, c): an all-transposed expression at row r, columns c .. c+N-1
 // of the view: N consecutive rows of every source.  Ordinary (not streaming)
@@ -753,9 +790,13 @@ int eval_views(T* z, const E& e, hipStream_t st) {
   const uint64_t bytes = (uint64_t)rows * (uint64_t)cols * sizeof(T);
   const bool vec = KT > 0 ? rows >= NV && cols >= NV && bytes > kElementBelow : rows > kElementRows;
   const bool nts = kNTS || bytes > kStreamStoresAbove;
-  const bool lines = whole_lines(e);
-  const uint64_t total = bytes * (leaf_count<E>::value + 1);
-  const bool ntl = KT > 0 ? lines && total > kCachedBelow : total > (lines ? 1 : 2) * kCachedBelow;
+  const bool lines = pitch_of(e, 128), sets = pitch_of(e, kSetsPitch);
+  view_arrays in;
+  arrays_in(e, in);
+  const uint64_t total = bytes + (uint64_t)rows * (uint64_t)cols * in.bytes;
+  const bool few_sets = KT == 0 && sets && total > kSetsFrom;
+  const bool ntl = few_sets ? total <= kSetsTo || total > kSetsBelow
+                            : total > kCachedLoadsUpTo && (KT == 0 || lines || total <= kStraddledBelow);
   auto with_policy = [&](auto&& go) {
     if (ntl) return nts ? go(std::true_type{}, std::true_type{}) : go(std::true_type{}, std::false_type{});
     return nts ? go(std::false_type{}, std::true_type{}) : go(std::false_type{}, std::false_type{});
@@ -773,12 +814,15 @@ int eval_views(T* z, const E& e, hipStream_t st) {
       });
     }
   }
-  // one column per thread where four would leave the chip with few blocks or
-  // threads without a column; the narrow tile of transposed parts as above
+  // one column per thread where four would leave threads without a column or
+  // the chip with few blocks (sums of two submatrices: BF16 4900 x 4900, 5
+  // blocks per CU, 6.7 us against 7.3; FP32 3000 x 3000, 2 per CU, 4.3 and 4.6,
+  // 4000 x 4000, 4 per CU, 8.6 and 8.0); the narrow tile of transposed parts as
+  // above
   const int64_t wide = ceil_div(cols, tile_geo<KT, NV, 4, T>::TC) * ceil_div(rows, tile_geo<KT, NV, 4, T>::TR);
-  const bool narrow = KT > 0 ? !(lines && wide >= (int64_t)16 * device_cus())
+  const bool narrow = KT > 0 ? !(sets && wide >= (int64_t)16 * device_cus())
                              : cols < tile_geo<KT, NV, 4, T>::TC ||
-                                   wide < (int64_t)8 * device_cus();
+                                   (wide < (int64_t)(sizeof(T) == 4 ? 3 : 8) * device_cus() && !few_sets);
   auto launch = [&](auto Nc, auto Qc, auto l, auto st_) {
     constexpr int N = decltype(Nc)::value, Q = decltype(Qc)::value;
     using G = tile_geo<KT, N, Q, T>;

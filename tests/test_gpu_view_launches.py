@@ -63,3 +63,23 @@ def test_small_results(which, dtype, m):
                                    (5, 4099), (64, 3001), (65, 3001), (66, 3001), (67, 30001)])
 def test_narrow_and_short(which, dtype, shape):
     _check(which, dtype, *shape)
+
+
+# ordinary and streaming loads on both sides of 256 MiB, of 640 MiB (columns that
+# are no whole cache lines) and of 176 MiB (columns at multiples of 16 KB); the
+# wide tile of transposed parts
+@pytest.mark.parametrize("which,dtype,m", [
+    ("expr1", "f32", 3104), ("expr1", "f32", 5000), ("expr1", "f32", 5856), ("expr1", "f32", 7500),
+    ("expr1", "f64", 3001), ("expr1", "f64", 4112), ("expr1", "bf16", 6700),
+    ("expr2", "f32", 3104), ("expr2", "f32", 4112), ("expr2", "f32", 8192),
+    ("expr2", "f64", 3001), ("expr2", "f64", 4096), ("expr2", "bf16", 5857)])
+def test_large_results_with_transposed_parts(which, dtype, m):
+    _check(which, dtype, m, m)
+
+
+@pytest.mark.parametrize("which,dtype,shape", [
+    ("addsub2", "f32", (4096, 4097)), ("addsub2", "f32", (8192, 4099)), ("addsub2", "f32", (8192, 8190)),
+    ("addsub4", "f32", (4099, 4099)), ("addsub4", "f32", (8200, 8200)), ("addsub2", "bf16", (8192, 4098)),
+    ("addsub4", "f64", (6003, 6001)), ("addsub2", "f64", (2048, 9000))])
+def test_large_submatrices(which, dtype, shape):
+    _check(which, dtype, *shape)
