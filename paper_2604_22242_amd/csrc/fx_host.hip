@@ -112,10 +112,22 @@ static fx_launch colsum_launch(int elem, int64_t n_rows, int64_t n_cols, int blo
   while (b < block && b * each < n_rows) b *= 2;
   return fx_launch{b, (int64_t)b * vec >= n_rows ? 1 : ept, 16, 0};
 }
-// One thread per column up to 64 bytes of it (C2 column sums, thin against one
-// wave per column: FP32 16 rows 84 and 95 us, 24 rows 97 and 65; FP64 8 rows 48 and
-// 270, 16 rows 151 and 138; BF16 32 rows 38 and 76, 40 rows the wave's 65).
-static constexpr int64_t kThinColumnBytes = 64;
+// One thread per column up to 64 bytes of it, and up to 32 rows where there are 16
+// columns per CU.
+// Matrix workload, a thread against a wave per column, us:
+//   2^26 elements    FP32 17 rows 255, 1340, 32 rows 529, 707
+//                    FP64  9 rows 489, 3645, 16 rows 1109, 2036, 32 rows 1052, 1029
+//                    BF16 17 rows 138, 2263, 32 rows 193, 1191
+//   2^16 elements    FP32 17 rows (3855 columns) 4.0, 4.1, 32 rows (2048) 5.3, 3.5
+//                    FP64 10 rows (6553) 4.2, 6.1, 16 rows (4096) 5.4, 4.8
+// (In FP32 the two meet again at 40 to 48 rows, in BF16 beyond 64.)  No other
+// launch reaches 2^26 columns: a grid has fewer than 2^32 threads.
+constexpr int64_t kThinColumnBytes = 64, kThinRows = 32, kThinColumnsPerCU = 16;
+constexpr int kThinBlock = 256;
+static bool thin_columns(int elem, int64_t n_rows, int64_t n_cols) {
+  return n_rows * elem <= kThinColumnBytes ||
+         (n_rows <= kThinRows && n_cols >= kThinColumnsPerCU * device_cus());
+}
 
 launch resolve(int kind, int elem, int64_t n_rows, int64_t n_cols, const fx_launch* cfg,
                bool vectors) {
@@ -150,8 +162,9 @@ launch resolve(int kind, int elem, int64_t n_rows, int64_t n_cols, const fx_laun
     const fx_launch d = colsum_launch(elem, n_rows, n_cols, default_block(kind, elem), default_ept(kind, elem));
     L.block = c.block ? c.block : c.ept ? default_block(kind, elem) : d.block;
     L.ept = c.ept ? c.ept : c.block ? default_ept(kind, elem) : d.ept;
-    if (!c.split && n_rows * elem <= kThinColumnBytes) {
+    if (!c.split && thin_columns(elem, n_rows, n_cols)) {
       L.split = 0;  // thin columns: one thread per column
+      if (!c.block) L.block = kThinBlock;
     } else {
       const int64_t ncol = std::max<int64_t>(1, n_cols);
       int64_t s = c.split;

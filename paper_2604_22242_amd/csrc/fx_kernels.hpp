@@ -508,6 +508,14 @@ template <class T, class E = void, class F> inline int with_vec(int vec_elems, F
               V8 ? " or half of it" : "");
 }
 
+// The widest vector, up to 16 bytes, that a column of `rows` elements holds (one
+// element or 16 bytes for expression types with their own evaluation).
+template <class T, class E, int N = 16 / (int)sizeof(T), class F> inline int with_rows(int64_t rows, F&& f) {
+  if (rows >= N) return f(ic<N>{});
+  if constexpr (N > 1) return with_rows<T, E, vec8_compiled_v<E> ? 1 : N / 2>(rows, f);
+  return f(ic<1>{});
+}
+
 // Resolve a configuration for `n_elems` elements of storage size `elem` with
 // `n_leaves` distinct inputs.  kind: 0 element-wise, FX_R_* reductions;
 // vectors: false where a column is shorter than a vector (one element then).
@@ -677,7 +685,7 @@ int reduce_dim_direct(int kind, const E& e, O* out, void* ws, size_t ws_bytes,
   if (kind == FX_R_COLSUM) {
     if (L.split == 0) {  // thin columns: one thread per column
       const int grid = (int)std::min<int64_t>(ceil_div(cols, L.block), 1 << 20);
-      return with_vec<T, E>(rows >= W16 ? W16 : 1, [&](auto Nc) {
+      return with_rows<T, E>(rows, [&](auto Nc) {
         hipLaunchKernelGGL((k_colsum_thin<E, O, decltype(Nc)::value>), dim3(grid), dim3(L.block), 0, st, e,
                            rows, cols, out);
         return hip_check(hipGetLastError(), "k_colsum_thin launch");

@@ -1,0 +1,34 @@
+"""CPU tests of the launch rules and of what a call is refused for: no call that
+an earlier rule took may need a workspace it did not need, or exceed a grid."""
+import ctypes
+import os
+
+import pytest
+
+
+@pytest.fixture(scope="module")
+def fx():
+    import paper_2604_22242_amd as fx
+    if not os.path.exists(fx.LIB_PATH):
+        from paper_2604_22242_amd import build
+        build.build()
+    return fx
+
+
+def test_thin_columns(fx):
+    """One thread per column up to 64 bytes of it, and up to 32 rows where there
+    are 16 columns per CU; a wave or more per column elsewhere."""
+    def split(dt, rows, cols):
+        return fx.fx_resolve_launch(fx.R_COLSUM, dt, (rows, cols))[3]
+
+    elem = {fx.F32: 4, fx.F64: 8, fx.BF16: 2, fx.U32: 4}
+    for dt, e in elem.items():
+        assert split(dt, 64 // e, 10) == 0
+        assert split(dt, 9, 1 << 20) == 0
+        assert split(dt, 32, 1 << 12) == 0
+        # a grid of a wave per column has no room for these
+        for rows in (17, 32):
+            assert split(dt, rows, (1 << 26) + 5) == 0
+        assert split(dt, 33, 1 << 20) != 0
+        assert split(dt, 64 // e + 1, 100) != 0
+        assert fx.fx_workspace_bytes(fx.R_COLSUM, dt, (32, 1 << 20)) == 0
