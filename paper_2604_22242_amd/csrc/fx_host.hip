@@ -160,8 +160,10 @@ launch resolve(int kind, int elem, int64_t n_rows, int64_t n_cols, const fx_laun
     }
   } else if (kind == FX_R_COLSUM) {
     const fx_launch d = colsum_launch(elem, n_rows, n_cols, default_block(kind, elem), default_ept(kind, elem));
-    L.block = c.block ? c.block : c.ept ? default_block(kind, elem) : d.block;
-    L.ept = c.ept ? c.ept : c.block ? default_ept(kind, elem) : d.ept;
+    // (a caller's own chunks are limited to a pass of the default block each, so
+    // that the workspace they need does not follow the threads' rule)
+    L.block = c.block ? c.block : c.ept || c.split ? default_block(kind, elem) : d.block;
+    L.ept = c.ept ? c.ept : c.block || c.split ? default_ept(kind, elem) : d.ept;
     if (!c.split && thin_columns(elem, n_rows, n_cols)) {
       L.split = 0;  // thin columns: one thread per column
       if (!c.block) L.block = kThinBlock;

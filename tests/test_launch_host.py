@@ -32,3 +32,17 @@ def test_thin_columns(fx):
         assert split(dt, 33, 1 << 20) != 0
         assert split(dt, 64 // e + 1, 100) != 0
         assert fx.fx_workspace_bytes(fx.R_COLSUM, dt, (32, 1 << 20)) == 0
+
+
+def test_column_chunks_of_the_caller(fx):
+    """A split given alone is limited to a pass of the default block per chunk
+    (512 threads, 256 for half storage, a vector each); the workspace covers a
+    tape's 256 threads as well."""
+    for dt, rows_per_pass, tape_pass in ((fx.F32, 2048, 1024), (fx.F64, 1024, 512), (fx.BF16, 2048, 2048)):
+        for rows, chunks in ((100, 1), (rows_per_pass, 1), (rows_per_pass + 1, 2), (8 * rows_per_pass, 8),
+                             (100 * rows_per_pass, 8)):
+            cfg = (0, 0, 0, 8)
+            assert fx.fx_resolve_launch(fx.R_COLSUM, dt, (rows, 1000), cfg)[3] == chunks, (dt, rows)
+            most = min(8, -(-rows // tape_pass))
+            need = 0 if most == 1 else 4096 + 1000 * most * 8
+            assert fx.fx_workspace_bytes(fx.R_COLSUM, dt, (rows, 1000), cfg) == need, (dt, rows)
