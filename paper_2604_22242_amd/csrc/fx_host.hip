@@ -102,11 +102,12 @@ static constexpr int64_t kHeldTwoFrom = (int64_t)1 << 24;
 // so no more threads than take ept vectors each; with few columns, whose blocks
 // do not fill the chip, than take one.  A column of half storage takes twice its 256
 // threads where there are one or two whole columns per CU (8192 x 512 BF16 11.4,
-// 8.8; chunked columns run as fast with 256: 65536 x 64 13.6 and 13.9).
+// 8.8; longer ones are chunked, and run as fast with 256: 65536 x 64 13.6 and 13.9).
+static constexpr int64_t kLongColumn = 16384;
 static fx_launch colsum_launch(int elem, int64_t n_rows, int64_t n_cols, int block, int ept) {
   const int vec = 16 / elem;
   const int64_t cus = device_cus();
-  if (elem == 2 && n_cols >= cus && n_cols <= 2 * cus) block = 512;
+  if (elem == 2 && n_cols >= cus && n_cols <= 2 * cus && n_rows < kLongColumn) block = 512;
   const int64_t each = (int64_t)vec * (n_cols < 4 * cus ? 1 : ept);
   int b = 64;
   while (b < block && b * each < n_rows) b *= 2;
@@ -175,13 +176,21 @@ launch resolve(int kind, int elem, int64_t n_rows, int64_t n_cols, const fx_laun
       } else {
         // Chunks only where there are fewer columns than CUs (each column
         // combined across blocks costs its last block some microseconds: 4096 x
-        // 1024 FP32 11 us whole, 16 in two chunks), each at least a pass of the
-        // block; about a block per CU, two from 64 columns on (32768 x 128 FP32
-        // 13.3 us with 8 chunks, 18.1 with 16; 2^22 x 1 21 us with 256, 71 with
-        // 2048).
+        // 1024 FP32 11 us whole, 16 in two chunks) and a column is at least two
+        // full passes of the block long, a pass or part of one each; about a
+        // block per CU, two from 64 columns on (32768 x 128 FP32 13.3 us with 8
+        // chunks, 18.1 with 16; 2^22 x 1 21 us with 256, 71 with 2048).
+        const int64_t pass = (int64_t)L.block * vec16;
         const int64_t target = ncol * 4 >= cus ? 2 * cus : cus;
-        s = ncol >= cus ? 1 : ceil_div(target, ncol);
-        s = std::min<int64_t>(s, n_rows / ((int64_t)L.block * vec16 * L.ept));
+        s = ncol >= cus || n_rows < 2 * pass * L.ept ? 1 : ceil_div(target, ncol);
+        s = std::min<int64_t>(s, ceil_div(n_rows, pass));
+        // Half storage does twice the arithmetic per byte and wants the waves: up
+        // to 8 blocks per CU of at least two passes each, at most 64 chunks, which
+        // the finish reads one after another (matrix workload BF16 2^20 x 16 34 us
+        // with 64 chunks, 66 with 16; 2^20 x 64 88 with 32, 145 with 8; 65536 x 256
+        // 25.6 with 8, 37.5 whole; 200000 x 255 68 with 9, 88 with 3).
+        if (elem == 2 && ncol < 4 * cus)
+          s = std::max<int64_t>(s, std::min<int64_t>({ceil_div(8 * cus, ncol), n_rows / (2 * pass), 64}));
       }
       L.split = (int)std::max<int64_t>(1, std::min<int64_t>(s, 65535));
       if (!c.split && n_rows > 32)
@@ -246,9 +255,10 @@ fx_launch tape_launch(int kind, int elem, int64_t n_rows, int64_t n_cols, const 
     }
     case FX_R_COLSUM:
       // 512 threads with at most two columns per CU, as above 256 (8192 x 512 FP32
-      // 15.8 us with 256, 12.3); fewer for short columns (128 x 32768 FP32 109 us, 24)
+      // 15.8 us with 256, 12.3; 65536 x 512 80.5, 89.6); fewer for short columns (128
+      // x 32768 FP32 109 us, 24)
       d = fx_launch{256, half ? 1 : 2, 16, 0};
-      if (all_default) d = colsum_launch(elem, n_rows, n_cols, n_cols <= 2 * cus ? 512 : 256, half ? 1 : 2);
+      if (all_default) d = colsum_launch(elem, n_rows, n_cols, n_cols < cus || (n_cols <= 2 * cus && n_rows < kLongColumn) ? 512 : 256, half ? 1 : 2);
       d.split = n_cols >= cus ? 1 : 0;
       break;
     case FX_R_ROWSUM: d = fx_launch{512, half ? 1 : 2, 16, 0}; break;

@@ -46,3 +46,7 @@ def test_column_chunks_of_the_caller(fx):
             most = min(8, -(-rows // tape_pass))
             need = 0 if most == 1 else 4096 + 1000 * most * 8
             assert fx.fx_workspace_bytes(fx.R_COLSUM, dt, (rows, 1000), cfg) == need, (dt, rows)
+    # many columns, where a column alone takes fewer threads
+    for rows in (305, 757):
+        assert fx.fx_resolve_launch(fx.R_COLSUM, fx.F32, (rows, 5000), (0, 0, 0, 8))[3] == 1
+        assert fx.fx_workspace_bytes(fx.R_COLSUM, fx.F32, (rows, 8158790), (0, 0, 0, 8)) == 0
