@@ -510,6 +510,25 @@ template <class T, int K> struct SumN : expr_tag {
 // unconditionally, so the waits follow the loads one by one.
 constexpr int kMaxFusedLeaves = 16;
 
+// Divisions and function calls in an expression.  They are tens of instructions
+// per element, which overlap with the loads of other waves only: the launch rules
+// of sums give an expression with them more blocks per CU.
+template <class Op>
+constexpr int is_function = std::is_same_v<Op, op_div> || std::is_same_v<Op, op_exp> ||
+                            std::is_same_v<Op, op_sqrt> || std::is_same_v<Op, op_log> ||
+                            std::is_same_v<Op, op_tanh> || std::is_same_v<Op, op_pow>;
+template <class E> struct functions { static constexpr int value = 0; };
+template <class Op, class A> struct functions<Unary<Op, A>> {
+  static constexpr int value = is_function<Op> + functions<A>::value;
+};
+template <class Op, class A, class B> struct functions<Binary<Op, A, B>> {
+  static constexpr int value = is_function<Op> + functions<A>::value + functions<B>::value;
+};
+template <class Op, class A, bool LEFT> struct functions<Scalar<Op, A, LEFT>> {
+  static constexpr int value = is_function<Op> + functions<A>::value;
+};
+template <class To, class A> struct functions<Convert<To, A>> : functions<A> {};
+
 template <class E, class = void> struct leaves_of { static constexpr int value = 0; };
 template <class E> struct leaves_of<E, std::void_t<decltype(E::kLeaves)>> {
   static constexpr int value = E::kLeaves;
@@ -547,6 +566,7 @@ template <class E> struct Fused : expr_tag {
     return false;
   }
 };
+template <class E> struct functions<Fused<E>> : functions<E> {};
 
 // Host: wrap E when it has two or more register leaves.
 template <class E> inline auto fuse_leaves(const E& e) {

@@ -71,7 +71,12 @@ int check_launch(const fx_launch* c) {
 //     blocks share the latency: 2^20 FP64 7.8 against 8.7 us), every thread
 //     gets 8 vectors but at least kReduceMinBlocks blocks run (2^20 BF16: 64
 //     blocks 6.4 us, 32 blocks 7.5), and an input of at most 32 KB is one
-//     block, which needs no cross-block finish (2^12 FP32 2.7 against 3.9 us);
+//     block, which needs no cross-block finish (2^12 FP32 2.7 against 3.9 us).
+//     Expressions that divide or call functions take EPT 2 and, from 2^24
+//     elements on, two blocks per CU, whose waves overlap one's arithmetic with
+//     the other's loads (2^26 elements, us with one and with two: X / (1 + Y % Y)
+//     FP32 107, 86, BF16 93, 62; the matrix workload's expression FP32 175, 125,
+//     FP64 316, 244; five functions FP32 365, 230);
 //   column sums: one block per column, 512 threads, EPT 2 for 4- and 8-byte
 //     types, 256, EPT 1 for half types, fewer where the column has no work for
 //     them (colsum_launch), a column split into chunks only where there are
@@ -131,7 +136,7 @@ static bool thin_columns(int elem, int64_t n_rows, int64_t n_cols) {
 }
 
 launch resolve(int kind, int elem, int64_t n_rows, int64_t n_cols, const fx_launch* cfg,
-               bool vectors) {
+               bool vectors, int funcs) {
   fx_launch c = cfg ? *cfg : fx_launch{0, 0, 0, 0};
   launch L;
   const bool ew = kind == 0;
@@ -146,12 +151,13 @@ launch resolve(int kind, int elem, int64_t n_rows, int64_t n_cols, const fx_laun
   if (ew || full) {
     L.block = c.block ? c.block : default_block(kind, elem);
     L.ept = c.ept ? c.ept : default_ept(kind, elem);
-    if (full && !c.ept && n < kReduceDeepFrom) L.ept = 2;
+    if (full && !c.ept && (funcs > 0 || n < kReduceDeepFrom)) L.ept = 2;
     const int64_t tiles = std::max<int64_t>(1, ceil_div(n, (int64_t)L.block * L.ept * vec16));
     int64_t want = tiles;
     if (full) {
       const int64_t per_block = (int64_t)L.block * kReduceMinVecs * vec16;
-      want = std::min<int64_t>({tiles, cus, std::max<int64_t>(kReduceMinBlocks, n / per_block)});
+      const int64_t most = funcs > 0 && n >= kHeldTwoFrom ? 2 * cus : cus;
+      want = std::min<int64_t>({tiles, most, std::max<int64_t>(kReduceMinBlocks, n / per_block)});
       if (n * elem <= kReduceOneBlockBytes) want = 1;
     }
     L.split = c.split ? c.split : (int)std::min<int64_t>(want, 1 << 30);
@@ -189,7 +195,9 @@ launch resolve(int kind, int elem, int64_t n_rows, int64_t n_cols, const fx_laun
         // the finish reads one after another (matrix workload BF16 2^20 x 16 34 us
         // with 64 chunks, 66 with 16; 2^20 x 64 88 with 32, 145 with 8; 65536 x 256
         // 25.6 with 8, 37.5 whole; 200000 x 255 68 with 9, 88 with 3).
-        if (elem == 2 && ncol < 4 * cus)
+        // Expressions of three functions or more likewise (262144 x 256 FP32, that expression,
+        // 170 us with 8, 201 whole).
+        if ((elem == 2 || funcs >= 3) && ncol < 4 * cus)
           s = std::max<int64_t>(s, std::min<int64_t>({ceil_div(8 * cus, ncol), n_rows / (2 * pass), 64}));
       }
       L.split = (int)std::max<int64_t>(1, std::min<int64_t>(s, 65535));

@@ -518,9 +518,10 @@ template <class T, class E, int N = 16 / (int)sizeof(T), class F> inline int wit
 
 // Resolve a configuration for `n_elems` elements of storage size `elem` with
 // `n_leaves` distinct inputs.  kind: 0 element-wise, FX_R_* reductions;
-// vectors: false where a column is shorter than a vector (one element then).
+// vectors: false where a column is shorter than a vector (one element then);
+// funcs: divisions and function calls in the expression.
 launch resolve(int kind, int elem, int64_t n_rows, int64_t n_cols, const fx_launch* cfg,
-               bool vectors);
+               bool vectors, int funcs = 0);
 
 // Workspace layout: [counters, 256-byte aligned][FP64/u64 partials].
 struct ws_layout {
@@ -627,7 +628,7 @@ int reduce_full_direct(const E& e, void* out, void* ws, size_t ws_bytes, const f
   if (!out) return fail(FX_E_ARG, "NULL output pointer");
   if (int rc = check_launch(cfg)) return rc;
   const int64_t n = rows * cols;
-  launch L = resolve(FX_R_ACCU, sizeof(T), rows, cols, cfg, true);
+  launch L = resolve(FX_R_ACCU, sizeof(T), rows, cols, cfg, true, functions<E>::value);
   clamp_ept<E>(L, cfg);
   const int vec = L.vec_bytes / (int)sizeof(T);
   ws_layout W = workspace_for(FX_R_ACCU, rows, cols, L, vec);
@@ -674,7 +675,7 @@ int reduce_dim_direct(int kind, const E& e, O* out, void* ws, size_t ws_bytes,
     return hip_check(hipGetLastError(), "k_fill_zero launch");
   }
   const int W16 = 16 / (int)sizeof(T);
-  launch L = resolve(kind, sizeof(T), rows, cols, cfg, rows >= W16);
+  launch L = resolve(kind, sizeof(T), rows, cols, cfg, rows >= W16, functions<E>::value);
   clamp_ept<E>(L, cfg);
   const int vec = L.vec_bytes / (int)sizeof(T);
   ws_layout W = workspace_for(kind, rows, cols, L, vec);

@@ -1,5 +1,6 @@
 // A user's program on top of the expression front end: expressions over strided
-// views that no entry point of the library instantiates.
+// views, and sums of expressions with functions, that no entry point of the
+// library instantiates.
 #include "fx_views.hpp"
 
 using namespace fx;
@@ -20,7 +21,23 @@ template <class T> static int five(void* z, const void* const* m, int64_t n, voi
                                             t(M(5)) % X, S(st));
 }
 
+// The sum of X / (1 + Y%Y), or the column sums of exp(X)%sqrt(|Y|) / (1 + Y%Y).
+template <class T>
+static int sums(int kind, const void* x, const void* y, fx_shape s, void* out, void* ws, size_t bytes, void* st) {
+  const auto X = leaf<T>(x, s.n_rows, s.n_cols), Y = leaf<T>(y, s.n_rows, s.n_cols);
+  if (kind == FX_R_ACCU) return reduce_full<map_id>(X / (1 + Y % Y), out, ws, bytes, nullptr, S(st));
+  return reduce_dim(FX_R_COLSUM, exp(X) % sqrt(abs(Y)) / (1 + Y % Y), static_cast<acc_out_t<T>*>(out), ws,
+                    bytes, nullptr, S(st));
+}
+
 extern "C" {
+
+int user_sums_f32(int kind, const void* x, const void* y, fx_shape s, void* out, void* ws, size_t bytes, void* st) {
+  return sums<float>(kind, x, y, s, out, ws, bytes, st);
+}
+int user_sums_f64(int kind, const void* x, const void* y, fx_shape s, void* out, void* ws, size_t bytes, void* st) {
+  return sums<double>(kind, x, y, s, out, ws, bytes, st);
+}
 
 int user_five_f32(void* z, const void* const* m, int64_t n, void* st) { return five<float>(z, m, n, st); }
 int user_five_f64(void* z, const void* const* m, int64_t n, void* st) { return five<double>(z, m, n, st); }

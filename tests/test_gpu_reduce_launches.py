@@ -1,8 +1,11 @@
 """GPU tests of the dimension sums at both sides of their launch rules' lines,
 against FP64 sums."""
+import ctypes
+
 import pytest
 
 from gpu_util import need_gpu
+from test_gpu_user_views import _lib
 
 pytestmark = pytest.mark.gpu
 
@@ -54,3 +57,32 @@ def test_more_short_columns_than_waves_in_a_grid():
     fx.fx_colsum_xy(x, x, out, (rows, cols))
     torch.cuda.synchronize()
     assert bool((out[:-1] == 17).all()) and float(out[-1]) == 25.0
+
+
+@pytest.mark.parametrize("dtype", ["float32", "float64"])
+@pytest.mark.parametrize("kind,rows,cols", [
+    (1, (1 << 24) - 1, 1), (1, (1 << 24) + 5, 1), (1, 1000, 1000),     # one and two blocks per CU
+    (2, 70001, 3), (2, 40000, 1023), (2, 40000, 1024), (2, 16383, 300)])    # chunked and whole columns
+def test_sums_of_functions(dtype, kind, rows, cols):
+    """Expressions with divisions and functions in a user's program."""
+    torch, fx = need_gpu()
+    x, y = _inputs(torch, rows, cols, dtype)
+    X, Y = (v.to(torch.float64).view(cols, rows) for v in (x, y))
+    terms = X / (1 + Y * Y) if kind == 1 else X.exp() * Y.abs().sqrt() / (1 + Y * Y)
+    want, scale = (terms.sum().view(1), terms.abs().sum().view(1)) if kind == 1 else (terms.sum(1), terms.abs().sum(1))
+    n, acc = (1, torch.float64) if kind == 1 else (cols, getattr(torch, dtype))
+    out = torch.full((n,), float("nan"), dtype=acc, device="cuda")
+    ws = fx.workspace(kind, fx.dtype_code(x), (rows, cols))
+    ptr = lambda t: ctypes.c_void_p(t.data_ptr() if t is not None else 0)
+    f = getattr(_lib(), "user_sums_f32" if dtype == "float32" else "user_sums_f64")
+    # each term: exp and sqrt within 2 units together, three roundings, the sum's own
+    # (FP64: the reference's too), one rounding to the output
+    u = 2.0 ** -24 if dtype == "float32" else 2.0 ** -53 * 2
+    for _ in range(2):
+        assert f(kind, ptr(x), ptr(y), fx.Shape(rows, cols), ptr(out), ptr(ws),
+                 ctypes.c_size_t(ws.numel() if ws is not None else 0),
+                 ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+        torch.cuda.synchronize()
+        err = (out.to(torch.float64) - want).abs()
+        bound = (6.5 * u + 2.0 ** -52 * rows * cols / n) * scale
+        assert bool((err <= bound).all()), float((err / scale).max())
