@@ -280,11 +280,18 @@ constexpr int default_ept(int kind, int elem) {
 }
 
 // Blocks of a generated full reduction for the `split` that resolve() chose
-// from its block and EPT: a tree known only at run time may be bound by its
-// arithmetic, which one block per CU (a wave per SIMD) does not overlap with
-// its loads, so a grid that fills the chip is doubled.
-inline int generated_full_split(int split, int cus, int64_t tiles) {
-  return split < cus ? split : (int)(tiles < 2 * (int64_t)cus ? tiles : 2 * (int64_t)cus);
+// from its block and EPT, where the expression calls functions or may (a tree
+// known only at run time): from 2^24 elements on a grid that fills the chip is
+// doubled, as for compiled ones; below, the second half costs more in the finish
+// than it hides (2^20 FP64 11.5 us against 9.7).
+inline int generated_full_split(int split, int cus, int64_t n, int64_t tiles) {
+  return split < cus || n < (int64_t)1 << 24 ? split : (int)(tiles < 2 * (int64_t)cus ? tiles : 2 * (int64_t)cus);
+}
+
+// Threads per column of a generated column sum: those of the compiled one, at most
+// the `block` written into the source, and a wave where that takes a thread.
+inline int generated_block(int block, const launch& compiled) {
+  return compiled.split == 0 ? 64 : compiled.block < block ? compiled.block : block;
 }
 
 // Validate the user-facing fields (zeros mean "choose").

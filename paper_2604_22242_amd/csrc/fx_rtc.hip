@@ -277,12 +277,13 @@ int fx_rtc_eval(fx_rtc* r, const void* const* inputs, int32_t n_inputs, fx_shape
     return r->dt == FX_F64 ? fill_zero<double>(out, nout, st) : fill_zero<float>(out, nout, st);
   const int rkind = kind == FX_R_NORM ? FX_R_ACCU : kind;
   const int N = 16 / r->elem;
-  const fx_launch text{r->block, r->ept, 0, 0};  // what the source fixes
+  const launch chosen = resolve(rkind, r->elem, rows, cols, nullptr, true);
+  fx_launch text{r->block, r->ept, 0, 0};  // what the source fixes
+  if (kind == FX_R_COLSUM) text.block = generated_block(r->block, chosen);
   launch L = resolve(rkind, r->elem, rows, cols, &text, true);
   if (full)
-    L.split = generated_full_split(L.split, device_cus(),
-                                   ceil_div(n, (int64_t)r->block * r->ept * N));
-  L.held = resolve(rkind, r->elem, rows, cols, nullptr, true).held;
+    L.split = generated_full_split(L.split, device_cus(), n, ceil_div(n, (int64_t)r->block * r->ept * N));
+  L.held = chosen.held;
   const int vec = kind == 0 || full || rows >= N ? N : 1;
   const ws_layout W = workspace_for(rkind, rows, cols, L, vec);
   if (W.total() > 0 && (!ws || ws_bytes < W.total()))
@@ -309,7 +310,7 @@ int fx_rtc_eval(fx_rtc* r, const void* const* inputs, int32_t n_inputs, fx_shape
   if (kind == FX_R_COLSUM) {
     long rpc = (long)(ceil_div(ceil_div(rows, split), vec) * vec);
     void* args[] = {&p[0], &p[1], &p[2], &p[3], &rows_l, &split, &rpc, &parts, &ctr, &o};
-    return jit_launch(f, cols, split, r->block, args, st);
+    return jit_launch(f, cols, split, L.block, args, st);
   }
   int rl = rowsum_lanes(rows, vec);
   const int64_t rblocks = ceil_div(rows, (int64_t)rl * vec);

@@ -142,7 +142,7 @@ __device__ __forceinline__ double fx_block_sum(double v, double* lds) {
   if (lane == 0) lds[wave] = v;
   __syncthreads();
   double t = 0;
-  for (int w = 0; w < FX_BLOCK / 64; ++w) t += lds[w];
+  for (unsigned w = 0; w < blockDim.x / 64; ++w) t += lds[w];
   return t;
 }
 
@@ -227,7 +227,10 @@ extern "C" __global__ __launch_bounds__(FX_BLOCK) void fx_rtc_full(FX_PARAMS, lo
 // column c, a contiguous run; with split > 1 the chunk partials go to
 // partials[c*split + s] and the last block of column c adds them in chunk
 // order.  rpc is a multiple of N; the last rows that are no whole vector are
-// taken as one that overlaps the one before (n_rows >= N).
+// taken as one that overlaps the one before (n_rows >= N).  FX_BLOCK bounds the
+// threads; a launch has as many as the column has work for, by the same rule as
+// the compile-time skeleton (128 x 32768 FP32, matrix workload: 64 threads 18 us,
+// 512 98).
 inline constexpr char kColsum[] = R"(
 template <int N>
 __device__ __forceinline__ void fx_colsum(FX_PARAMS, long n_rows, int split, long rpc, double* partials,
@@ -241,14 +244,14 @@ __device__ __forceinline__ void fx_colsum(FX_PARAMS, long n_rows, int split, lon
   const long nv = r1 > r0 ? (r1 - r0) / N : 0;
   const long nvt = r1 > r0 + nv * N ? nv + 1 : nv;  // with the overlapping vector
   fx_acc acc[N];
-  const long tile = (long)FX_BLOCK * FX_EPT;
+  const long tile = (long)blockDim.x * FX_EPT;
   for (long t0 = 0; t0 < nvt; t0 += tile) {
     const long v0 = t0 + threadIdx.x;
     if (t0 + tile <= nv) {
       fx_raw<N> raw[FX_EPT];
       ct_t r[FX_EPT][N];
 #pragma unroll
-      for (int k = 0; k < FX_EPT; ++k) fx_load<N>(FX_ARGS, base + (v0 + (long)k * FX_BLOCK) * N, raw[k]);
+      for (int k = 0; k < FX_EPT; ++k) fx_load<N>(FX_ARGS, base + (v0 + (long)k * blockDim.x) * N, raw[k]);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int k = 0; k < FX_EPT; ++k) fx_eval<N>(FX_ARGS, raw[k], r[k]);
@@ -259,7 +262,7 @@ __device__ __forceinline__ void fx_colsum(FX_PARAMS, long n_rows, int split, lon
     } else {
 #pragma unroll
       for (int k = 0; k < FX_EPT; ++k) {
-        const long v = v0 + (long)k * FX_BLOCK;
+        const long v = v0 + (long)k * blockDim.x;
         if (v < nvt) {
           const int lo = v < nv ? 0 : (int)((nv + 1) * N - (r1 - r0));
           fx_raw<N> raw;

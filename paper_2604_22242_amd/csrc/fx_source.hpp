@@ -311,10 +311,14 @@ int eval_source(const E& e, void* out, void* ws, size_t ws_bytes, hipStream_t st
     hipLaunchKernelGGL((k_fill_zero<O>), dim3(grid), dim3(256), 0, st, static_cast<O*>(out), nout);
     return hip_check(hipGetLastError(), "k_fill_zero launch");
   }
-  const fx_launch text{default_block(rk, elem), default_ept(rk, elem), 0, 0};  // fixed in the source
-  launch L = resolve(rk, elem, rows, cols, &text, true);
-  L.held = resolve(rk, elem, rows, cols, nullptr, true).held;
-  constexpr int N = 16 / elem;
+  constexpr int N = 16 / elem, funcs = functions<E>::value;
+  const launch chosen = resolve(rk, elem, rows, cols, nullptr, true, funcs);
+  fx_launch text{default_block(rk, elem), default_ept(rk, elem), 0, 0};  // fixed in the source
+  if (KIND == FX_R_COLSUM) text.block = generated_block(text.block, chosen);
+  launch L = resolve(rk, elem, rows, cols, &text, true, funcs);
+  if (full && funcs > 0)
+    L.split = generated_full_split(L.split, device_cus(), n, ceil_div(n, (int64_t)text.block * text.ept * N));
+  L.held = chosen.held;
   const int vec = KIND == 0 || full || rows >= N ? N : 1;
   const ws_layout W = workspace_for(rk, rows, cols, L, vec);
   if (W.total() > 0 && (!ws || ws_bytes < W.total()))

@@ -86,3 +86,20 @@ def test_sums_of_functions(dtype, kind, rows, cols):
         err = (out.to(torch.float64) - want).abs()
         bound = (6.5 * u + 2.0 ** -52 * rows * cols / n) * scale
         assert bool((err <= bound).all()), float((err / scale).max())
+
+
+@pytest.mark.parametrize("dtype", ["float32", "float64", "bfloat16"])
+@pytest.mark.parametrize("cols", [7, 300, 5000])
+def test_generated_column_sums(dtype, cols):
+    """Generated kernels, with as many threads per column as it has work for."""
+    torch, fx = need_gpu()
+    code = {"float32": fx.F32, "float64": fx.F64, "bfloat16": fx.BF16}[dtype]
+    rtc = fx.Rtc(NODES, code, fx.R_COLSUM)
+    for rows in (1, 8, 24, 33, 64, 136, 257, 513, 1032, 2049, 8200):
+        x, y = _inputs(torch, rows, cols, dtype)
+        want, scale = _sums(torch, x, y, rows, cols, 0)
+        acc = torch.float64 if dtype == "float64" else torch.float32
+        ws = fx.workspace(fx.R_COLSUM, code, (rows, cols))
+        for run in (lambda o: rtc.eval([x, y], o, (rows, cols), ws),
+                    lambda o: fx.fx_source_eval("colsum_xy", [x, y], o, (rows, cols), ws)):
+            _check(torch, run, cols, acc, want, scale, dtype, rows, (rows, cols))
