@@ -208,8 +208,9 @@ launch resolve(int kind, int elem, int64_t n_rows, int64_t n_cols, const fx_laun
   } else {  // FX_R_ROWSUM
     L.block = c.block ? c.block : default_block(kind, elem);
     L.ept = c.ept ? c.ept : default_ept(kind, elem);
-    const int rl = rowsum_lanes(n_rows, vec16);
-    const int64_t tiles = std::max<int64_t>(1, ceil_div(n_rows, (int64_t)rl * vec16));
+    const int vec = vb / elem;
+    const int rl = rowsum_lanes(n_rows, n_cols, vec, elem, L.block);
+    const int64_t tiles = std::max<int64_t>(1, ceil_div(n_rows, (int64_t)rl * vec));
     int64_t s = c.split;
     if (!s) {
       const int64_t per_thread = (int64_t)(L.block / rl) * kRowsumMinCols;
@@ -288,7 +289,7 @@ fx_launch tape_launch(int kind, int elem, int64_t n_rows, int64_t n_cols, const 
 
 static size_t round256(size_t b) { return (b + 255) & ~(size_t)255; }
 
-ws_layout workspace_for(int kind, int64_t n_rows, int64_t n_cols, const launch& L, int) {
+ws_layout workspace_for(int kind, int64_t n_rows, int64_t n_cols, const launch& L, int elem, int vec) {
   ws_layout W;
   const int parts = std::max(L.split, L.held);
   if (kind == FX_R_ACCU || kind == FX_R_NORM || kind == FX_R_DOT) {
@@ -303,8 +304,8 @@ ws_layout workspace_for(int kind, int64_t n_rows, int64_t n_cols, const launch& 
     }
   } else if (kind == FX_R_ROWSUM) {
     if (parts > 1) {
-      // one counter per row tile: 64 rows or more, or the whole matrix
-      W.counter_bytes = round256((size_t)ceil_div(n_rows, 64) * 4);
+      const int rl = rowsum_lanes(n_rows, n_cols, vec, elem, L.block);  // one counter per row tile
+      W.counter_bytes = round256((size_t)ceil_div(n_rows, (int64_t)rl * vec) * 4);
       W.partial_bytes = (size_t)n_rows * parts * 8;
     }
   }
@@ -314,12 +315,13 @@ ws_layout workspace_for(int kind, int64_t n_rows, int64_t n_cols, const launch& 
 // The workspace of a tape reduction whose launch is left to the library: the
 // partials of two blocks per CU, or of kRowsumChunksHeld column chunks, so that a
 // launch model's or a caller's own split of that many fits it.
-size_t tape_workspace(int kind, int64_t n_rows, int64_t n_cols) {
+size_t tape_workspace(int kind, int elem, int64_t n_rows, int64_t n_cols) {
   launch L{};
+  L.block = 256;
   if (kind == FX_R_ACCU || kind == FX_R_NORM) L.split = 2 * device_cus();
   else if (kind == FX_R_ROWSUM) L.split = (int)std::min<int64_t>(kRowsumChunksHeld, std::max<int64_t>(1, n_cols));
   else return 0;
-  return workspace_for(kind, n_rows, n_cols, L, 1).total();
+  return workspace_for(kind, n_rows, n_cols, L, elem, 16 / elem).total();
 }
 
 }  // namespace fx
@@ -350,15 +352,15 @@ size_t fx_workspace_bytes(int kind, fx_dtype dt, fx_shape shape, const fx_launch
   if (!elem || shape.n_rows < 0 || shape.n_cols < 0 || check_launch(cfg)) return 0;
   if (kind < FX_R_ACCU || kind > FX_R_DOT) return 0;
   launch L = resolve(kind, elem, shape.n_rows, shape.n_cols, cfg, true);
-  size_t b = workspace_for(kind, shape.n_rows, shape.n_cols, L, 16 / elem).total();
+  size_t b = workspace_for(kind, shape.n_rows, shape.n_cols, L, elem, L.vec_bytes / elem).total();
   // the same call may evaluate a run-time tape, whose defaults differ:
   // enough for both
   if (kind != FX_R_DOT) {
     const fx_launch t = tape_launch(kind, elem, shape.n_rows, shape.n_cols, cfg);
     launch T = resolve(kind, elem, shape.n_rows, shape.n_cols, &t, true);
-    b = std::max(b, workspace_for(kind, shape.n_rows, shape.n_cols, T, 16 / elem).total());
+    b = std::max(b, workspace_for(kind, shape.n_rows, shape.n_cols, T, elem, T.vec_bytes / elem).total());
     if (!cfg || (!cfg->block && !cfg->ept && !cfg->vec_bytes && !cfg->split))
-      b = std::max(b, tape_workspace(kind, shape.n_rows, shape.n_cols));
+      b = std::max(b, tape_workspace(kind, elem, shape.n_rows, shape.n_cols));
   }
   return b;
 }

@@ -327,8 +327,7 @@ __global__ __launch_bounds__(kMaxBlock) void k_colsum_thin(E e, int64_t n_rows, 
 
 // ============================================================================
 // Row sums.  A block owns a tile of rl * N rows (rl lanes hold one column's
-// rows as vectors, so a wave reads 64 / rl columns at a time and the block
-// S = blockDim / rl) and chunk s of the columns: steps s, s + split, ... of
+// rows as vectors, so the block reads S = blockDim / rl columns at a time) and chunk s of the columns: steps s, s + split, ... of
 // S * EPT columns each.  Thread group g takes every S-th column of a step, EPT
 // loads per input in flight.  The S partial sums of a row are added through
 // LDS in group order; with split > 1 the chunk partials go to
@@ -350,15 +349,37 @@ __global__ __launch_bounds__(kMaxBlock) void k_colsum_thin(E e, int64_t n_rows, 
 // Now BF16 97, FP32 118, FP64 234 us; with the former kernel 210, 151, 270.
 // Dynamic LDS: blockDim * N values.
 
-// Lanes of a wave that share a column: n_rows in vectors of `vec` elements,
-// fewer (down to 128-byte runs) where that gives the finish more row tiles to
-// work on.
+// Lanes that share a column: a wave's 64, n_rows in vectors of `vec` elements where
+// that is less, fewer (down to 128-byte runs) where that gives the finish more row
+// tiles to work on, and half where 64 lanes make between half a row tile and one
+// per CU: then every tile is whole, in one block, and needs no finish (50000 x 20
+// FP32 5 us against 17, 100000 x 64 BF16 13 and 33, 65536 x 256 FP32 32 and 34).
+// Tall matrices take several waves down a column, up to the whole block,
+//  * where a step of the block has more thread groups than the matrix has columns
+//    to give each four, and the tiles still cover the chip: the groups without a
+//    column idle (2^20 x 1 BF16 13.4 us with 64 lanes, 4.5 with 512; 3 * 10^6 x 2 27
+//    and 16 FP32; 10^6 x 10 BF16 26 and 17);
+//  * where columns start at multiples of 16 KB, which share few cache sets: longer
+//    runs, while two to eight tiles per CU are left (262144 x 64 FP64 72 us with 64
+//    lanes, 59 with 256, 262144 x 256 289 and 239; 2^20 x 64 268 and 318).
+// And a grid holds less than 2^32 threads: beyond, every thread has rows of its own.
 constexpr int kRowsumMinLanes = 8, kRowsumMinTiles = 16;
-inline int rowsum_lanes(int64_t n_rows, int vec) {
+inline int rowsum_lanes(int64_t n_rows, int64_t n_cols, int vec, int elem, int block) {
   int rl = 1;
   while (rl < 64 && (int64_t)rl * vec < n_rows) rl *= 2;
   while (rl > kRowsumMinLanes && n_rows < (int64_t)kRowsumMinTiles * rl * vec) rl /= 2;
-  return rl;
+  if (rl < 64) return rl;
+  const int64_t cus = device_cus();
+  auto tiles = [&](int lanes) { return (n_rows - 1) / ((int64_t)lanes * vec) + 1; };
+  if (tiles(rl) > cus / 2 && tiles(rl) <= cus) return rl / 2;
+  while (block % (2 * rl) == 0) {
+    const int64_t t = tiles(2 * rl);
+    const bool few = n_cols < 4 * (block / rl) && t > cus;
+    const bool sets = n_rows * elem % 16384 == 0 && t >= 2 * cus && t <= 8 * cus;
+    if (!few && !sets) break;
+    rl *= 2;
+  }
+  return tiles(rl) * block > 0xffffffffll ? block : rl;
 }
 
 // Row idx of the tile: the sum over groups of lds[g * rows + idx], in order.
@@ -408,6 +429,13 @@ __global__ __launch_bounds__(kMaxBlock) void k_rowsum(E e, int64_t n_rows, int64
       for (int j = 0; j < N; ++j) acc[j].add(r.v[j]);
     }
   }
+  if (S == 1 && split == 1) {  // a row is one thread's
+    if (first < n_rows)
+#pragma unroll
+      for (int j = 0; j < N; ++j)
+        if (j >= sh) out[r0 + j] = static_cast<O>(acc[j].value());
+    return;
+  }
 #pragma unroll
   for (int j = 0; j < N; ++j)  // [group][row]
     if (j >= sh) lds[t * N + j - sh] = acc[j].value();
@@ -422,7 +450,7 @@ __global__ __launch_bounds__(kMaxBlock) void k_rowsum(E e, int64_t n_rows, int64
   if (take_last_ticket(counters + tile, split)) {
     // fl lanes side by side over rows; each of the F thread groups adds every
     // F-th chunk of its rows, then the groups' sums are added in order
-    const int fl = rows < 64 ? rows : 64, F = blockDim.x / fl, f = t / fl;
+    const int fl = rl > 64 ? rl : rows < 64 ? rows : 64, F = blockDim.x / fl, f = t / fl;
     D sum[N];
 #pragma unroll
     for (int j = 0; j < N; ++j) sum[j] = 0;
@@ -442,8 +470,8 @@ __global__ __launch_bounds__(kMaxBlock) void k_rowsum(E e, int64_t n_rows, int64
 #pragma unroll
         for (int j = 0; j < N; ++j) sum[j] += v[u][j];
     }
-    // (rows / fl <= N: rl * N rows, at least 64 of them per step unless the
-    // whole tile is smaller)
+    // (rows / fl <= N: rl * N rows, 64 or rl of them per step unless the whole
+    // tile is smaller)
 #pragma unroll
     for (int j = 0; j < N; ++j)
       if (t % fl + fl * j < rows) lds[f * rows + t % fl + fl * j] = sum[j];
@@ -528,7 +556,7 @@ struct ws_layout {
   size_t counter_bytes = 0, partial_bytes = 0;
   size_t total() const { return counter_bytes + partial_bytes; }
 };
-ws_layout workspace_for(int kind, int64_t n_rows, int64_t n_cols, const launch& L, int vec_elems);
+ws_layout workspace_for(int kind, int64_t n_rows, int64_t n_cols, const launch& L, int elem, int vec);
 
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
@@ -631,7 +659,7 @@ int reduce_full_direct(const E& e, void* out, void* ws, size_t ws_bytes, const f
   launch L = resolve(FX_R_ACCU, sizeof(T), rows, cols, cfg, true, functions<E>::value);
   clamp_ept<E>(L, cfg);
   const int vec = L.vec_bytes / (int)sizeof(T);
-  ws_layout W = workspace_for(FX_R_ACCU, rows, cols, L, vec);
+  ws_layout W = workspace_for(FX_R_ACCU, rows, cols, L, sizeof(T), vec);
   if (W.total() > 0 && (!ws || ws_bytes < W.total()))
     return fail(FX_E_WORKSPACE, "workspace of %zu bytes needed, %zu given", W.total(), ws_bytes);
   return with_vec<T, E>(vec, [&](auto Nc) {
@@ -678,7 +706,7 @@ int reduce_dim_direct(int kind, const E& e, O* out, void* ws, size_t ws_bytes,
   launch L = resolve(kind, sizeof(T), rows, cols, cfg, rows >= W16, functions<E>::value);
   clamp_ept<E>(L, cfg);
   const int vec = L.vec_bytes / (int)sizeof(T);
-  ws_layout W = workspace_for(kind, rows, cols, L, vec);
+  ws_layout W = workspace_for(kind, rows, cols, L, sizeof(T), vec);
   if (W.total() > 0 && (!ws || ws_bytes < W.total()))
     return fail(FX_E_WORKSPACE, "workspace of %zu bytes needed, %zu given", W.total(), ws_bytes);
   D* parts = ws ? ws_partials<D>(ws, W) : nullptr;
@@ -702,7 +730,7 @@ int reduce_dim_direct(int kind, const E& e, O* out, void* ws, size_t ws_bytes,
       });
     });
   }
-  const int rl = rowsum_lanes(rows, vec);
+  const int rl = rowsum_lanes(rows, cols, vec, sizeof(T), L.block);
   const int64_t rblocks = ceil_div(rows, (int64_t)rl * vec);
   return with_vec<T, E>(vec, [&](auto Nc) {
     return with_ept<max_ept<E>::value>(L.ept, [&](auto Ec) {

@@ -285,7 +285,7 @@ int fx_rtc_eval(fx_rtc* r, const void* const* inputs, int32_t n_inputs, fx_shape
     L.split = generated_full_split(L.split, device_cus(), n, ceil_div(n, (int64_t)r->block * r->ept * N));
   L.held = chosen.held;
   const int vec = kind == 0 || full || rows >= N ? N : 1;
-  const ws_layout W = workspace_for(rkind, rows, cols, L, vec);
+  const ws_layout W = workspace_for(rkind, rows, cols, L, r->elem, vec);
   if (W.total() > 0 && (!ws || ws_bytes < W.total()))
     return fail(FX_E_WORKSPACE, "workspace of %zu bytes needed, %zu given", W.total(), ws_bytes);
   const char* names[2] = {nullptr, nullptr};
@@ -312,7 +312,7 @@ int fx_rtc_eval(fx_rtc* r, const void* const* inputs, int32_t n_inputs, fx_shape
     void* args[] = {&p[0], &p[1], &p[2], &p[3], &rows_l, &split, &rpc, &parts, &ctr, &o};
     return jit_launch(f, cols, split, L.block, args, st);
   }
-  int rl = rowsum_lanes(rows, vec);
+  int rl = rowsum_lanes(rows, cols, vec, r->elem, r->block);
   const int64_t rblocks = ceil_div(rows, (int64_t)rl * vec);
   void* args[] = {&p[0], &p[1], &p[2], &p[3], &rows_l, &cols_l, &split, &rl, &parts, &ctr, &o};
   return jit_launch(f, rblocks, split, r->block, args, st);

@@ -320,7 +320,7 @@ int eval_source(const E& e, void* out, void* ws, size_t ws_bytes, hipStream_t st
     L.split = generated_full_split(L.split, device_cus(), n, ceil_div(n, (int64_t)text.block * text.ept * N));
   L.held = chosen.held;
   const int vec = KIND == 0 || full || rows >= N ? N : 1;
-  const ws_layout W = workspace_for(rk, rows, cols, L, vec);
+  const ws_layout W = workspace_for(rk, rows, cols, L, elem, vec);
   if (W.total() > 0 && (!ws || ws_bytes < W.total()))
     return fail(FX_E_WORKSPACE, "workspace of %zu bytes needed, %zu given", W.total(), ws_bytes);
   jit_program* prog = nullptr;
@@ -362,7 +362,7 @@ int eval_source(const E& e, void* out, void* ws, size_t ws_bytes, hipStream_t st
     args.insert(args.end(), {&rows_l, &split, &rpc, &parts, &ctr, &o});
     return jit_launch(fn, cols, split, L.block, args.data(), st);
   } else {
-    int rl = rowsum_lanes(rows, vec);
+    int rl = rowsum_lanes(rows, cols, vec, elem, L.block);
     args.insert(args.end(), {&rows_l, &cols_l, &split, &rl, &parts, &ctr, &o});
     return jit_launch(fn, ceil_div(rows, (int64_t)rl * vec), split, L.block, args.data(), st);
   }

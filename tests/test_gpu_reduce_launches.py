@@ -103,3 +103,42 @@ def test_generated_column_sums(dtype, cols):
         for run in (lambda o: rtc.eval([x, y], o, (rows, cols), ws),
                     lambda o: fx.fx_source_eval("colsum_xy", [x, y], o, (rows, cols), ws)):
             _check(torch, run, cols, acc, want, scale, dtype, rows, (rows, cols))
+
+
+# shapes at the lines of the row sums' lanes: half a wave down a column, a wave,
+# two and four waves, the whole block; ragged rows; with one block per row tile and
+# with several (the caller's split)
+@pytest.mark.parametrize("dtype", ["float32", "float64", "bfloat16"])
+@pytest.mark.parametrize("shape", [(1, 70000), (130001, 1), (131072, 2), (32769, 20), (32768, 5), (65537, 33),
+                                   (65536, 64), (200003, 1), (262144, 6), (262144, 64), (262151, 9), (1048579, 3),
+                                   (1000000, 7), (4194304, 1), (3000001, 2)])
+def test_row_sums(dtype, shape):
+    torch, fx = need_gpu()
+    rows, cols = shape
+    code = {"float32": fx.F32, "float64": fx.F64, "bfloat16": fx.BF16}[dtype]
+    x, y = _inputs(torch, rows, cols, dtype)
+    want, scale = _sums(torch, x, y, rows, cols, 1)
+    acc = torch.float64 if dtype == "float64" else torch.float32
+    tape, rtc = fx.Tape(NODES), fx.Rtc(NODES, code, fx.R_ROWSUM)
+    for cfg in ((0, 0, 0, 0), (0, 0, 0, 2), (192, 1, 0, 3), (64, 2, 16, 0), (512, 2, 0, 2)):
+        ws = fx.workspace(fx.R_ROWSUM, code, (rows, cols), cfg)
+        runs = [lambda o: fx.fx_tape_eval(tape, [x, y], o, (rows, cols), fx.R_ROWSUM, ws, cfg)]
+        if not any(cfg):
+            runs.append(lambda o: rtc.eval([x, y], o, (rows, cols), ws))
+        for run in runs:
+            _check(torch, run, rows, acc, want, scale, dtype, cols, (rows, cols, cfg))
+
+
+def test_more_rows_than_threads_in_a_grid():
+    """2^32 + 8 rows of half storage: with 64 lanes down a column a grid of blocks of
+    512 would be 2^32 threads and more."""
+    torch, fx = need_gpu()
+    rows = (1 << 32) + 8
+    x = torch.ones(rows, dtype=torch.bfloat16, device="cuda")
+    y = torch.full((rows,), 2.0, dtype=torch.bfloat16, device="cuda")
+    y[-1] = 3.0
+    out = torch.zeros(rows, dtype=torch.float32, device="cuda")
+    ws = fx.workspace(fx.R_ROWSUM, fx.BF16, (rows, 1))
+    fx.fx_tape_eval(fx.Tape(NODES), [x, y], out, (rows, 1), fx.R_ROWSUM, ws)
+    torch.cuda.synchronize()
+    assert bool((out[:-1] == 2).all()) and float(out[-1]) == 3.0
