@@ -350,33 +350,44 @@ __global__ __launch_bounds__(kMaxBlock) void k_colsum_thin(E e, int64_t n_rows, 
 // Dynamic LDS: blockDim * N values.
 
 // Lanes that share a column: a wave's 64, n_rows in vectors of `vec` elements where
-// that is less, fewer (down to 128-byte runs) where that gives the finish more row
-// tiles to work on, and half where 64 lanes make between half a row tile and one
-// per CU: then every tile is whole, in one block, and needs no finish (50000 x 20
-// FP32 5 us against 17, 100000 x 64 BF16 13 and 33, 65536 x 256 FP32 32 and 34).
+// that is less, and fewer (down to 128-byte runs) where that gives the finish at
+// least 16 row tiles to work on, 4 from 2^24 elements on, where longer runs matter
+// more (500 x 134217 FP64 315 us with 8 lanes, 257 with 32; 512 x 8192 21 and 23).
+// 32 where 64 make
+//  * between half a row tile and one per CU: then every tile is whole, in one
+//    block, and needs no finish (50000 x 20 FP32 5 us against 17, 100000 x 64 BF16 13
+//    and 33, 65536 x 256 FP32 32 and 34);
+//  * between 2 and 3 1/4 per CU, of which two run at a time and the rest fill half
+//    a round (200000 x 256 FP32 102 and 110, 100000 x 100 FP64 40 and 48).
 // Tall matrices take several waves down a column, up to the whole block,
-//  * where a step of the block has more thread groups than the matrix has columns
-//    to give each four, and the tiles still cover the chip: the groups without a
-//    column idle (2^20 x 1 BF16 13.4 us with 64 lanes, 4.5 with 512; 3 * 10^6 x 2 27
-//    and 16 FP32; 10^6 x 10 BF16 26 and 17);
+//  * where the block has more thread groups than the matrix keeps in columns, and
+//    the tiles still cover the chip.  Half storage: while a group has at most four
+//    columns (2^20 x 1 13.4 us with 64 lanes, 5.6 with 256; 10^6 x 10 26 and 17).
+//    Others the whole block up to 10 columns (3 * 10^6 x 2 FP32 27 and 16, 10^6 x 6
+//    15 and 13, x 10 22 and 21; x 20 39 and 40);
 //  * where columns start at multiples of 16 KB, which share few cache sets: longer
 //    runs, while two to eight tiles per CU are left (262144 x 64 FP64 72 us with 64
 //    lanes, 59 with 256, 262144 x 256 289 and 239; 2^20 x 64 268 and 318).
 // And a grid holds less than 2^32 threads: beyond, every thread has rows of its own.
-constexpr int kRowsumMinLanes = 8, kRowsumMinTiles = 16;
+constexpr int kRowsumMinLanes = 8, kRowsumMinTiles = 16, kRowsumLargeTiles = 4;
+constexpr int64_t kRowsumLarge = int64_t(1) << 24;
 inline int rowsum_lanes(int64_t n_rows, int64_t n_cols, int vec, int elem, int block) {
   int rl = 1;
   while (rl < 64 && (int64_t)rl * vec < n_rows) rl *= 2;
-  while (rl > kRowsumMinLanes && n_rows < (int64_t)kRowsumMinTiles * rl * vec) rl /= 2;
+  const int64_t least = n_rows * n_cols < kRowsumLarge ? kRowsumMinTiles : kRowsumLargeTiles;
+  while (rl > kRowsumMinLanes && n_rows < least * rl * vec) rl /= 2;
   if (rl < 64) return rl;
   const int64_t cus = device_cus();
   auto tiles = [&](int lanes) { return (n_rows - 1) / ((int64_t)lanes * vec) + 1; };
-  if (tiles(rl) > cus / 2 && tiles(rl) <= cus) return rl / 2;
+  const bool same_sets = n_rows * elem % 16384 == 0;
+  const int64_t t64 = tiles(rl);
+  if (t64 > cus / 2 && t64 <= cus) return rl / 2;
+  if (t64 > 2 * cus && 4 * t64 <= 13 * cus && n_cols >= 16 && !same_sets) return rl / 2;
+  if (elem != 2 && n_cols <= 10 && 2 * tiles(block) > 3 * cus) return block;
   while (block % (2 * rl) == 0) {
     const int64_t t = tiles(2 * rl);
-    const bool few = n_cols < 4 * (block / rl) && t > cus;
-    const bool sets = n_rows * elem % 16384 == 0 && t >= 2 * cus && t <= 8 * cus;
-    if (!few && !sets) break;
+    const bool few = elem == 2 && n_cols <= 4 * (block / rl) && t > cus;
+    if (!few && !(same_sets && t >= 2 * cus && t <= 8 * cus)) break;
     rl *= 2;
   }
   return tiles(rl) * block > 0xffffffffll ? block : rl;
