@@ -257,7 +257,7 @@ struct launch {
   int ept;        // independent vector loads per leaf per thread (1,2,4,8)
   int vec_bytes;  // bytes per vector load (storage bytes, 2..16)
   int split;      // grid size / blocks per column / column chunks
-  int held = 0;   // partials the workspace has to hold where these are more than split
+  size_t held = 0;  // bytes of workspace to ask for where the launch needs fewer
 };
 
 inline bool pow2(int v) { return v > 0 && (v & (v - 1)) == 0; }

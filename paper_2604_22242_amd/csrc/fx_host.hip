@@ -96,9 +96,15 @@ static constexpr int kRowsumMinCols = 2;
 static constexpr int kRowsumMaxSplit = 128;
 static constexpr int kRowsumChunksHeld = 64;
 // Whether a reduction needs a workspace, and of what size, is part of the
-// interface and does not follow the launch heuristics down: calls that leave the
-// split to the library ask for the partials of the two-blocks-per-CU launches
-// (launch::held), though fewer are written.
+// interface and does not follow the launch heuristics: calls that leave the
+// split to the library ask for the bytes of fixed launches (launch::held: full sums
+// by two blocks per CU, column sums by eight, row sums in chunks of at least 32
+// columns), though they write fewer partials.
+static size_t round256(size_t b) { return (b + 255) & ~(size_t)255; }
+// `parts` partial sums of each of n_out results, `counters` finish counters
+static size_t held_bytes(int64_t parts, int64_t n_out, int64_t counters) {
+  return parts > 1 ? round256((size_t)counters * 4) + (size_t)n_out * parts * 8 : 0;
+}
 static constexpr int64_t kHeldTwoFrom = (int64_t)1 << 24;
 
 // Column sums: threads for a column of n_rows, at most `block` of them with `ept`
@@ -163,7 +169,7 @@ launch resolve(int kind, int elem, int64_t n_rows, int64_t n_cols, const fx_laun
     L.split = c.split ? c.split : (int)std::min<int64_t>(want, 1 << 30);
     if (full && !c.split) {
       const int64_t t2 = std::max<int64_t>(1, ceil_div(n, (int64_t)L.block * (c.ept ? c.ept : 2) * vec16));
-      L.held = (int)std::min<int64_t>({t2, n < kHeldTwoFrom ? cus : 2 * cus, std::max<int64_t>(32, t2 / 4)});
+      L.held = held_bytes(std::min<int64_t>({t2, n < kHeldTwoFrom ? cus : 2 * cus, std::max<int64_t>(32, t2 / 4)}), 1, 1);
     }
   } else if (kind == FX_R_COLSUM) {
     const fx_launch d = colsum_launch(elem, n_rows, n_cols, default_block(kind, elem), default_ept(kind, elem));
@@ -202,8 +208,8 @@ launch resolve(int kind, int elem, int64_t n_rows, int64_t n_cols, const fx_laun
       }
       L.split = (int)std::max<int64_t>(1, std::min<int64_t>(s, 65535));
       if (!c.split && n_rows > 32)
-        L.held = (int)std::min<int64_t>({ceil_div(8 * cus, ncol), 65535, std::max<int64_t>(1, ceil_div(
-            n_rows, (int64_t)(c.block ? c.block : default_block(kind, elem)) * vec16))});
+        L.held = held_bytes(std::min<int64_t>({ceil_div(8 * cus, ncol), 65535, std::max<int64_t>(1, ceil_div(
+            n_rows, (int64_t)(c.block ? c.block : default_block(kind, elem)) * vec16))}), n_cols, n_cols);
     }
   } else {  // FX_R_ROWSUM
     L.block = c.block ? c.block : default_block(kind, elem);
@@ -222,7 +228,8 @@ launch resolve(int kind, int elem, int64_t n_rows, int64_t n_cols, const fx_laun
     if (!c.block && !c.ept && !c.vec_bytes && !c.split) {
       const int block = elem == 2 ? 64 : 256;
       const int64_t blocks = std::max<int64_t>(1, ceil_div(n_rows, (int64_t)block * vec16));
-      L.held = (int)std::max<int64_t>(1, std::min<int64_t>({ceil_div(cus * 512 / block, blocks), n_cols / 32, 65535}));
+      L.held = held_bytes(std::max<int64_t>(1, std::min<int64_t>({ceil_div(cus * 512 / block, blocks), n_cols / 32, 65535})),
+                          n_rows, ceil_div(n_rows, block));
     }
   }
   return L;
@@ -287,46 +294,34 @@ fx_launch tape_launch(int kind, int elem, int64_t n_rows, int64_t n_cols, const 
   return c;
 }
 
-static size_t round256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 ws_layout workspace_for(int kind, int64_t n_rows, int64_t n_cols, const launch& L, int elem, int vec) {
   ws_layout W;
-  const int parts = std::max(L.split, L.held);
+  const size_t parts = L.split > 1 ? L.split : 0;
   if (kind == FX_R_ACCU || kind == FX_R_NORM || kind == FX_R_DOT) {
-    if (parts > 1) {
-      W.counter_bytes = 256;
-      W.partial_bytes = (size_t)parts * 8;
-    }
+    if (parts) W.counter_bytes = 256;
+    W.partial_bytes = parts * 8;
   } else if (kind == FX_R_COLSUM) {
-    if (parts > 1) {
-      W.counter_bytes = round256((size_t)n_cols * 4);
-      W.partial_bytes = (size_t)n_cols * parts * 8;
-    }
+    if (parts) W.counter_bytes = round256((size_t)n_cols * 4);
+    W.partial_bytes = (size_t)n_cols * parts * 8;
   } else if (kind == FX_R_ROWSUM) {
-    if (parts > 1) {
-      const int rl = rowsum_lanes(n_rows, n_cols, vec, elem, L.block);  // one counter per row tile
-      W.counter_bytes = round256((size_t)ceil_div(n_rows, (int64_t)rl * vec) * 4);
-      W.partial_bytes = (size_t)n_rows * parts * 8;
-    }
+    const int rl = rowsum_lanes(n_rows, n_cols, vec, elem, L.block);  // one counter per row tile
+    if (parts) W.counter_bytes = round256((size_t)ceil_div(n_rows, (int64_t)rl * vec) * 4);
+    W.partial_bytes = (size_t)n_rows * parts * 8;
   }
+  if (W.total() < L.held) W.partial_bytes = L.held - W.counter_bytes;
   return W;
 }
 
 // The workspace of a tape reduction whose launch is left to the library: the
 // partials of two blocks per CU, or of kRowsumChunksHeld column chunks, so that a
 // launch model's or a caller's own split of that many fits it.
-size_t tape_workspace(int kind, int elem, int64_t n_rows, int64_t n_cols) {
-  launch L{};
-  L.block = 256;
-  if (kind == FX_R_ACCU || kind == FX_R_NORM) L.split = 2 * device_cus();
-  else if (kind == FX_R_ROWSUM) L.split = (int)std::min<int64_t>(kRowsumChunksHeld, std::max<int64_t>(1, n_cols));
-  else return 0;
-  return workspace_for(kind, n_rows, n_cols, L, elem, 16 / elem).total();
+size_t tape_workspace(int kind, int64_t n_rows, int64_t n_cols) {
+  if (kind == FX_R_ACCU || kind == FX_R_NORM) return held_bytes(2 * device_cus(), 1, 1);
+  if (kind == FX_R_ROWSUM)
+    return held_bytes(std::min<int64_t>(kRowsumChunksHeld, n_cols), n_rows, ceil_div(n_rows, 256));
+  return 0;
 }
-
-}  // namespace fx
-
-using namespace fx;
 
 static int elem_size(fx_dtype dt) {
   switch (dt) {
@@ -336,6 +331,25 @@ static int elem_size(fx_dtype dt) {
   }
   return 0;
 }
+
+size_t rowsum_extra_counters(int kind, fx_dtype dt, fx_shape s, const fx_launch* cfg) {
+  const int elem = elem_size(dt);
+  if (kind != FX_R_ROWSUM || !elem || !cfg || (!cfg->block && !cfg->ept && !cfg->vec_bytes && !cfg->split)) return 0;
+  const int64_t block = cfg->block ? cfg->block : elem == 2 ? 64 : 256;
+  const fx_launch t = tape_launch(kind, elem, s.n_rows, s.n_cols, cfg);
+  size_t most = 0;
+  for (const fx_launch* c : {cfg, &t}) {
+    const launch L = resolve(kind, elem, s.n_rows, s.n_cols, c, true);
+    if (L.split > 1)
+      most = std::max(most, workspace_for(kind, s.n_rows, s.n_cols, L, elem, L.vec_bytes / elem).counter_bytes);
+  }
+  const size_t one_per_block = round256((size_t)ceil_div(s.n_rows, block) * 4);
+  return most > one_per_block ? most - one_per_block : 0;
+}
+
+}  // namespace fx
+
+using namespace fx;
 
 extern "C" {
 
@@ -360,7 +374,7 @@ size_t fx_workspace_bytes(int kind, fx_dtype dt, fx_shape shape, const fx_launch
     launch T = resolve(kind, elem, shape.n_rows, shape.n_cols, &t, true);
     b = std::max(b, workspace_for(kind, shape.n_rows, shape.n_cols, T, elem, T.vec_bytes / elem).total());
     if (!cfg || (!cfg->block && !cfg->ept && !cfg->vec_bytes && !cfg->split))
-      b = std::max(b, tape_workspace(kind, elem, shape.n_rows, shape.n_cols));
+      b = std::max(b, tape_workspace(kind, shape.n_rows, shape.n_cols));
   }
   return b;
 }

@@ -2,7 +2,7 @@
 //
 // The reductions of a tape need a workspace (per-block partials and the
 // finish counters).  Here it is one file-scope device array, `scratch`, of
-// kStaticScratchBytes; every GPU holds its own copy for the life of the
+// kStaticAllBytes; every GPU holds its own copy for the life of the
 // process.  In host code the array's name is only a stand-in for the symbol,
 // so the first call on a device looks its device address up
 // (hipGetSymbolAddress) and clears the array with a fill kernel on the
@@ -16,9 +16,14 @@
 namespace fx {
 
 constexpr size_t kStaticScratchBytes = size_t(16) << 20;
+// Row sums keep a finish counter per row tile, of 32 rows or more: up to 2^20 rows
+// (two chunks of 8 bytes each fill the scratch) they have room of their own, so
+// that which calls fit does not depend on the tiles.
+constexpr size_t kStaticCounterBytes = size_t(128) << 10;
+constexpr size_t kStaticAllBytes = kStaticScratchBytes + kStaticCounterBytes;
 constexpr int kMaxDevices = 64;
 
-static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
+static __device__ __align__(256) unsigned char scratch[kStaticAllBytes];
 
 namespace {
 
@@ -36,7 +41,7 @@ int device_scratch(hipStream_t st, void** out) {
     void* p = nullptr;
     if (int rc = hip_check(hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)), "hipGetSymbolAddress"))
       return rc;
-    const int64_t words = (int64_t)(kStaticScratchBytes / sizeof(uint32_t));
+    const int64_t words = (int64_t)(kStaticAllBytes / sizeof(uint32_t));
     hipLaunchKernelGGL((k_fill_zero<uint32_t>), dim3(1024), dim3(256), 0, st,
                        static_cast<uint32_t*>(p), words);
     if (int rc = hip_check(hipGetLastError(), "k_fill_zero launch")) return rc;
@@ -59,7 +64,7 @@ int fx_tape_eval_static(const fx_tape* t, fx_dtype dt, const void* const* inputs
   if (int rc = check_shape(s)) return rc;
   if (int rc = check_launch(cfg)) return rc;
   if (kind != 0) {
-    const size_t need = fx_workspace_bytes(kind, dt, s, cfg);
+    const size_t need = fx_workspace_bytes(kind, dt, s, cfg) - rowsum_extra_counters(kind, dt, s, cfg);
     if (need > kStaticScratchBytes)
       return fail(FX_E_WORKSPACE,
                   "the reduction needs %zu bytes of workspace; the static scratch holds %zu",
@@ -67,7 +72,7 @@ int fx_tape_eval_static(const fx_tape* t, fx_dtype dt, const void* const* inputs
   }
   void* ws = nullptr;
   if (int rc = device_scratch(S(stream), &ws)) return rc;
-  return tape_eval_exact(t, dt, inputs, n_inputs, s, kind, out, ws, kStaticScratchBytes, cfg,
+  return tape_eval_exact(t, dt, inputs, n_inputs, s, kind, out, ws, kStaticAllBytes, cfg,
                          S(stream));
 }
 

@@ -330,7 +330,11 @@ template <class T, bool B, int S> struct vec8_compiled<TapeExpr<T, B, S>> {
 // launch heuristics in fx_host.hip.
 fx_launch tape_launch(int kind, int elem, int64_t n_rows, int64_t n_cols, const fx_launch* cfg);
 // The workspace a tape reduction asks for when its launch is left to the library.
-size_t tape_workspace(int kind, int elem, int64_t n_rows, int64_t n_cols);
+size_t tape_workspace(int kind, int64_t n_rows, int64_t n_cols);
+
+// Bytes of fx_workspace_bytes that are finish counters of row sums beyond one per
+// `block` rows of a caller's configuration (0 for the library's own).
+size_t rowsum_extra_counters(int kind, fx_dtype dt, fx_shape s, const fx_launch* cfg);
 
 // Evaluate a tape of storage type T (defined once per dtype, in its own
 // translation unit, to keep compile times short).
@@ -350,7 +354,7 @@ int tape_eval_impl(const tape_prog& prog, const void* const* inputs, fx_shape s,
   // fields left at 0 take the interpreter's own defaults, not the library's
   const fx_launch c = tape_launch(kind, (int)sizeof(T), s.n_rows, s.n_cols, cfg);
   if (out && (!cfg || (!cfg->block && !cfg->ept && !cfg->vec_bytes && !cfg->split))) {
-    const size_t need = tape_workspace(kind, (int)sizeof(T), s.n_rows, s.n_cols);
+    const size_t need = tape_workspace(kind, s.n_rows, s.n_cols);
     if (need > 0 && (!ws || ws_bytes < need))
       return fail(FX_E_WORKSPACE, "workspace of %zu bytes needed, %zu given", need, ws_bytes);
   }

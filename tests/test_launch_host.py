@@ -50,3 +50,25 @@ def test_column_chunks_of_the_caller(fx):
     for rows in (305, 757):
         assert fx.fx_resolve_launch(fx.R_COLSUM, fx.F32, (rows, 5000), (0, 0, 0, 8))[3] == 1
         assert fx.fx_workspace_bytes(fx.R_COLSUM, fx.F32, (rows, 8158790), (0, 0, 0, 8)) == 0
+
+
+FAKE = 0x10000
+C2 = [("leaf", -1, -1, 0, 0.0), ("leaf", -1, -1, 1, 0.0), ("add", 0, 1, -1, 0.0)]
+
+
+def test_static_scratch_takes_the_row_sums_it_took(fx):
+    """64 chunks of 32767 rows and a counter per 256 of them fill 16 MiB; the finer
+    counters that the tiles need do not count against it."""
+    def refused(dt, rows, cols, cfg):
+        # (a NULL input is found after the workspace: nothing is enqueued)
+        L, tape = fx.lib(), fx.Tape(C2)
+        arr = (ctypes.c_void_p * 2)(None, FAKE)
+        c = ctypes.pointer(fx.Launch(*cfg)) if cfg else None
+        return L.fx_tape_eval_static(tape.handle, dt, arr, 2, fx.Shape(rows, cols), fx.R_ROWSUM, FAKE, c,
+                                     None) == 4 and "static scratch" in fx.fx_last_error()
+
+    for dt in (fx.F32, fx.F64, fx.BF16):
+        assert fx.fx_workspace_bytes(fx.R_ROWSUM, dt, (32767, 126)) == 16 << 20
+        for cfg in (None, (256, 2, 0, 64), (256, 1, 8, 64)):
+            assert not refused(dt, 32767, 126, cfg), (dt, cfg)
+            assert refused(dt, 32768, 126, cfg), (dt, cfg)
