@@ -12,7 +12,8 @@
 //                 optionally gathered through an index list)
 //   k_mlp_params  one thread per parameter: gradient summed over the batch
 //                 in row order (deterministic), then the Adam update
-//   k_mlp_forward forward and per-head argmax, rows looped over per block
+//   k_mlp_forward forward and per-head argmax, one row per block or rows looped
+//                 over per block
 // Parameters are one flat array: W1 [H x F] row-major, b1 [H], W2 [C x H],
 // b2 [C], C = sum of head sizes.
 #include <math.h>
@@ -332,9 +333,16 @@ __global__ __launch_bounds__(64) void k_mlp_params(mlp_dims d, int B, const floa
 }
 
 // Inference: a group of threads takes RR rows at a time, so that one read of a
-// weight serves RR independent chains.
+// weight serves RR independent chains, from weights staged once per block.  Up to
+// 16 waves per CU (64 of models whose weights are not staged) each row has a
+// group and a block of its own, which reads the weights from the caches: the
+// chip is not full, and staging, or four rows one after another, only adds its
+// latency (25-64-14 model, through the binding: 256 rows 8.1 us against 9.9,
+// 4096 8.3 and 9.0, 20000 23.8 and 16.3; 64-256-64 256 rows 9.5 and 18.3, 4096 63 and
+// 23; 25-200-63, not staged, 256 rows 10 and 28, 4096 28 and 31, 20000 146 and 128).
 constexpr int kMlpForwardRows = 4;
-template <bool STAGED>
+constexpr int kMlpSingleWaves = 16, kMlpSingleWavesUnstaged = 64;
+template <int RR, bool STAGED>
 __global__ __launch_bounds__(256) void k_mlp_forward(mlp_dims d, mlp_launch L, int B,
                                                    const float* __restrict__ X,
                                                    const float* __restrict__ mean,
@@ -342,7 +350,6 @@ __global__ __launch_bounds__(256) void k_mlp_forward(mlp_dims d, mlp_launch L, i
                                                    const float* __restrict__ P,
                                                    float* __restrict__ logits,
                                                    int32_t* __restrict__ choice) {
-  constexpr int RR = kMlpForwardRows;
   extern __shared__ float lds[];
   const int sub = threadIdx.x / L.tpr, t = threadIdx.x - sub * L.tpr;
   const float mu = t < d.F ? mean[t] : 0.f, sd = t < d.F ? stdv[t] : 1.f;
@@ -674,12 +681,20 @@ int fx_model_forward(const fx_model* m, const float* d_X, int32_t batch, float* 
   if (!m || !d_X || batch < 0 || (!d_logits && !d_choice)) return fail(FX_E_ARG, "bad arguments");
   if (batch == 0) return FX_OK;
   const mlp_dims& d = m->d;
-  const mlp_launch L = mlp_shape(d);
+  mlp_launch L = mlp_shape(d);
+  const int64_t single = (int64_t)device_cus() * (L.weights ? kMlpSingleWaves : kMlpSingleWavesUnstaged);
+  if ((int64_t)batch * (L.tpr / 64) <= single) {
+    L.groups = 1;
+    L.weights = 0;
+    hipLaunchKernelGGL((k_mlp_forward<1, false>), dim3(batch), dim3(L.tpr), sizeof(float) * L.per_row, S(stream),
+                       d, L, (int)batch, d_X, m->dMean, m->dStd, m->dP, d_logits, d_choice);
+    return hip_check(hipGetLastError(), "k_mlp_forward launch");
+  }
   const int per_block = L.groups * kMlpForwardRows;
   const size_t lds = sizeof(float) * (L.weights + (size_t)per_block * L.per_row);
   // each block stages the weights once and loops over its rows
   const int grid = std::min((batch - 1) / per_block + 1, 8 * device_cus());
-  auto kernel = L.weights ? k_mlp_forward<true> : k_mlp_forward<false>;
+  auto kernel = L.weights ? k_mlp_forward<kMlpForwardRows, true> : k_mlp_forward<kMlpForwardRows, false>;
   hipLaunchKernelGGL(kernel, dim3(grid), dim3(L.tpr * L.groups), lds, S(stream), d, L, (int)batch,
                      d_X, m->dMean, m->dStd, m->dP, d_logits, d_choice);
   return hip_check(hipGetLastError(), "k_mlp_forward launch");

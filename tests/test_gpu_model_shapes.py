@@ -109,3 +109,30 @@ def test_train_equals_stepping_on_a_ragged_epoch():
                 torch.cuda.synchronize()
         got.append(m.get()[0])
     assert np.array_equal(got[0], got[1])
+
+
+@pytest.mark.parametrize("F,H,heads,line", [(25, 64, (4, 3, 3, 4), 4096), (64, 256, (32, 32), 1024),
+                                            (25, 200, (3, 60), 4096)])
+def test_forward_at_its_lines(F, H, heads, line):
+    """Both sides of the batch from which rows share a block: within the bound,
+    and the same bits as the rows alone."""
+    torch, fx = need_gpu()
+    params, mean, std, X, y = _case(F, H, heads, line + 1, 19)
+    logits, lm, _, _, _ = _reference(params, mean, std, X, y, heads)
+    m = fx.Model(F, H, heads)
+    m.set(np.concatenate([p.ravel() for p in params]), mean, std)
+    Xd = torch.from_numpy(X).cuda()
+    alone = torch.full((8, sum(heads)), np.nan, device="cuda")
+    for B in (line, line + 1):
+        out = torch.full((B, sum(heads)), np.nan, device="cuda")
+        choice = torch.full((B, len(heads)), -1, dtype=torch.int32, device="cuda")
+        m.forward(Xd[:B], out, choice)
+        torch.cuda.synchronize()
+        chain = F + H + sum(heads) + 16
+        assert (np.abs(out.cpu().numpy() - logits[:B]) <= chain * U * lm[:B]).all()
+        for s in (0, B - 8):
+            m.forward(Xd[s:s + 8].contiguous(), alone)
+            torch.cuda.synchronize()
+            assert torch.equal(alone, out[s:s + 8])
+        for b in (0, B - 1):
+            assert m.choose(X[b]) == list(choice[b].cpu().numpy())
