@@ -37,9 +37,12 @@
  *   - An element-wise output may be exactly one of the inputs (in place);
  *     partial overlap is not allowed.
  *   - Inputs are read with streaming (nontemporal) loads, except by compiled
- *     element-wise calls whose inputs and output together are at most 256 MiB
- *     (MI355X's last-level cache) and by strided views whose tiles share cache
- *     lines: these leave the inputs in that cache.  An element-wise output
+ *     element-wise calls and strided views whose distinct inputs and output
+ *     together are at most 256 MiB (MI355X's last-level cache), by views with
+ *     transposed parts above 640 MiB whose columns are no whole cache lines, and
+ *     by sums of short columns: these leave the inputs in that cache.  (Views of
+ *     submatrices whose columns start at multiples of 16 KB stream already from
+ *     176 MiB, and between 32 and 64.)  An element-wise output
  *     larger than 256 MiB that is written with 16-byte vectors is written with
  *     streaming stores, so it is not left in that cache; smaller outputs use
  *     ordinary stores.
@@ -371,8 +374,8 @@ int32_t fx_tape_program(const fx_tape* t, uint16_t* op, uint8_t* slot, uint8_t* 
  * threads, EPT 2 for 4- and 8-byte types from 2^20 elements on);
  * accu / norm 512 threads (128 between one tile of those and 2^17 elements),
  * EPT 2 (1 for half types), a block per tile up to 2 per CU;
- * column sums up to 256 threads (512 with at most two columns per CU; no more
- * than the column has work for), EPT 2 (1 for half types), one block per column
+ * column sums up to 256 threads (512 with fewer columns than CUs, and with at
+ * most two per CU of less than 16384 rows; no more than the column has work for), EPT 2 (1 for half types), one block per column
  * when there are at least as many columns as CUs; row sums 512 threads,
  * EPT 2 (1 for half types).  The split default applies
  * only when all of cfg is 0 (or cfg is NULL); then a model attached with
@@ -391,8 +394,9 @@ int fx_tape_eval(const fx_tape* t, fx_dtype dt, const void* const* inputs, int32
  * of a caller's.  The caller still passes inputs and outputs.  The launch is
  * cfg, or the interpreter's defaults for fields left at 0; a model attached
  * with fx_tape_set_model is not consulted.  A reduction whose
- * fx_workspace_bytes exceeds 16 MiB gives FX_E_WORKSPACE before anything is
- * enqueued.  The first call on a device looks the array's address up and
+ * fx_workspace_bytes exceeds 16 MiB (of row sums under a configuration of the
+ * caller's: not counting finish counters beyond one per block of rows) gives
+ * FX_E_WORKSPACE before anything is enqueued.  The first call on a device looks the array's address up and
  * clears it with a kernel on `stream`; every call leaves its finish counters
  * at zero.  No call allocates: no hipMalloc, hipFree or allocating library
  * routine.  All calls on one GPU share the array, so calls that may overlap

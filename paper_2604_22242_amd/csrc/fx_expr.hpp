@@ -37,9 +37,9 @@ struct leaf_info {
   int64_t n_rows = -1, n_cols = -1;
   bool shape_ok = true;
   bool any_null = false;
-  int arrays = 0;  // leaves that read one, repeats included
-  void add(const void* p, int64_t r, int64_t c) {
-    ++arrays;
+  int bytes = 0;  // storage bytes per element of the arrays read, repeats included
+  void add(const void* p, int64_t r, int64_t c, int elem) {
+    bytes += elem;
     if (!p && r * c > 0) any_null = true;
     if (n_rows < 0) { n_rows = r; n_cols = c; }
     else if (r != n_rows || c != n_cols) shape_ok = false;
@@ -77,7 +77,7 @@ template <class T> struct Leaf : expr_tag {
   __device__ __forceinline__ lanes<ct, N> at_vec(int64_t i) const {
     return load_lanes<N, NT>(p, i);
   }
-  void collect(leaf_info& li) const { li.add(p, n_rows, n_cols); }
+  void collect(leaf_info& li) const { li.add(p, n_rows, n_cols, sizeof(T)); }
   // two-phase evaluation (see Fused below): this leaf is register leaf OFF
   static constexpr int kLeaves = 1;
   template <int OFF, int N, bool NT, class R>
@@ -135,9 +135,11 @@ __device__ __forceinline__ bool any_lane(bool c) { return __builtin_amdgcn_ballo
 // function: each element's value depends on it alone.  In issue slots per lane
 // (a transcendental takes four): exp 16 -> 12.5, sqrt 19 -> 10.
 //
-// exp, |x| <= 87: x log2(e) = n + f with n the nearest integer; log2(e) in two
-// parts, the product's rounding error recovered by an FMA, so that f is rounded
-// once; 2^f in hardware; 2^n added to the exponent field (the result and 2^f
+// exp, |x| <= 87: x log2(e) = n + f with n the nearest integer (the additive
+// reduction of Cody and Waite, Software Manual for the Elementary Functions, 1980);
+// log2(e) in two parts, the product's rounding error recovered by an FMA (Muller
+// et al., Handbook of Floating-Point Arithmetic, on the exact product), so that f
+// is rounded once; 2^f in hardware; 2^n added to the exponent field (the result and 2^f
 // are normal there).  n is the low end of t, whose ulp is 1.
 __device__ __forceinline__ float exp_common(float x) {
 #pragma clang fp contract(off)
@@ -186,8 +188,9 @@ template <class MOD, bool IN_PLACE, int N> __device__ __forceinline__ void exp_l
 }
 
 // sqrt, 2^-96 <= x finite, and 0: s = x y from the hardware's y ~ 1 / sqrt(x),
-// then one Newton step on the exact residual x - s s.  Correctly rounded, as
-// the library's: compared for every FP32 in that range.  (The addend, nothing to
+// then one Newton step on the exact residual x - s s (Markstein, IBM J. Res. Dev.
+// 34, 1990).  Correctly rounded, as the library's: compared for every FP32 in that
+// range.  (The addend, nothing to
 // x from 2^-96 on, keeps y finite at 0.)
 __device__ __forceinline__ float sqrt_common(float x) {
 #pragma clang fp contract(off)
@@ -480,7 +483,7 @@ template <class T, int K> struct SumN : expr_tag {
     return x[0];
   }
   void collect(leaf_info& li) const {
-    for (int q = 0; q < K; ++q) li.add(p[q], n_rows, n_cols);
+    for (int q = 0; q < K; ++q) li.add(p[q], n_rows, n_cols, sizeof(T));
   }
   // its K loads are issued together already
   static constexpr int kLeaves = 0;

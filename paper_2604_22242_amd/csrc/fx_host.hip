@@ -237,12 +237,12 @@ launch resolve(int kind, int elem, int64_t n_rows, int64_t n_cols, const fx_laun
 
 // Interpreted tapes want other configurations than compiled expressions:
 // the interpreter's per-instruction cost shifts the balance towards more,
-// smaller blocks.  Each default below is the single configuration with the
-// best geometric-mean time (over each item's best) on the autotuner's
-// 20,000 random training trees, per kind and storage width; on the 2,000
-// held-out trees these give 1.10x the best against 1.47x for the library
-// defaults.  Element-wise FP32 / FP64 tapes of 2^20 elements or more take
-// two vectors per thread.  Column sums keep the split heuristic when there are fewer
+// smaller blocks.  The element-wise defaults are, per storage width, the single
+// configuration with the best geometric-mean time (over each item's best) on the
+// autotuner's 20,000 random training trees, two vectors per thread for FP32 and
+// FP64 from 2^20 elements on.  Those of the reductions follow the shape, from the
+// sweeps given at each.  On the 2,000 held-out trees all of them together give
+// 1.06x the best of 145 configurations.  Column sums keep the split heuristic when there are fewer
 // columns than CUs (one block per column would leave the chip idle), and row
 // sums keep it always: 512 threads on full vectors are within 2% of the best
 // of 144 configurations on the trees swept since their kernel combines in the

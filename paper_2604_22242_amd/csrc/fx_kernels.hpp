@@ -581,12 +581,16 @@ template <class E> int check_expr(const E& e, int64_t* n_rows, int64_t* n_cols) 
   return FX_OK;
 }
 
-// Arrays that e reads.
-template <class E> int arrays_of(const E& e) { return info_of(e).arrays; }
-template <class E> int arrays_of(const Fused<E>& f) {
-  int repeats = 0;
-  for (int k = 0; k < Fused<E>::L; ++k) repeats += f.alias[k] != k;
-  return info_of(f).arrays - repeats;
+// Storage bytes per element of the distinct arrays that e reads (diagonals, one
+// element per column, not counted).
+template <class E> int bytes_of(const E& e) { return info_of(e).bytes; }
+template <class E> int bytes_of(const Fused<E>& f) {
+  leaf_id ids[Fused<E>::L];
+  int n = 0, b = info_of(f).bytes;
+  f.e.leaf_ids(ids, n);
+  for (int k = 0; k < Fused<E>::L; ++k)
+    if (f.alias[k] != k) b -= (int)ids[k].size;
+  return b;
 }
 
 // A defaulted EPT never exceeds what is compiled for the expression type.
@@ -623,7 +627,7 @@ int eval_direct(T* z, const E& e, const fx_launch* cfg, hipStream_t st) {
       // they matter)
       if constexpr (N * sizeof(T) == 16) {
         if constexpr (kNT && cached_loads_v<E>) {
-          if ((uint64_t)n * sizeof(T) * (arrays_of(e) + 1) <= kCachedLoadsUpTo) {
+          if ((uint64_t)n * (sizeof(T) + bytes_of(e)) <= kCachedLoadsUpTo) {
             hipLaunchKernelGGL((k_ew<E, T, N, EPT, kNTS, false>), dim3(L.split), dim3(L.block), 0, st, e, z, n);
             return hip_check(hipGetLastError(), "k_ew launch");
           }

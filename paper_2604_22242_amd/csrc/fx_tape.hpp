@@ -287,7 +287,7 @@ template <class T, bool BYREF = false, int SLOTS = kTapeSmallSlots> struct TapeE
     return interpret<N>(in);
   }
   void collect(leaf_info& li) const {
-    for (int q = 0; q < P().n_in; ++q) li.add(p[q], n_rows, n_cols);
+    for (int q = 0; q < P().n_in; ++q) li.add(p[q], n_rows, n_cols, sizeof(T));
     if (P().n_in == 0) li.add_shape(n_rows, n_cols);
   }
 };
