@@ -50,7 +50,8 @@
  * Workspaces: reductions that combine results across blocks take a caller
  * allocated device workspace of fx_workspace_bytes() bytes, which must be
  * zero-filled once before its first use; the library leaves it zeroed again
- * after every call (its counters reset themselves).  One workspace must not
+ * after every call (the last block clears the counters and partial sums), so
+ * calls of any kinds and shapes may use it one after another.  One workspace must not
  * be used by two calls that may run concurrently.
  */
 #ifndef FX_H
@@ -397,8 +398,8 @@ int fx_tape_eval(const fx_tape* t, fx_dtype dt, const void* const* inputs, int32
  * fx_workspace_bytes exceeds 16 MiB (of row sums under a configuration of the
  * caller's: not counting finish counters beyond one per block of rows) gives
  * FX_E_WORKSPACE before anything is enqueued.  The first call on a device looks the array's address up and
- * clears it with a kernel on `stream`; every call leaves its finish counters
- * at zero.  No call allocates: no hipMalloc, hipFree or allocating library
+ * clears it with a kernel on `stream`; every call leaves what it used at
+ * zero.  No call allocates: no hipMalloc, hipFree or allocating library
  * routine.  All calls on one GPU share the array, so calls that may overlap
  * on one GPU (different streams, or other host threads) race and must be
  * serialised by the caller. */

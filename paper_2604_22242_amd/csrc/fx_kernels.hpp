@@ -216,7 +216,10 @@ __global__ __launch_bounds__(kMaxBlock) void k_full(E e, int64_t n, typename wid
   if (threadIdx.x == 0) publish(partials + blockIdx.x, s);
   if (take_last_ticket(counter, gridDim.x)) {
     D t = 0;
-    for (unsigned b = threadIdx.x; b < gridDim.x; b += blockDim.x) t += partials[b];
+    for (unsigned b = threadIdx.x; b < gridDim.x; b += blockDim.x) {
+      t += partials[b];
+      publish(partials + b, D(0));
+    }
     t = block_sum<D>(t, lds);
     if (threadIdx.x == 0) {
       *out = static_cast<O>(M::finish(t));
@@ -286,6 +289,8 @@ __global__ __launch_bounds__(kMaxBlock) void k_colsum(E e, int64_t n_rows, int s
       out[col] = static_cast<O>(sum_strided<D>(partials + col * split, 1, split));
       reset_counter(counters + col);
     }
+    __syncthreads();
+    for (int q = threadIdx.x; q < split; q += blockDim.x) publish(partials + col * split + q, D(0));
   }
 }
 
@@ -479,7 +484,12 @@ __global__ __launch_bounds__(kMaxBlock) void k_rowsum(E e, int64_t n_rows, int64
 #pragma unroll
       for (int u = 0; u < U; ++u)
 #pragma unroll
-        for (int j = 0; j < N; ++j) sum[j] += v[u][j];
+        for (int j = 0; j < N; ++j) {
+          const int i = t % fl + fl * j;
+          sum[j] += v[u][j];
+          if (i < rows && row0 + i < n_rows && q + u * F < split)
+            publish(partials + (int64_t)(q + u * F) * n_rows + row0 + i, D(0));
+        }
     }
     // (rows / fl <= N: rl * N rows, 64 or rl of them per step unless the whole
     // tile is smaller)

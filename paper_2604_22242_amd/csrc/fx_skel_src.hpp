@@ -103,7 +103,7 @@ extern "C" __global__ __launch_bounds__(FX_BLOCK) void fx_rtc_ew(FX_PARAMS, st_t
 // wave64 butterfly and then the waves' results in order; partials are
 // published with agent-scope stores and the block that draws the last ticket
 // of an agent-scope counter adds them in index order after one acquire, then
-// clears the counter.
+// clears the counter and them.
 inline constexpr char kSums[] = R"(
 template <class C> struct fx_acc_of {
   C s = 0, c = 0;
@@ -213,7 +213,10 @@ extern "C" __global__ __launch_bounds__(FX_BLOCK) void fx_rtc_full(FX_PARAMS, lo
   if (threadIdx.x == 0) fx_publish(partials + blockIdx.x, s);
   if (fx_last_ticket(counter, gridDim.x)) {
     double t = 0;
-    for (unsigned b = threadIdx.x; b < gridDim.x; b += FX_BLOCK) t += partials[b];
+    for (unsigned b = threadIdx.x; b < gridDim.x; b += FX_BLOCK) {
+      t += partials[b];
+      fx_publish(partials + b, 0.0);
+    }
     t = fx_block_sum(t, lds);
     if (threadIdx.x == 0) {
       *out = FX_FINISH(t);
@@ -288,6 +291,8 @@ __device__ __forceinline__ void fx_colsum(FX_PARAMS, long n_rows, int split, lon
       out[col] = (acc_out_t)t;
       fx_reset(counters + col);
     }
+    __syncthreads();
+    for (int q = threadIdx.x; q < split; q += blockDim.x) fx_publish(partials + col * split + q, 0.0);
   }
 }
 extern "C" __global__ __launch_bounds__(FX_BLOCK) void fx_rtc_colsum_v(FX_PARAMS, long n_rows, int split,
@@ -393,7 +398,12 @@ __device__ __forceinline__ void fx_rowsum(FX_PARAMS, long n_rows, long n_cols, i
 #pragma unroll
       for (int u = 0; u < U; ++u)
 #pragma unroll
-        for (int j = 0; j < N; ++j) sum[j] += v[u][j];
+        for (int j = 0; j < N; ++j) {
+          const int i = t % fl + fl * j;
+          sum[j] += v[u][j];
+          if (i < rows && row0 + i < n_rows && q + u * F < split)
+            fx_publish(partials + (long)(q + u * F) * n_rows + row0 + i, 0.0);
+        }
     }
 #pragma unroll
     for (int j = 0; j < N; ++j)

@@ -6,8 +6,8 @@
 // process.  In host code the array's name is only a stand-in for the symbol,
 // so the first call on a device looks its device address up
 // (hipGetSymbolAddress) and clears the array with a fill kernel on the
-// caller's stream; after that the finish counters are left at zero by every
-// call, like a caller's workspace.  No call allocates device or pinned
+// caller's stream; after that every call leaves what it used at zero, like a
+// caller's workspace.  No call allocates device or pinned
 // memory.  Calls that overlap on one GPU share the array and race.
 #include <mutex>
 

@@ -16,8 +16,10 @@ LIB = os.path.join(HERE, "native", "libuser_views.so")
 
 def _lib():
     import paper_2604_22242_amd as fx
+    from paper_2604_22242_amd import build
+    if not os.path.exists(fx.LIB_PATH):
+        build.build()
     if not os.path.exists(LIB):
-        from paper_2604_22242_amd import build
         build.build_user(SRC, LIB)
     fx.lib()
     return ctypes.CDLL(LIB)
