@@ -37,12 +37,10 @@
  *   - An element-wise output may be exactly one of the inputs (in place);
  *     partial overlap is not allowed.
  *   - Inputs are read with streaming (nontemporal) loads, except by compiled
- *     element-wise calls and strided views whose distinct inputs and output
- *     together are at most 256 MiB (MI355X's last-level cache), by views with
- *     transposed parts above 640 MiB whose columns are no whole cache lines, and
- *     by sums of short columns: these leave the inputs in that cache.  (Views of
- *     submatrices whose columns start at multiples of 16 KB stream already from
- *     176 MiB, and between 32 and 64.)  An element-wise output
+ *     element-wise calls whose distinct inputs and output together are at most
+ *     256 MiB (MI355X's last-level cache), by strided views that are small or
+ *     whose tiles share cache lines, and by sums of short columns: these leave
+ *     the inputs in that cache.  An element-wise output
  *     larger than 256 MiB that is written with 16-byte vectors is written with
  *     streaming stores, so it is not left in that cache; smaller outputs use
  *     ordinary stores.

@@ -281,25 +281,31 @@ template <class C, class G, bool NTL> struct tile_ctx {
   int64_t r0, c0;
 };
 
-// Cache policy of the direct leaves, by the bytes of all arrays and by where the
-// columns start (sums of two and four submatrices, "2" and "4"; the 10000 x
-// 10000 expressions expr1 and expr2; us with streaming against ordinary loads).
-//  * All that fits the 256 MiB last-level cache takes ordinary loads, which leave
-//    it there for the next call: FP32 4900 x 4900 "4" 23.9 against 18.5, 3000 x
-//    3000 expr1 26 and 21; FP64 6000 x 6000 "2" (216 MB) 36.6 and 31.4.
-//  * More takes streaming loads: FP32 10000 x 10000 "4" 92 and 100, 4096 x 4096
-//    expr2 (335 MB) 52 and 67.
-//  * With transposed parts and columns that are no whole number of cache lines,
-//    the lines that the runs straddle are read again by the tile beside; far
-//    beyond the cache those reads decide, and ordinary loads are the better ones
-//    again: FP32 10000 x 10000 expr1 267 and 250, FP64 5999 x 5999 expr2 300 and
-//    293 (864 MB), but FP64 5000 x 5000 expr1 (600 MB) 111 and 130.
-//  * Columns of submatrices that start at multiples of 16 KB share a few sets of
-//    the caches, and hold less in them: streaming from 176 MiB on (FP32 8192 x
-//    8192 "2", 201 MB: 33 and 37), and between the 32 MB of the eight L2 caches
-//    and 64 MiB (FP32 4096 x 4096 "2": 9.4 and 10.7, 16384 x 1000 8.0 and 8.6).
+// Cache policy of the direct leaves, by the bytes of the distinct arrays and the
+// output, and by where the columns start.  Ordinary loads leave the data in the
+// last-level cache for the next call on them, and serve the second read of a line
+// that two runs straddle; streaming loads leave that cache to the output.  us
+// with streaming against ordinary loads, on inputs that change from call to call
+// (repeated):
+//  * with transposed parts and columns of whole cache lines, streaming from 176
+//    MiB on (FP32 3040 x 3040 expr2, 176 MiB: 40.3, 41.1 (31.5, 28.4); 4096 x 4096,
+//    320 MiB: 52, 67 repeated), in paired tiles, which read an array once, from
+//    104 MiB (3040 x 3040 expr1, 106 MiB: 23.4, 28.5 (22.9, 20.2); 4096 x 4096 40.2,
+//    47.1 (39.2, 32.2));
+//  * with columns that are no whole lines, ordinary ones at any size, for the lines
+//    read by two tiles (FP32 7000 x 7000 expr1 171, 149; FP64 5000 x 5000 153, 134;
+//    FP32 10000 x 10000 expr1 267, 250 repeated);
+//  * submatrices, whose runs are long: streaming from 176 MiB with whole lines
+//    (FP32 8192 x 8192 "2", a sum of two, 192 MiB: 33, 37 repeated), from twice
+//    that without (10000 x 10000 "2", 286 MiB: 50.4, 46.7 repeated; "4", 477 MiB:
+//    92, 100).  Up to there what ordinary loads win on repeated inputs they lose on
+//    new ones (FP64 4096 x 4096 "2" 18.0, 21.6 (17.1, 15.6));
+//  * submatrices whose columns start at multiples of 16 KB, which share a few sets
+//    of the caches, stream as well between the 32 MB of the eight L2 caches and 64
+//    MiB (FP32 4096 x 4096 "2": 12.7, 13.8 (9.4, 10.7); 16384 x 1000 8.0, 8.6
+//    repeated).
 constexpr uint64_t kMiB = uint64_t(1) << 20;
-constexpr uint64_t kStraddledBelow = 640 * kMiB, kSetsBelow = 176 * kMiB, kSetsFrom = 32 * kMiB,
+constexpr uint64_t kStreamFrom = 176 * kMiB, kStreamPairsFrom = 104 * kMiB, kSetsFrom = 32 * kMiB,
                    kSetsTo = 64 * kMiB;
 constexpr int kSetsPitch = 16384;
 
@@ -795,8 +801,8 @@ int eval_views(T* z, const E& e, hipStream_t st) {
   arrays_in(e, in);
   const uint64_t total = bytes + (uint64_t)rows * (uint64_t)cols * in.bytes;
   const bool few_sets = KT == 0 && sets && total > kSetsFrom;
-  const bool ntl = few_sets ? total <= kSetsTo || total > kSetsBelow
-                            : total > kCachedLoadsUpTo && (KT == 0 || lines || total <= kStraddledBelow);
+  const uint64_t from = KT == 0 ? (lines ? 1 : 2) * kStreamFrom : pairable<E, T>::value ? kStreamPairsFrom : kStreamFrom;
+  const bool ntl = total > from ? KT == 0 || lines : few_sets && total <= kSetsTo;
   auto with_policy = [&](auto&& go) {
     if (ntl) return nts ? go(std::true_type{}, std::true_type{}) : go(std::true_type{}, std::false_type{});
     return nts ? go(std::false_type{}, std::true_type{}) : go(std::false_type{}, std::false_type{});

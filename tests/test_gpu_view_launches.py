@@ -65,9 +65,8 @@ def test_narrow_and_short(which, dtype, shape):
     _check(which, dtype, *shape)
 
 
-# ordinary and streaming loads on both sides of 256 MiB, of 640 MiB (columns that
-# are no whole cache lines) and of 176 MiB (columns at multiples of 16 KB); the
-# wide tile of transposed parts
+# ordinary and streaming loads, by size and by whether columns are whole cache
+# lines; the wide tile of transposed parts
 @pytest.mark.parametrize("which,dtype,m", [
     ("expr1", "f32", 3104), ("expr1", "f32", 5000), ("expr1", "f32", 5856), ("expr1", "f32", 7500),
     ("expr1", "f64", 3001), ("expr1", "f64", 4112), ("expr1", "bf16", 6700),
