@@ -202,7 +202,8 @@ __device__ __forceinline__ D block_sum(D v, D* lds) {
 // write-back (an agent-scope release fence), which would cost one per block.
 // That block also clears what it has read, the partials as well as the counter:
 // the next call on the workspace, of another kind or shape, may have its counters
-// where this one had partials.
+// where this one had partials.  Ordinary stores do: the end of the kernel writes
+// them back.
 
 template <class D> __device__ __forceinline__ void publish(D* p, D v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

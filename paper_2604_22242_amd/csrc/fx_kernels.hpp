@@ -218,7 +218,7 @@ __global__ __launch_bounds__(kMaxBlock) void k_full(E e, int64_t n, typename wid
     D t = 0;
     for (unsigned b = threadIdx.x; b < gridDim.x; b += blockDim.x) {
       t += partials[b];
-      publish(partials + b, D(0));
+      partials[b] = D(0);
     }
     t = block_sum<D>(t, lds);
     if (threadIdx.x == 0) {
@@ -290,7 +290,7 @@ __global__ __launch_bounds__(kMaxBlock) void k_colsum(E e, int64_t n_rows, int s
       reset_counter(counters + col);
     }
     __syncthreads();
-    for (int q = threadIdx.x; q < split; q += blockDim.x) publish(partials + col * split + q, D(0));
+    for (int q = threadIdx.x; q < split; q += blockDim.x) partials[col * split + q] = D(0);
   }
 }
 
@@ -356,8 +356,10 @@ __global__ __launch_bounds__(kMaxBlock) void k_colsum_thin(E e, int64_t n_rows, 
 
 // Lanes that share a column: a wave's 64, n_rows in vectors of `vec` elements where
 // that is less, and fewer (down to 128-byte runs) where that gives the finish at
-// least 16 row tiles to work on, 4 from 2^24 elements on, where longer runs matter
-// more (500 x 134217 FP64 315 us with 8 lanes, 257 with 32; 512 x 8192 21 and 23).
+// least 16 row tiles to work on; 4 from 2^24 elements on, where longer runs matter
+// more (500 x 134217 FP64 315 us with 8 lanes, 257 with 32; 512 x 8192 21 and 23),
+// but for half storage, whose tiles have the most rows (6001 x 2999 FP16 35 us with
+// 32 lanes, 40 with 64; 1000 x 16777 BF16 32 with 16, 49 with 64).
 // 32 where 64 make
 //  * between half a row tile and one per CU: then every tile is whole, in one
 //    block, and needs no finish (50000 x 20 FP32 5 us against 17, 100000 x 64 BF16 13
@@ -379,7 +381,7 @@ constexpr int64_t kRowsumLarge = int64_t(1) << 24;
 inline int rowsum_lanes(int64_t n_rows, int64_t n_cols, int vec, int elem, int block) {
   int rl = 1;
   while (rl < 64 && (int64_t)rl * vec < n_rows) rl *= 2;
-  const int64_t least = n_rows * n_cols < kRowsumLarge ? kRowsumMinTiles : kRowsumLargeTiles;
+  const int64_t least = elem == 2 || n_rows * n_cols < kRowsumLarge ? kRowsumMinTiles : kRowsumLargeTiles;
   while (rl > kRowsumMinLanes && n_rows < least * rl * vec) rl /= 2;
   if (rl < 64) return rl;
   const int64_t cus = device_cus();
@@ -484,12 +486,7 @@ __global__ __launch_bounds__(kMaxBlock) void k_rowsum(E e, int64_t n_rows, int64
 #pragma unroll
       for (int u = 0; u < U; ++u)
 #pragma unroll
-        for (int j = 0; j < N; ++j) {
-          const int i = t % fl + fl * j;
-          sum[j] += v[u][j];
-          if (i < rows && row0 + i < n_rows && q + u * F < split)
-            publish(partials + (int64_t)(q + u * F) * n_rows + row0 + i, D(0));
-        }
+        for (int j = 0; j < N; ++j) sum[j] += v[u][j];
     }
     // (rows / fl <= N: rl * N rows, 64 or rl of them per step unless the whole
     // tile is smaller)
@@ -499,6 +496,10 @@ __global__ __launch_bounds__(kMaxBlock) void k_rowsum(E e, int64_t n_rows, int64
     __syncthreads();
     for (int i = t; i < rows; i += blockDim.x)
       if (row0 + i < n_rows) out[row0 + i] = static_cast<O>(sum_groups(lds, rows, i, F));
+    // (a loop of its own: beside the loads above it costs the whole kernel
+    // registers, 8192 x 8192 BF16 152 us against 93)
+    for (int i = t % fl; i < rows && row0 + i < n_rows; i += fl)
+      for (int q = f; q < split; q += F) partials[(int64_t)q * n_rows + row0 + i] = D(0);
     if (t == 0) reset_counter(counters + tile);
   }
 }

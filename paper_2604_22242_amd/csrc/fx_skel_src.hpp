@@ -215,7 +215,7 @@ extern "C" __global__ __launch_bounds__(FX_BLOCK) void fx_rtc_full(FX_PARAMS, lo
     double t = 0;
     for (unsigned b = threadIdx.x; b < gridDim.x; b += FX_BLOCK) {
       t += partials[b];
-      fx_publish(partials + b, 0.0);
+      partials[b] = 0.0;
     }
     t = fx_block_sum(t, lds);
     if (threadIdx.x == 0) {
@@ -292,7 +292,7 @@ __device__ __forceinline__ void fx_colsum(FX_PARAMS, long n_rows, int split, lon
       fx_reset(counters + col);
     }
     __syncthreads();
-    for (int q = threadIdx.x; q < split; q += blockDim.x) fx_publish(partials + col * split + q, 0.0);
+    for (int q = threadIdx.x; q < split; q += blockDim.x) partials[col * split + q] = 0.0;
   }
 }
 extern "C" __global__ __launch_bounds__(FX_BLOCK) void fx_rtc_colsum_v(FX_PARAMS, long n_rows, int split,
@@ -398,12 +398,7 @@ __device__ __forceinline__ void fx_rowsum(FX_PARAMS, long n_rows, long n_cols, i
 #pragma unroll
       for (int u = 0; u < U; ++u)
 #pragma unroll
-        for (int j = 0; j < N; ++j) {
-          const int i = t % fl + fl * j;
-          sum[j] += v[u][j];
-          if (i < rows && row0 + i < n_rows && q + u * F < split)
-            fx_publish(partials + (long)(q + u * F) * n_rows + row0 + i, 0.0);
-        }
+        for (int j = 0; j < N; ++j) sum[j] += v[u][j];
     }
 #pragma unroll
     for (int j = 0; j < N; ++j)
@@ -411,6 +406,8 @@ __device__ __forceinline__ void fx_rowsum(FX_PARAMS, long n_rows, long n_cols, i
     __syncthreads();
     for (int i = t; i < rows; i += FX_BLOCK)
       if (row0 + i < n_rows) out[row0 + i] = (acc_out_t)fx_groups(lds, rows, i, F);
+    for (int i = t % fl; i < rows && row0 + i < n_rows; i += fl)
+      for (int q = f; q < split; q += F) partials[(long)q * n_rows + row0 + i] = 0.0;
     if (t == 0) fx_reset(counters + tile);
   }
 }
