@@ -374,9 +374,10 @@ int32_t fx_tape_program(const fx_tape* t, uint16_t* op, uint8_t* slot, uint8_t* 
  * accu / norm 512 threads (128 between one tile of those and 2^17 elements),
  * EPT 2 (1 for half types), a block per tile up to 2 per CU;
  * column sums up to 256 threads (512 with fewer columns than CUs, and with at
- * most two per CU of less than 16384 rows; no more than the column has work for), EPT 2 (1 for half types), one block per column
- * when there are at least as many columns as CUs; row sums 512 threads,
- * EPT 2 (1 for half types).  The split default applies
+ * most two per CU of half types or of less than 65536 rows; no more than the
+ * column has work for), EPT 2 (1 for half types), one block per column when
+ * there are at least as many columns as CUs; row sums 512 threads, EPT 2 (1 for
+ * half types).  The split default applies
  * only when all of cfg is 0 (or cfg is NULL); then a model attached with
  * fx_tape_set_model chooses instead.  Tapes are compiled for EPT 1, 2 and 4
  * and for vectors of one element, 8 or 16 bytes: other explicit values give

@@ -113,12 +113,19 @@ static constexpr int64_t kHeldTwoFrom = (int64_t)1 << 24;
 // so no more threads than take ept vectors each; with few columns, whose blocks
 // do not fill the chip, than take one.  A column of half storage takes twice its 256
 // threads where there are one or two whole columns per CU (8192 x 512 BF16 11.4,
-// 8.8; longer ones are chunked, and run as fast with 256: 65536 x 64 13.6 and 13.9).
-static constexpr int64_t kLongColumn = 16384;
+// 8.4; 20000 x 400 25, 16.6; 65536 x 512 71, 45); chunked ones run as fast with 256
+// (65536 x 64 13.6 and 13.9).
+// With a column per CU or more chunks pay only where the columns are long and hardly
+// more than one per CU (65536 x 256 BF16 31 us in 4 chunks, 38 whole; 65536 x 400 47 and
+// 44, 65536 x 512 56 and 45, 12000 x 700 32 and 18): each column has a finish.
+static constexpr int64_t kLongColumn = 65536;
+static bool long_columns(int64_t n_rows, int64_t n_cols) {
+  return n_rows >= kLongColumn && 2 * n_cols < 3 * (int64_t)device_cus();
+}
 static fx_launch colsum_launch(int elem, int64_t n_rows, int64_t n_cols, int block, int ept) {
   const int vec = 16 / elem;
   const int64_t cus = device_cus();
-  if (elem == 2 && n_cols >= cus && n_cols <= 2 * cus && n_rows < kLongColumn) block = 512;
+  if (elem == 2 && n_cols >= cus && n_cols <= 2 * cus && !long_columns(n_rows, n_cols)) block = 512;
   const int64_t each = (int64_t)vec * (n_cols < 4 * cus ? 1 : ept);
   int b = 64;
   while (b < block && b * each < n_rows) b *= 2;
@@ -128,10 +135,14 @@ static fx_launch colsum_launch(int elem, int64_t n_rows, int64_t n_cols, int blo
 // columns per CU.
 // Matrix workload, a thread against a wave per column, us:
 //   2^26 elements    FP32 17 rows 255, 1340, 32 rows 529, 707
-//                    FP64  9 rows 489, 3645, 16 rows 1109, 2036, 32 rows 1052, 1029
+//                    FP64  9 rows 489, 3645, 16 rows 1050, 2039, 28 rows 1030, 1188,
+//                          32 rows 1348, 1030
 //                    BF16 17 rows 138, 2263, 32 rows 193, 1191
 //   2^16 elements    FP32 17 rows (3855 columns) 4.0, 4.1, 32 rows (2048) 5.3, 3.5
-//                    FP64 10 rows (6553) 4.2, 6.1, 16 rows (4096) 5.4, 4.8
+//                    FP64 10 rows (6553) 4.2, 6.1, 12 rows (5461) 5.5, 5.9, 16 rows
+//                          (4096) 6.7, 4.8 (6144) 6.9, 5.7 (8192) 6.9, 6.6 (65536) 8.6, 34
+// (FP64 loses up to 2 us at the line's lower end and a quarter at 32 rows of a
+// power of two of columns; one line serves all types.)
 // (In FP32 the two meet again at 40 to 48 rows, in BF16 beyond 64.)  No other
 // launch reaches 2^26 columns: a grid has fewer than 2^32 threads.
 constexpr int64_t kThinColumnBytes = 64, kThinRows = 32, kThinColumnsPerCU = 16;
@@ -188,22 +199,25 @@ launch resolve(int kind, int elem, int64_t n_rows, int64_t n_cols, const fx_laun
       } else {
         // Chunks only where there are fewer columns than CUs (each column
         // combined across blocks costs its last block some microseconds: 4096 x
-        // 1024 FP32 11 us whole, 16 in two chunks) and a column is at least two
-        // full passes of the block long, a pass or part of one each; about a
+        // 1024 FP32 11 us whole, 16 in two chunks) and a column is at least five
+        // full passes of the block long, two of half storage and with fewer than 64
+        // columns (whole and in chunks: 10000 x 104 FP32 7.1 us and 12.5, FP64 11.2 and
+        // 14.8; 10000 x 6 FP64 8.8 and 6.6, 20000 x 60 FP64 18.3 and 13.3, FP32 10.6 and
+        // 10.8), a pass or part of one each; about a
         // block per CU, two from 64 columns on (32768 x 128 FP32 13.3 us with 8
         // chunks, 18.1 with 16; 2^22 x 1 21 us with 256, 71 with 2048).
         const int64_t pass = (int64_t)L.block * vec16;
         const int64_t target = ncol * 4 >= cus ? 2 * cus : cus;
-        s = ncol >= cus || n_rows < 2 * pass * L.ept ? 1 : ceil_div(target, ncol);
+        s = ncol >= cus || n_rows < (elem == 2 || ncol * 4 < cus ? 2 : 5) * pass * L.ept ? 1 : ceil_div(target, ncol);
         s = std::min<int64_t>(s, ceil_div(n_rows, pass));
         // Half storage does twice the arithmetic per byte and wants the waves: up
         // to 8 blocks per CU of at least two passes each, at most 64 chunks, which
         // the finish reads one after another (matrix workload BF16 2^20 x 16 34 us
         // with 64 chunks, 66 with 16; 2^20 x 64 88 with 32, 145 with 8; 65536 x 256
-        // 25.6 with 8, 37.5 whole; 200000 x 255 68 with 9, 88 with 3).
+        // 31 with 8, 38 whole; 200000 x 255 68 with 9, 88 with 3).
         // Expressions of three functions or more likewise (262144 x 256 FP32, that expression,
         // 170 us with 8, 201 whole).
-        if ((elem == 2 || funcs >= 3) && ncol < 4 * cus)
+        if ((elem == 2 || funcs >= 3) && (ncol < cus || long_columns(n_rows, ncol)))
           s = std::max<int64_t>(s, std::min<int64_t>({ceil_div(8 * cus, ncol), n_rows / (2 * pass), 64}));
       }
       L.split = (int)std::max<int64_t>(1, std::min<int64_t>(s, 65535));
@@ -271,10 +285,10 @@ fx_launch tape_launch(int kind, int elem, int64_t n_rows, int64_t n_cols, const 
     }
     case FX_R_COLSUM:
       // 512 threads with at most two columns per CU, as above 256 (8192 x 512 FP32
-      // 15.8 us with 256, 12.3; 65536 x 512 80.5, 89.6); fewer for short columns (128
-      // x 32768 FP32 109 us, 24)
+      // 15.8 us with 256, 12.3; 65536 x 512 BF16 101, 59, but FP64 155, 169); fewer for
+      // short columns (128 x 32768 FP32 109 us, 24)
       d = fx_launch{256, half ? 1 : 2, 16, 0};
-      if (all_default) d = colsum_launch(elem, n_rows, n_cols, n_cols < cus || (n_cols <= 2 * cus && n_rows < kLongColumn) ? 512 : 256, half ? 1 : 2);
+      if (all_default) d = colsum_launch(elem, n_rows, n_cols, n_cols < cus || (n_cols <= 2 * cus && (half || n_rows < kLongColumn)) ? 512 : 256, half ? 1 : 2);
       d.split = n_cols >= cus ? 1 : 0;
       break;
     case FX_R_ROWSUM: d = fx_launch{512, half ? 1 : 2, 16, 0}; break;

@@ -52,6 +52,29 @@ def test_column_chunks_of_the_caller(fx):
         assert fx.fx_workspace_bytes(fx.R_COLSUM, fx.F32, (rows, 8158790), (0, 0, 0, 8)) == 0
 
 
+def test_whole_columns(fx):
+    """Columns are chunked where there are fewer than CUs and each is five passes
+    of its block long (two of half storage and below 64 columns), or where half-storage columns are
+    long and hardly more than one per CU; up to two per CU take 512 threads whole."""
+    def launch(dt, rows, cols, cfg=(0, 0, 0, 0)):
+        return fx.fx_resolve_launch(fx.R_COLSUM, dt, (rows, cols), cfg)
+
+    for rows, cols in ((10000, 419), (20000, 400), (65536, 512), (65535, 256), (65536, 384)):
+        assert launch(fx.BF16, rows, cols)[::3] == (512, 1), (rows, cols)
+    # more columns, and the 256 threads that generated kernels start from
+    for rows, cols in ((12000, 700), (16384, 700), (65536, 700)):
+        assert launch(fx.BF16, rows, cols)[3] == 1, (rows, cols)
+    for rows, cols in ((10000, 419), (65535, 300)):
+        assert launch(fx.BF16, rows, cols, (256, 1, 0, 0))[3] == 1, (rows, cols)
+    for rows, cols in ((65536, 256), (65536, 383), (65536, 255), (8192, 104)):
+        assert launch(fx.BF16, rows, cols)[3] > 1, (rows, cols)
+    for dt, passes in ((fx.F32, 512 * 4 * 2), (fx.F64, 512 * 2 * 2)):
+        assert launch(dt, 5 * passes - 1, 104)[3] == 1
+        assert launch(dt, 5 * passes, 104)[3] == 5
+        assert launch(dt, 2 * passes - 1, 63)[3] == 1
+        assert launch(dt, 2 * passes, 63)[3] > 1
+
+
 FAKE = 0x10000
 C2 = [("leaf", -1, -1, 0, 0.0), ("leaf", -1, -1, 1, 0.0), ("add", 0, 1, -1, 0.0)]
 
