@@ -334,14 +334,16 @@ __global__ __launch_bounds__(64) void k_mlp_params(mlp_dims d, int B, const floa
 
 // Inference: a group of threads takes RR rows at a time, so that one read of a
 // weight serves RR independent chains, from weights staged once per block.  Up to
-// 16 waves per CU (64 of models whose weights are not staged) each row has a
+// 16 waves per CU (64 of models whose weights are neither staged nor over 96 KiB) each row has a
 // group and a block of its own, which reads the weights from the caches: the
 // chip is not full, and staging, or four rows one after another, only adds its
 // latency (25-64-14 model, through the binding: 256 rows 8.1 us against 9.9,
 // 4096 8.3 and 9.0, 20000 23.8 and 16.3; 64-256-64 256 rows 9.5 and 18.3, 4096 63 and
 // 23; 25-200-63, not staged, 256 rows 10 and 28, 4096 28 and 31, 20000 146 and 128).
+// Rows of their own read the weights from the L2 again each: over 96 KiB that bounds
+// them from 1024 rows on (64-256-64, 1024 rows 18 us both ways).
 constexpr int kMlpForwardRows = 4;
-constexpr int kMlpSingleWaves = 16, kMlpSingleWavesUnstaged = 64;
+constexpr int kMlpSingleWaves = 16, kMlpSingleWavesUnstaged = 64, kMlpLargeFloats = 24 * 1024;
 template <int RR, bool STAGED>
 __global__ __launch_bounds__(256) void k_mlp_forward(mlp_dims d, mlp_launch L, int B,
                                                    const float* __restrict__ X,
@@ -682,7 +684,8 @@ int fx_model_forward(const fx_model* m, const float* d_X, int32_t batch, float* 
   if (batch == 0) return FX_OK;
   const mlp_dims& d = m->d;
   mlp_launch L = mlp_shape(d);
-  const int64_t single = (int64_t)device_cus() * (L.weights ? kMlpSingleWaves : kMlpSingleWavesUnstaged);
+  const bool many = !L.weights && d.H * L.p1 + d.C * L.p2 <= kMlpLargeFloats;
+  const int64_t single = (int64_t)device_cus() * (many ? kMlpSingleWavesUnstaged : kMlpSingleWaves);
   if ((int64_t)batch * (L.tpr / 64) <= single) {
     L.groups = 1;
     L.weights = 0;
